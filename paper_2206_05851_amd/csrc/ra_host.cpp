@@ -55,6 +55,7 @@ struct ra_ctx {
     int64_t* dstep = nullptr;
     double* src = nullptr;          // [sum_g N_g][3] centre-of-mass frame of the clone source
     int64_t* drep_off = nullptr;    // [n_groups + 1] first replica of each group
+    unsigned long long* event_queue = nullptr;   // [n_groups][2] work queues of ra_mftu_events
     int64_t n_reps = 0;
     hipEvent_t ev_parent = nullptr, ev_reclone = nullptr;   // RSF cycle across two streams
     int64_t step = 0;
@@ -243,7 +244,8 @@ void ra_destroy(ra_ctx* c) {
     // pos[1] points into the pos[0] allocation and is not freed on its own
     void* ptrs[] = {c->dgroups, c->ditems, c->dtiles, c->dpar_off, c->ditem_begin, c->state, c->pos[0],
                     c->samples, c->tsf, c->tsf_acc, c->ckpt, c->segbuf, c->dseg_off,
-                    c->partial, c->lam_mu, c->status, c->clamps, c->dstep, c->src, c->drep_off};
+                    c->partial, c->lam_mu, c->status, c->clamps, c->dstep, c->src, c->drep_off,
+                    c->event_queue};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->ev_parent) (void)hipEventDestroy(c->ev_parent);
@@ -420,6 +422,7 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
     ALLOC(c->dstep, 1);
     ALLOC(c->src, par);
     ALLOC(c->drep_off, n_groups + 1);
+    ALLOC(c->event_queue, 2 * n_groups);
     if (run->plain) {
         ALLOC(p8, 2 * c->pos_total * esz);
         c->pos[0] = p8;
@@ -841,7 +844,7 @@ ra_status ra_mftu_events(ra_ctx* c, const double* rates, int64_t n_windows, int3
     for (const auto& g : c->hgroups) max_springs = std::max(max_springs, g.N - 1);
     HIPCHK(c, launch_mftu_events(c->dgroups, ng, rates, n_windows, c->spr_total, n_trials, max_windows,
                                  c->run.sample_every, (uint32_t)c->run.seed, (uint32_t)(c->run.seed >> 32),
-                                 max_springs, first_window, mftu, c->stream));
+                                 max_springs, first_window, c->event_queue, mftu, c->stream));
     return RA_OK;
 }
 

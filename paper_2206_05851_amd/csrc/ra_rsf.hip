@@ -312,64 +312,154 @@ __device__ __forceinline__ uint64_t event_threshold(double p) {
     return (uint64_t)ceil((x - 1.0) * 0.5);
 }
 
-// Thresholds in LDS, one workgroup of four wavefronts per (trial, group):
-// thread t takes window base + t, so lane order within a wavefront and the
-// wavefront index are window order; every thread draws all springs of its
-// window. The earliest window with a vote in any wavefront ends the trial for
-// the whole workgroup.
+// Thresholds in LDS. The windows of a trial are cut into
+// segments, and the workgroups of a group take (segment, trial) tickets from a
+// queue, segment-major, so that all live trials advance together and the last
+// ones are shared by the whole chip (trials last exponentially long: with one
+// workgroup per trial the longest of 1024 kept a few SIMDs busy for most of
+// the call). A ticket whose trial already has an event in an earlier window is
+// skipped; tickets come in segment order, so once every trial has an event all
+// further tickets are dead and the workgroup leaves (the count is read before
+// the ticket is taken: an event known by then came from an earlier ticket). first[]
+// holds the least window found so far (atomicMin: the result does not depend on
+// the order of the work).
+//
+// A thread draws all springs of its EVENT_WPT windows. Of the Philox block only
+// the first word is computed: m < t needs word 0 = m >> 20 <= (t - 1) >> 20, which
+// a draw meets about as rarely as it unfolds (1e-7 here); a wavefront where some
+// lane meets it recomputes the block and compares all 52 bits. With the spring
+// and the trial uniform, rounds 1-3 cost four VALU instructions: what depends
+// on the window alone is computed once per window, what depends on the spring
+// alone once per spring for both windows.
+// Bound by VALU issue: 34.5 instructions per draw. 1024 trials of up to 2^20
+// windows of 49 springs, 1.06e10 draws: 38.8 ms with a workgroup per trial and
+// whole blocks, 10.4 ms now, against 9.6 ms for the instructions at full rate.
+// With one segment of four rounds per ticket (5e5 tickets) it took 26.1 ms: the
+// atomics on the queue's address, about 50 ns each, bound it.
 constexpr int EVENT_THREADS = 256;
-constexpr size_t EVENT_LDS_MAX = 32 << 10;   // thresholds in LDS up to this size, else the kernel below
+constexpr int EVENT_WPT = 2;                       // windows per thread and round
+constexpr int EVENT_MOST_ROUNDS = 32;              // most rounds of a ticket
+constexpr int EVENT_ROUND = EVENT_THREADS * EVENT_WPT;   // windows of a round
+constexpr size_t EVENT_LDS_MAX = 32 << 10;   // table of 64-bit thresholds up to this size, else the kernel below
+constexpr unsigned long long EVENT_NONE = ~0ull;   // no event found
+constexpr uint32_t EVENT_NEVER = 0x80000000u;      // the threshold 0: no draw unfolds
+constexpr int EVENT_BLOCKS = 2048;                 // workgroups of a launch: 8 on each of 256 CUs
+
+// The queue of group g: queue[2 g] the next ticket, queue[2 g + 1] the trials
+// that have an event.
+__global__ void event_setup_kernel(unsigned long long* __restrict__ first, int64_t n_first,
+                                   unsigned long long* __restrict__ queue, int n_groups) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t; i < n_first; i += stride) first[i] = EVENT_NONE;
+    for (int64_t i = t; i < 2 * (int64_t)n_groups; i += stride) queue[i] = 0;
+}
+
+// What of the block (v, j, trial, ctr3) depends on the window v alone.
+struct EventWindow {
+    uint32_t a, b, c, d;   // lo(p0), lo(p1) ^ k0[2], hi and lo(p2): the window's products of rounds 1-3
+};
+
+__device__ __forceinline__ EventWindow event_window(uint32_t v, uint32_t trial, uint32_t ctr3, const RoundKeys& k) {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * v, q1 = (uint64_t)0xCD9E8D57u * trial;
+    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ ctr3 ^ k.k1[0];           // round 1
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * n2;                      // round 2
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ (uint32_t)q1 ^ k.k0[1];
+    const uint64_t p2 = (uint64_t)0xD2511F53u * n0;                      // round 3
+    return EventWindow{(uint32_t)p0, (uint32_t)p1 ^ k.k0[2], (uint32_t)(p2 >> 32), (uint32_t)p2};
+}
+
+// Word 0 of the block: sa = hi(M0 n0) ^ k1[1] and sb = lo(M0 n0) ^ k1[2] of the
+// spring, with n0 = hi(M1 trial) ^ j ^ k0[0] its first word after round 1.
+__device__ __forceinline__ uint32_t event_word0(const EventWindow& w, uint32_t sa, uint32_t sb, const RoundKeys& k) {
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (w.a ^ sa);              // rounds 2 and 3
+    uint32_t c0 = (uint32_t)(p1 >> 32) ^ w.b, c1 = (uint32_t)p1, c2 = w.c ^ sb, c3 = w.d;
+#pragma unroll
+    for (int r = 3; r < 10; ++r) {
+        const uint64_t a = (uint64_t)0xD2511F53u * c0, b = (uint64_t)0xCD9E8D57u * c2;
+        c0 = xor3((uint32_t)(b >> 32), c1, k.k0[r]);
+        c2 = xor3((uint32_t)(a >> 32), c3, k.k1[r]);
+        c1 = (uint32_t)b;
+        c3 = (uint32_t)a;
+    }
+    return c0;
+}
 
 __global__ __launch_bounds__(EVENT_THREADS) void first_event_lds_kernel(
     const GroupDev* __restrict__ groups, const double* __restrict__ rates, int64_t n_windows, int64_t spr_total,
-    int64_t max_windows, int S, uint32_t key0, uint32_t key1, int64_t* __restrict__ first_window, int n_groups) {
-    extern __shared__ uint64_t thr[];   // [n_windows][N - 1]
-    __shared__ int64_t found[EVENT_THREADS / WAVE];
-    const int trial = blockIdx.x;
+    int n_trials, int64_t max_windows, int rounds, int S, uint32_t key0, uint32_t key1,
+    unsigned long long* __restrict__ first, unsigned long long* __restrict__ queue, int n_groups) {
+    extern __shared__ uint32_t thr[];   // [2][n_windows][N - 1]: upper 32 and lower 20 bits of t - 1
+    __shared__ unsigned long long ticket;
     const int g = blockIdx.y;
     const GroupDev& G = groups[g];
     const int tid = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & (WAVE - 1);
     const int nm1 = G.N - 1;
     const double window_time = (double)S * G.dt;
     const uint32_t ctr3 = (2u << 24) | (G.stream & 0xFFFFFFu);
-    const RoundKeys keys = round_keys<false>(key0, key1);
-    const int64_t n_thr = n_windows * nm1;
-    for (int64_t i = tid; i < n_thr; i += EVENT_THREADS) {
-        const int64_t w = i / nm1, j = i - w * nm1;
+    const RoundKeys keys = round_keys(key0, key1);
+    const int n_thr = (int)n_windows * nm1;
+    for (int i = tid; i < n_thr; i += EVENT_THREADS) {
+        const int w = i / nm1, j = i - w * nm1;
         const double k = rates[w * spr_total + G.spr_off + j];
-        thr[i] = event_threshold(-expm1(-k * window_time));
+        const uint64_t t = event_threshold(-expm1(-k * window_time));
+        thr[i] = t ? (uint32_t)((t - 1) >> 20) : 0u;
+        thr[n_thr + i] = t ? (uint32_t)(t - 1) & 0xFFFFFu : EVENT_NEVER;
     }
-    __syncthreads();
     const uint32_t nw = (uint32_t)n_windows;
-    for (int64_t base = 0; base < max_windows; base += EVENT_THREADS) {
-        const int64_t v = base + tid;
-        bool hit = false;
-        if (v < max_windows) {
-            const uint64_t* tw = thr + (int64_t)((uint32_t)v % nw) * nm1;
+    const uint64_t seg = (uint64_t)rounds * EVENT_ROUND;
+    const uint64_t n_seg = ((uint64_t)max_windows + seg - 1) / seg;
+    const uint64_t n_tickets = n_seg * (uint64_t)n_trials;
+    for (;;) {
+        __syncthreads();   // the table is written; every thread has read the last ticket
+        if (tid == 0) {
+            const uint64_t with_event = __hip_atomic_load(queue + 2 * g + 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+            ticket = with_event < (uint64_t)n_trials ? atomicAdd(queue + 2 * g, 1ull) : n_tickets;
+        }
+        __syncthreads();
+        const uint64_t t = ticket;
+        if (t >= n_tickets) return;
+        const uint32_t trial = __builtin_amdgcn_readfirstlane((uint32_t)(t % (uint64_t)n_trials));
+        const int64_t v0 = (int64_t)(t / (uint64_t)n_trials * seg);
+        unsigned long long* const mine = first + (int64_t)trial * n_groups + g;
+        const uint32_t n0_trial = (uint32_t)(((uint64_t)0xCD9E8D57u * trial) >> 32) ^ key0;
+        for (int round = 0; round < rounds; ++round) {
+            const int64_t base = v0 + (int64_t)round * EVENT_ROUND;
+            // an event in an earlier window, found here or by another
+            // workgroup, leaves nothing to find in the rest
+            if (base >= max_windows ||
+                __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned long long)base)
+                break;
+            EventWindow win[EVENT_WPT];
+            int row[EVENT_WPT];
+#pragma unroll
+            for (int q = 0; q < EVENT_WPT; ++q) {
+                const uint32_t v = (uint32_t)(base + q * EVENT_THREADS + tid);
+                win[q] = event_window(v, trial, ctr3, keys);
+                row[q] = (int)(v % nw) * nm1;
+            }
             for (int j = 0; j < nm1; ++j) {
-                const Words u = philox10((uint32_t)v, (uint32_t)j, (uint32_t)trial, ctr3, keys);
-                const uint64_t m = ((uint64_t)u.x << 20) | (uint64_t)(u.y >> 12);
-                hit |= m < tw[j];
+                const uint64_t p = (uint64_t)0xD2511F53u * (n0_trial ^ (uint32_t)j);
+                const uint32_t sa = (uint32_t)(p >> 32) ^ (key1 + 0xBB67AE85u);
+                const uint32_t sb = (uint32_t)p ^ (key1 + 2u * 0xBB67AE85u);
+#pragma unroll
+                for (int q = 0; q < EVENT_WPT; ++q) {
+                    const uint32_t x = event_word0(win[q], sa, sb, keys);
+                    const bool near = x <= thr[row[q] + j];
+                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(near) != 0, 0)) {
+                        const int64_t v = base + q * EVENT_THREADS + tid;
+                        const Words u = philox10((uint32_t)v, (uint32_t)j, trial, ctr3, keys);
+                        const uint64_t m = ((uint64_t)u.x << 20) | (uint64_t)(u.y >> 12);
+                        const uint32_t lo = thr[n_thr + row[q] + j];
+                        const uint64_t last = ((uint64_t)thr[row[q] + j] << 20) | lo;
+                        if (lo != EVENT_NEVER && m <= last && v < max_windows &&
+                            atomicMin(mine, (unsigned long long)v) == EVENT_NONE)
+                            atomicAdd(queue + 2 * g + 1, 1ull);
+                    }
+                }
             }
         }
-        const uint64_t b = __builtin_amdgcn_ballot_w64(hit);
-        if (lane == 0) found[wv] = b ? base + WAVE * wv + __builtin_ctzll(b) : -1;
-        __syncthreads();
-        int64_t f = -1;
-#pragma unroll
-        for (int q = 0; q < EVENT_THREADS / WAVE; ++q) {
-            const int64_t x = found[q];
-            if (f < 0 && x >= 0) f = x;
-        }
-        __syncthreads();   // found[] is rewritten by the next round
-        if (f >= 0) {
-            if (tid == 0) first_window[(int64_t)trial * n_groups + g] = f;
-            return;
-        }
     }
-    if (tid == 0) first_window[(int64_t)trial * n_groups + g] = -1;
 }
 
 // The same without the LDS table (chains whose thresholds do not fit): one
@@ -379,7 +469,8 @@ __global__ __launch_bounds__(64) void first_event_kernel(const GroupDev* __restr
                                                          const double* __restrict__ rates, int64_t n_windows,
                                                          int64_t spr_total, int64_t max_windows, int S,
                                                          uint32_t key0, uint32_t key1,
-                                                         int64_t* __restrict__ first_window, int n_groups) {
+                                                         unsigned long long* __restrict__ first_window,
+                                                         int n_groups) {
     const int trial = blockIdx.x;
     const int g = blockIdx.y;
     const GroupDev& G = groups[g];
@@ -388,7 +479,7 @@ __global__ __launch_bounds__(64) void first_event_kernel(const GroupDev* __restr
     const double window_time = (double)S * G.dt;
     const uint32_t ctr3 = (2u << 24) | (G.stream & 0xFFFFFFu);
     const RoundKeys keys = round_keys<false>(key0, key1);
-    int64_t first = -1;
+    unsigned long long first = EVENT_NONE;
     int64_t w = 0;
     for (int64_t v = 0; v < max_windows; ++v) {
         bool hit = false;
@@ -398,7 +489,7 @@ __global__ __launch_bounds__(64) void first_event_kernel(const GroupDev* __restr
             hit |= u01_f64_53(u.x, u.y) < -expm1(-k * window_time);
         }
         if (__builtin_amdgcn_ballot_w64(hit) != 0) {
-            first = v;
+            first = (unsigned long long)v;
             break;
         }
         if (++w == n_windows) w = 0;
@@ -410,16 +501,17 @@ __global__ __launch_bounds__(64) void first_event_kernel(const GroupDev* __restr
 // trials' times (first-passage or censoring) over the number of events; one
 // wavefront per group, trials summed in fixed order.
 __global__ __launch_bounds__(64) void mftu_events_kernel(const GroupDev* __restrict__ groups,
-                                                         const int64_t* __restrict__ first_window, int n_trials,
+                                                         unsigned long long* __restrict__ first, int n_trials,
                                                          int64_t max_windows, int S, int n_groups,
                                                          double* __restrict__ mftu) {
     const int g = blockIdx.x;
     const double window_time = (double)S * groups[g].dt;
     double total = 0.0, events = 0.0;
     for (int t = threadIdx.x; t < n_trials; t += WAVE) {
-        const int64_t f = first_window[(int64_t)t * n_groups + g];
-        total += (double)(f >= 0 ? f + 1 : max_windows) * window_time;
-        events += f >= 0 ? 1.0 : 0.0;
+        const unsigned long long f = first[(int64_t)t * n_groups + g];
+        const bool hit = f != EVENT_NONE;   // EVENT_NONE is the -1 of a censored trial
+        total += (double)(hit ? (int64_t)f + 1 : max_windows) * window_time;
+        events += hit ? 1.0 : 0.0;
     }
     total = wave_sum_d(total);
     events = wave_sum_d(events);
@@ -494,17 +586,29 @@ hipError_t launch_block_sigma(const GroupDev* groups, const ColTile* tiles, int 
 
 hipError_t launch_mftu_events(const GroupDev* groups, int n_groups, const double* rates, int64_t n_windows,
                               int64_t spr_total, int n_trials, int64_t max_windows, int S, uint32_t key0,
-                              uint32_t key1, int max_springs, int64_t* first_window, double* mftu, hipStream_t st) {
+                              uint32_t key1, int max_springs, int64_t* first_window, unsigned long long* queue,
+                              double* mftu, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     const size_t lds = (size_t)n_windows * (size_t)std::max(max_springs, 1) * sizeof(uint64_t);
-    if (n_windows <= 0xFFFFFFFFll && lds <= EVENT_LDS_MAX)
-        hipLaunchKernelGGL(first_event_lds_kernel, dim3((unsigned)n_trials, (unsigned)n_groups), dim3(EVENT_THREADS),
-                           lds, st, groups, rates, n_windows, spr_total, max_windows, S, key0, key1, first_window,
-                           n_groups);
-    else
+    unsigned long long* first = (unsigned long long*)first_window;   // -1 is EVENT_NONE
+    if (n_windows <= 0xFFFFFFFFll && lds <= EVENT_LDS_MAX) {
+        const int64_t n_first = (int64_t)n_trials * n_groups;
+        hipLaunchKernelGGL(event_setup_kernel, dim3((unsigned)std::min<int64_t>(1024, (n_first + 255) / 256)), dim3(256),
+                           0, st, first, n_first, queue, n_groups);
+        // about 64 segments per trial, of 1 to 32 rounds: a ticket is an atomic on
+        // one address that the whole chip takes in turn
+        const int rounds = (int)std::min<int64_t>(EVENT_MOST_ROUNDS, std::max<int64_t>(1, max_windows / (64 * EVENT_ROUND)));
+        const int64_t seg = (int64_t)rounds * EVENT_ROUND;
+        const int64_t tickets = (max_windows + seg - 1) / seg * n_trials;
+        const int64_t blocks = std::min<int64_t>(tickets, (EVENT_BLOCKS + n_groups - 1) / n_groups);
+        hipLaunchKernelGGL(first_event_lds_kernel, dim3((unsigned)blocks, (unsigned)n_groups), dim3(EVENT_THREADS),
+                           lds, st, groups, rates, n_windows, spr_total, n_trials, max_windows, rounds, S, key0, key1,
+                           first, queue, n_groups);
+    } else {
         hipLaunchKernelGGL(first_event_kernel, dim3((unsigned)n_trials, (unsigned)n_groups), dim3(64), 0, st, groups,
-                           rates, n_windows, spr_total, max_windows, S, key0, key1, first_window, n_groups);
-    hipLaunchKernelGGL(mftu_events_kernel, dim3((unsigned)n_groups), dim3(64), 0, st, groups, first_window, n_trials,
+                           rates, n_windows, spr_total, max_windows, S, key0, key1, first, n_groups);
+    }
+    hipLaunchKernelGGL(mftu_events_kernel, dim3((unsigned)n_groups), dim3(64), 0, st, groups, first, n_trials,
                        max_windows, S, n_groups, mftu);
     return hipGetLastError();
 }

@@ -181,6 +181,28 @@ def test_mftu_events_threshold_edges_and_wide_chain_match_oracle():
     rep.close()
 
 
+@pytest.mark.parametrize("cap,trials,rate", [(1, 1, 0.5), (511, 3, 2e-3), (513, 40, 4e-4), (32769, 5, 2e-5),
+                                             (70000, 9, 1e-5)])
+def test_mftu_events_at_the_edges_of_rounds_and_segments(cap, trials, rate):
+    # caps about the 512 windows of a round and the segments that a ticket takes
+    # (one round up to 65536 windows, two above), few and many trials, two groups;
+    # whole numbers: the windows are equal
+    import torch
+    from oracle import ora
+    from paper_2206_05851_amd import ra
+    gs = [wl.group(3, 2, 1e-2, stream_id=6), wl.group(6, 2, 1e-2, stream_id=2)]
+    S, W = 10, 3
+    rates = np.random.default_rng(cap).uniform(0.0, rate, size=(W, 7))
+    o = ora.Oracle(gs, 77, S, W)
+    rep = ra.Replicas(gs, 77, sample_every=S, max_windows=W)
+    announce("MFTU by events: cap %d, %d trials" % (cap, trials))
+    m_ref, f_ref = o.mftu_events(rates, trials, cap)
+    m, f = rep.mftu_events(torch.from_numpy(rates).cuda(), trials, cap)
+    assert np.array_equal(f.cpu().numpy(), f_ref)
+    assert np.allclose(m.cpu().numpy(), m_ref, rtol=1e-13, atol=0)
+    rep.close()
+
+
 def test_conformation_after_cycle_matches_oracle():
     gs = [wl.group(40, 16, 1e-4, wl.FENE, 1.0, 100.0, wl.SHEAR, wl.wi_to_rate(50.0, 40), stream_id=1),
           wl.group(7, 9, 1e-3, wl.HOOKEAN, 1.0, 0.0, wl.QUIESCENT, 0.0, stream_id=2)]
