@@ -82,7 +82,7 @@ SLOTS_PER_BEAD_STEP = {0: 40 + 8 + 5 + 31, 1: 30 + 6 + 4.5 + 31, 2: 30 + 6 + 4.5
 # any of them differs.
 FWD_TRAFFIC = {"sha256": "4db2b2d7ac6e4b9e7fead47e53ba5fac9fdcdb728271da68bd6cfff70a7bbcf5", "noise_map": 2,
                "tile": (16, 1, 16), "bytes": (48764.958 * 2.0 + 2655974.031) * 1024}
-FWD_SOURCES = ("ra_kernels.hip", "ra_chain.hpp", "ra_device.hpp", "ra_types.hpp", "ra_launch.hpp")
+FWD_SOURCES = ("ra_fwd_wide.hip", "ra_forward.hpp", "ra_chain.hpp", "ra_device.hpp", "ra_types.hpp", "ra_launch.hpp")
 
 
 def fwd_sources_digest(files=FWD_SOURCES):

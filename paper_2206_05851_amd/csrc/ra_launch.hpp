@@ -66,6 +66,16 @@ struct AdjArgs {
 // nmap: noise map of the context (1 selects the kernels compiled for map 1)
 hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves_per_block, int nmap,
                           hipStream_t st);
+// one kernel family each, noise map nmap (blocks_a of the grid run context a)
+void launch_forward_lane(const FwdArgs& a, int nmap, dim3 grid, dim3 block, hipStream_t st);
+void launch_forward_wide(const FwdArgs& a, int nmap, dim3 grid, dim3 block, hipStream_t st);
+void launch_forward_f64(const FwdArgs& a, int nmap, dim3 grid, dim3 block, hipStream_t st);
+void launch_forward_dual_lane(const FwdArgs& a, const FwdArgs& b, int blocks_a, int nmap, dim3 grid, dim3 block,
+                              hipStream_t st);
+void launch_forward_dual_wide(const FwdArgs& a, const FwdArgs& b, int blocks_a, int nmap, dim3 grid, dim3 block,
+                              hipStream_t st);
+void launch_forward_dual_f64(const FwdArgs& a, const FwdArgs& b, int blocks_a, int nmap, dim3 grid, dim3 block,
+                             hipStream_t st);
 hipError_t launch_advance(int64_t* step, int64_t n, hipStream_t st);
 hipError_t launch_reset(int32_t* status, unsigned long long* clamps, int n_groups, int64_t* step, hipStream_t st);
 hipError_t launch_clone(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
