@@ -120,12 +120,12 @@ __device__ __forceinline__ void rev_flush(const RevSums& r, const GroupDev& G, d
 }
 
 // Reverse step through Phi at the state q = Q^n; lambda holds lambda^{n+1}.
-// kc.cF is 0 on slots that are not a spring of an active replica: their
+// cF is H dt/zeta, 0 on slots that are not a spring of an active replica: their
 // lambda starts at 0, gets no injection, and with a zero coefficient on the
 // neighbour term stays 0 without a per-step select (their Q is 0, so they add
 // nothing to the theta sums either).
 template <int M, bool FENE>
-__device__ __forceinline__ void reverse_step(const Lane<float, M>& q, const SlotCoef<float, M>& kc, const GroupDev& G,
+__device__ __forceinline__ void reverse_step(const Lane<float, M>& q, const float (&cF)[M], const GroupDev& G,
                                              float (&lx)[M], float (&ly)[M], float (&lz)[M], RevSums& r) {
     const float kx = G.kx, ky = G.ky, kz = G.kz, kxz = G.kxz;
     const float plx = from_prev_lane(lx[M - 1]), ply = from_prev_lane(ly[M - 1]), plz = from_prev_lane(lz[M - 1]);
@@ -157,14 +157,14 @@ __device__ __forceinline__ void reverse_step(const Lane<float, M>& q, const Slot
         const float muQ = fmadd(ux[m], Qx, fmadd(uy[m], Qy, uz[m] * Qz));
         // lambda^n = lambda + (dt kappa)^T lambda + cF J mu with
         // J mu = g mu + (2 g^2 / Q0^2) (Q.mu) Q off the guard, g mu on it
-        const float cg = kc.cF[m] * g;
+        const float cg = cF[m] * g;
         const float t = g * muQ;
         r.s1 += t;
         float ce = 0.0f;
         if constexpr (FENE) {
             const float ge = g * t;
             r.s2 = fmadd(ge, smooth ? s : 0.0f, r.s2);
-            ce = kc.cF[m] * (smooth ? ge * (2.0f * G.inv_q0sq) : 0.0f);
+            ce = cF[m] * (smooth ? ge * (2.0f * G.inv_q0sq) : 0.0f);
         }
         const float nx = lx[m] + fmadd(kx, lx[m], fmadd(cg, ux[m], ce * Qx));
         const float ny = ly[m] + fmadd(ky, ly[m], fmadd(cg, uy[m], ce * Qy));
@@ -200,7 +200,16 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
     double gr = 0.0, gH = 0.0, gb = 0.0;      // FP64 totals
     int dummy = 0;
     const RoundKeys keys = round_keys<false>(a.key0, a.key1);
-    SlotCoef<float, M> kc;
+    using Blocks = LaneBlocks<M, NMAP>;
+    const LaneCounters<Blocks::value, false> lc = lane_counters<Blocks::value, false>(
+        Blocks::first((uint32_t)tg.j0), (uint32_t)tg.k, G.stream, a.key0, a.key1);
+    SlotMask<float, M> mask;
+    float cF[M];
+    auto set_slots = [&]() {
+        mask = slot_mask<float, M>(valid);
+#pragma unroll
+        for (int m = 0; m < M; ++m) cF[m] = valid[m] ? G.cF : 0.0f;
+    };
     constexpr int STRIDE = M * 3 * WAVE;      // floats per stored state
     const AdjArgs* ap = &a;                   // for inject(); not touched in the step loops
     const int n_seg = (int)((n_end + K - 1) / K);
@@ -211,19 +220,16 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
         // expressions as the segment loop below with segments of one step.
         const float* cp = ckpt + (int64_t)(n_end - 1) * ckpt_total;
         load_ckpt<float, M>(qn, valid, cp, G, tg);
-        kc = slot_coef<float, M>(G, valid);
+        set_slots();
         s = qn;
         if constexpr (NMAP == 1) {
             Carry<float, M> cy;
-            init_carry<float, M>(cy, G, (uint32_t)(n_end - 1), (uint32_t)tg.j0, (uint32_t)tg.k, keys);
-            em_step_map1<float, M, FENE>(s, cy, G, valid, kc, (uint32_t)(n_end - 1), (uint32_t)tg.j0, (uint32_t)tg.k,
-                                         keys, dummy);
+            init_carry<float, M, false>(cy, lc, G, (uint32_t)(n_end - 1), keys);
+            em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)(n_end - 1), keys, dummy);
         } else if constexpr (NMAP == 2) {
-            em_step_map2<float, M, FENE>(s, G, valid, kc, (uint32_t)(n_end - 1), (uint32_t)tg.j0, (uint32_t)tg.k, keys,
-                                         dummy);
+            em_step_map2<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)(n_end - 1), keys, dummy);
         } else {
-            em_step<float, M, FENE>(s, G, valid, kc, (uint32_t)(n_end - 1), (uint32_t)tg.j0, (uint32_t)tg.k, keys,
-                                    dummy);
+            em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)(n_end - 1), keys, dummy);
         }
         int rr = (int)(n_end % S);
         int w = (int)(n_end / S) - 1;
@@ -239,7 +245,7 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                 gb += db;
                 --w;
             }
-            reverse_step<M, FENE>(q, kc, G, lx, ly, lz, rs);
+            reverse_step<M, FENE>(q, cF, G, lx, ly, lz, rs);
             // FP32 partials over at most 128 steps, as the segments below hold
             // theirs over one checkpoint interval
             if ((n & 127) == 0) {
@@ -254,11 +260,11 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
         const int s0 = sgi * K;
         const int s1 = (int)min(n_end, (int64_t)s0 + K);
         load_ckpt<float, M>(s, valid, ckpt + (int64_t)sgi * ckpt_total, G, tg);
-        kc = slot_coef<float, M>(G, valid);
+        set_slots();
         float* wp = seg;
         if constexpr (NMAP == 1) {
             Carry<float, M> cy;
-            init_carry<float, M>(cy, G, (uint32_t)s0, (uint32_t)tg.j0, (uint32_t)tg.k, keys);
+            init_carry<float, M, false>(cy, lc, G, (uint32_t)s0, keys);
             int n = s0;
             if constexpr (M <= 2) {
                 // aligned groups of four steps as in the forward: the group's
@@ -267,56 +273,53 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                 for (; n < s1 && (n & 3) != 0; ++n) {
                     seg_store<M>(wp, 0, s, lane);
                     wp += STRIDE;
-                    em_step_map1<float, M, FENE>(s, cy, G, valid, kc, (uint32_t)n, (uint32_t)tg.j0, (uint32_t)tg.k,
-                                                 keys, dummy);
+                    em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
                 }
                 for (; n + 4 <= s1; n += 4) {
                     Words w[3][M];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < 3; ++q) {
+                        const StepWords sw = lc.words((uint32_t)(n + q));
 #pragma unroll
-                        for (int m = 0; m < M; ++m)
-                            w[q][m] = philox10((uint32_t)(n + q), (uint32_t)tg.j0 + (uint32_t)m, (uint32_t)tg.k, G.stream,
-                                               keys);
+                        for (int m = 0; m < M; ++m) w[q][m] = lc.draw(m, sw, keys);
+                    }
                     Noise<float, M> e3;
 #pragma unroll
                     for (int u = 0; u < 3; ++u) {
                         Noise<float, M> e;
 #pragma unroll
                         for (int m = 0; m < M; ++m) {
-                            float d;
-                            normals4(w[u][m], e.x[m], e.y[m], e.z[m], d);
+                            Polar<float> d;
+                            polars4(w[u][m], G.cN, e.x[m], e.y[m], e.z[m], d);
                             if (u == 0) e3.x[m] = d;
                             if (u == 1) e3.y[m] = d;
                             if (u == 2) e3.z[m] = d;
                         }
                         seg_store<M>(wp, 0, s, lane);
                         wp += STRIDE;
-                        physics_step<float, M, FENE>(s, e, G, valid, kc, dummy);
+                        physics_step<float, M, FENE>(s, e, G, valid, mask, dummy);
                     }
                     seg_store<M>(wp, 0, s, lane);
                     wp += STRIDE;
-                    physics_step<float, M, FENE>(s, e3, G, valid, kc, dummy);
+                    physics_step<float, M, FENE>(s, e3, G, valid, mask, dummy);
                 }
             }
             for (; n < s1; ++n) {
                 seg_store<M>(wp, 0, s, lane);
                 wp += STRIDE;
-                em_step_map1<float, M, FENE>(s, cy, G, valid, kc, (uint32_t)n, (uint32_t)tg.j0, (uint32_t)tg.k, keys,
-                                             dummy);
+                em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else if constexpr (NMAP == 2) {
             for (int n = s0; n < s1; ++n) {
                 seg_store<M>(wp, 0, s, lane);
                 wp += STRIDE;
-                em_step_map2<float, M, FENE>(s, G, valid, kc, (uint32_t)n, (uint32_t)tg.j0, (uint32_t)tg.k, keys,
-                                             dummy);
+                em_step_map2<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else {
             for (int n = s0; n < s1; ++n) {
                 seg_store<M>(wp, 0, s, lane);
                 wp += STRIDE;
-                em_step<float, M, FENE>(s, G, valid, kc, (uint32_t)n, (uint32_t)tg.j0, (uint32_t)tg.k, keys, dummy);
+                em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         }
         // s = Q^{s1}; sweep n = s1-1 .. s0, injecting at states n+1 that were sampled.
@@ -337,7 +340,7 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                 gb += db;
                 --w;
             }
-            reverse_step<M, FENE>(q, kc, G, lx, ly, lz, rs);
+            reverse_step<M, FENE>(q, cF, G, lx, ly, lz, rs);
             s = q;
             rr = rr == 0 ? S - 1 : rr - 1;
         }

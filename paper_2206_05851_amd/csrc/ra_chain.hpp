@@ -3,12 +3,23 @@
 // must reproduce the forward trajectory bit for bit).
 //
 // Bond form of Eq. (1) with the free-draining tensor Eq. (2):
-//   Q_j' = Q_j + dt kappa Q_j + (H dt/zeta) [G_{j+1} - 2 G_j + G_{j-1}]
-//          + sigma (xi_{j+1} - xi_j),   G_j = g_j Q_j,  sigma = sqrt(2 kT dt/zeta)
+//   Y_i  = G_i - G_{i-1} + sigma xi_i,   G_j = cF g_j Q_j,  cF = H dt/zeta,
+//   Q_j' = Q_j + dt kappa Q_j + (Y_{j+1} - Y_j),  sigma = sqrt(2 kT dt/zeta)
 // which is the difference of the bead update r_i' = r_i + dt (kappa r_i +
-// Fnet_i/zeta) + sigma xi_i for beads j+1 and j. The increment is formed
-// first and added once, so FP32 keeps the small flow term dt*rate*Q exactly
-// as accurate as the other terms.
+// Fnet_i/zeta) + sigma xi_i for beads j+1 and j: Y_i is bead i's displacement
+// without the flow, formed once per bead and used by both its bonds. The
+// increment is formed first and added once, so FP32 keeps the small flow term
+// dt*rate*Q exactly as accurate as the other terms.
+//
+// The step is bound by VALU issue, so its form is the one with the fewest
+// instructions. Against the same update written per bond (Laplacian of G, noise
+// difference and sigma on each bond): 24 instructions of bond update per bead
+// instead of 31 with cF in the spring's reciprocal, the noise product in the
+// displacement's FMA and sigma in the Box-Muller radius; 4.5 more in the
+// transform; 8 of 40 per Philox block (philox_block). 1000 beads (16 per lane, map
+// 2, TSF, 8192 replicas, 5000 steps): 86.8 -> 75.4 ms; 512 chains of 20-200 beads,
+// 500 steps: 6.42 -> 5.88 ms. One wavefront per SIMD (50 beads, 1024 replicas)
+// is bound by latency as well: 1.86 -> 1.82 ms.
 #pragma once
 #include "ra_device.hpp"
 #include "ra_types.hpp"
@@ -62,20 +73,61 @@ __device__ __forceinline__ void spring_factors(const Lane<T, M>& s, const GroupD
     }
 }
 
-// Normals of the M beads of the lane at one step (bead j uses the counter
+// Noise of the M beads of the lane at one step (bead j uses the counter
 // (step, bead j, replica, tag|group)); independent of the chain state, so the
 // forward kernel generates several steps ahead for instruction-level parallelism.
 template <typename T, int M> struct Noise {
-    T x[M], y[M], z[M];
+    Polar<T> x[M], y[M], z[M];
 };
 
-template <typename T, int M>
-__device__ __forceinline__ void gen_noise(Noise<T, M>& e, const GroupDev& G, uint32_t n, uint32_t bead0,
-                                          uint32_t replica, const RoundKeys& keys) {
+template <typename T> __device__ __forceinline__ T noise_amp(const GroupDev& G) {
+    if constexpr (sizeof(T) == 4) return G.cN;
+    else return G.cN_d;
+}
+
+// The lane's part of its counters: NB blocks (of the lane's beads, or of its
+// groups of four beads under noise map 2) of one replica.
+template <int NB, bool UNI> struct LaneCounters {
+    BlockLane blk[NB];
+    uint32_t rl;            // lo(M1 replica) (several replicas per wavefront)
+    uint32_t replica, key0, key1, stream;
+
+    __device__ __forceinline__ StepWords words(uint32_t n) const {
+        return step_words<UNI>(n, UNI ? replica : 0u, stream, key0, key1);
+    }
+    __device__ __forceinline__ Words draw(int b, const StepWords& w, const RoundKeys& k) const {
+        return philox_block<UNI>(blk[b], w, rl, k);
+    }
+};
+
+template <int NB, bool UNI>
+__device__ __forceinline__ LaneCounters<NB, UNI> lane_counters(uint32_t first, uint32_t replica, uint32_t stream,
+                                                               uint32_t key0, uint32_t key1) {
+    LaneCounters<NB, UNI> c;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) c.blk[b] = block_lane(first + (uint32_t)b, replica, key0);
+    c.rl = 0xCD9E8D57u * replica;
+    c.replica = replica;
+    c.key0 = key0;
+    c.key1 = key1;
+    c.stream = stream;
+    return c;
+}
+
+// Blocks of a lane and the first block word, by noise map.
+template <int M, int NMAP> struct LaneBlocks {
+    static constexpr int value = NMAP == 2 ? 3 * M / 4 : M;
+    static __device__ __forceinline__ uint32_t first(uint32_t bead0) { return NMAP == 2 ? 3u * (bead0 >> 2) : bead0; }
+};
+
+template <typename T, int M, bool UNI>
+__device__ __forceinline__ void gen_noise(Noise<T, M>& e, const LaneCounters<M, UNI>& lc, const GroupDev& G,
+                                          uint32_t n, const RoundKeys& keys) {
+    const StepWords w = lc.words(n);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const Words w = philox10(n, bead0 + (uint32_t)m, replica, G.stream, keys);
-        normals3(w, e.x[m], e.y[m], e.z[m]);
+        Polar<T> d;
+        polars4(lc.draw(m, w, keys), noise_amp<T>(G), e.x[m], e.y[m], e.z[m], d);
     }
 }
 
@@ -85,14 +137,24 @@ __device__ __forceinline__ void gen_noise(Noise<T, M>& e, const GroupDev& G, uin
 // every step still gets three independent standard normals. The fourth
 // normals wait in a per-slot carry until step 4m+3.
 template <typename T, int M> struct Carry {
-    T c0[M], c1[M], c2[M];
+    Polar<T> c0[M], c1[M], c2[M];
 };
 
-// Normals of step n under map 1, updating the carry (r = n mod 4 is
+template <typename T>
+__device__ __forceinline__ void carry_slot(uint32_t r, const Polar<T>& d, Polar<T>& c0, Polar<T>& c1, Polar<T>& c2) {
+    c0.r = r == 0u ? d.r : c0.r;
+    c0.t = r == 0u ? d.t : c0.t;
+    c1.r = r == 1u ? d.r : c1.r;
+    c1.t = r == 1u ? d.t : c1.t;
+    c2.r = r == 2u ? d.r : c2.r;
+    c2.t = r == 2u ? d.t : c2.t;
+}
+
+// Noise of step n under map 1, updating the carry (r = n mod 4 is
 // wave-uniform, so the branch is uniform and the carry slot a select).
-template <typename T, int M>
-__device__ __forceinline__ void gen_noise_map1(Noise<T, M>& e, Carry<T, M>& cy, const GroupDev& G, uint32_t n,
-                                               uint32_t bead0, uint32_t replica, const RoundKeys& keys) {
+template <typename T, int M, bool UNI>
+__device__ __forceinline__ void gen_noise_map1(Noise<T, M>& e, Carry<T, M>& cy, const LaneCounters<M, UNI>& lc,
+                                               const GroupDev& G, uint32_t n, const RoundKeys& keys) {
     const uint32_t r = n & 3u;
     if (r == 3u) {
 #pragma unroll
@@ -103,89 +165,100 @@ __device__ __forceinline__ void gen_noise_map1(Noise<T, M>& e, Carry<T, M>& cy, 
         }
         return;
     }
+    const StepWords w = lc.words(n);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        T d;
-        normals4(philox10(n, bead0 + (uint32_t)m, replica, G.stream, keys), e.x[m], e.y[m], e.z[m], d);
-        cy.c0[m] = r == 0u ? d : cy.c0[m];
-        cy.c1[m] = r == 1u ? d : cy.c1[m];
-        cy.c2[m] = r == 2u ? d : cy.c2[m];
+        Polar<T> d;
+        polars4(lc.draw(m, w, keys), noise_amp<T>(G), e.x[m], e.y[m], e.z[m], d);
+        carry_slot(r, d, cy.c0[m], cy.c1[m], cy.c2[m]);
     }
 }
 
 // Carry for a run that starts at step n: the fourth normals of the blocks of
 // steps 4m .. n-1 of n's group of four (none when n is a multiple of 4).
-template <typename T, int M>
-__device__ __forceinline__ void init_carry(Carry<T, M>& cy, const GroupDev& G, uint32_t n, uint32_t bead0,
-                                           uint32_t replica, const RoundKeys& keys) {
+template <typename T, int M, bool UNI>
+__device__ __forceinline__ void init_carry(Carry<T, M>& cy, const LaneCounters<M, UNI>& lc, const GroupDev& G,
+                                           uint32_t n, const RoundKeys& keys) {
     const uint32_t r = n & 3u;
 #pragma unroll
-    for (int m = 0; m < M; ++m) cy.c0[m] = cy.c1[m] = cy.c2[m] = (T)0;
+    for (int m = 0; m < M; ++m) cy.c0[m] = cy.c1[m] = cy.c2[m] = Polar<T>{(T)0, (T)0};
     for (uint32_t q = 0; q < r; ++q) {
+        const StepWords w = lc.words(n - r + q);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            T a, b, c, d;
-            normals4(philox10(n - r + q, bead0 + (uint32_t)m, replica, G.stream, keys), a, b, c, d);
-            cy.c0[m] = q == 0u ? d : cy.c0[m];
-            cy.c1[m] = q == 1u ? d : cy.c1[m];
-            cy.c2[m] = q == 2u ? d : cy.c2[m];
+            Polar<T> a, b, c, d;
+            polars4(lc.draw(m, w, keys), noise_amp<T>(G), a, b, c, d);
+            carry_slot(q, d, cy.c0[m], cy.c1[m], cy.c2[m]);
         }
     }
 }
 
-// G_j = g_j Q_j of slot m (spring factor evaluated once per slot and step).
-// With TSF the slot's tension f = H g |Q| of the same state is added to
-// tsum[m] (Eq. 4, zero rest length): the step's force evaluation is the TSF
-// sample of the state it starts from, so no second spring-law evaluation is
-// needed for the time average.
+// G_j = cF g_j Q_j of slot m (spring factor evaluated once per slot and step).
+// With TSF the slot's cF g |Q| of the same state is added to tsum[m]: times
+// uH = H / cF it is the tension f = H g |Q| (Eq. 4, zero rest length), so the
+// step's force evaluation is the TSF sample of the state it starts from, and no
+// second spring-law evaluation is needed for the time average.
+template <typename T, int M, bool FENE>
+__device__ __forceinline__ T slot_factor(const Lane<T, M>& s, const GroupDev& G, int m, T q2, int& clamps) {
+    if constexpr (!FENE) return Co<T>{G}.cF();
+    else if constexpr (sizeof(T) == 4)
+        return fene_force(s.qx[m], s.qy[m], s.qz[m], q2, G.fA, G.fB, G.fT, G.fC_d, G.inv_q0sq_d, clamps);
+    else return fene_force(s.qx[m], s.qy[m], s.qz[m], q2, G.cF_d, G.inv_q0sq_d, clamps);
+}
+
 template <typename T, int M, bool FENE, bool TSF = false>
 __device__ __forceinline__ void slot_force(const Lane<T, M>& s, const GroupDev& G, int m, T& fx, T& fy, T& fz,
                                            int& clamps, T* tsum = nullptr) {
-    T g = (T)1;
     T q2 = (T)0;
     if constexpr (FENE || TSF) q2 = fmadd(s.qx[m], s.qx[m], fmadd(s.qy[m], s.qy[m], s.qz[m] * s.qz[m]));
-    if constexpr (FENE) g = fene_g(s.qx[m], s.qy[m], s.qz[m], q2, (T)G.inv_q0sq, G.inv_q0sq_d, clamps);
-    if constexpr (TSF) tsum[m] = fmadd(Co<T>{G}.H() * g, fast_sqrt(q2), tsum[m]);
-    fx = g * s.qx[m];
-    fy = g * s.qy[m];
-    fz = g * s.qz[m];
+    const T h = slot_factor<T, M, FENE>(s, G, m, q2, clamps);
+    if constexpr (TSF) tsum[m] = fmadd(h, fast_sqrt(q2), tsum[m]);
+    fx = h * s.qx[m];
+    fy = h * s.qy[m];
+    fz = h * s.qz[m];
 }
 
-// Per-slot force and noise coefficients (H dt/zeta and sigma), zero on slots
-// that are not a spring of an active replica. Such slots hold Q = 0, so with
-// zero coefficients their increment is exactly 0 and they stay 0 without a
-// per-step select. Used for up to 4 slots per lane; wider lanes keep the
-// coefficients in scalar registers and select instead.
-template <typename T, int M> struct SlotCoef {
-    T cF[M], sg[M];
+// cF g |Q| of every slot, the term that slot_force adds to a TSF sum.
+template <typename T, int M, bool FENE>
+__device__ __forceinline__ void tsf_terms(const Lane<T, M>& s, const GroupDev& G, T (&u)[M]) {
+    int dummy = 0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const T q2 = fmadd(s.qx[m], s.qx[m], fmadd(s.qy[m], s.qy[m], s.qz[m] * s.qz[m]));
+        u[m] = slot_factor<T, M, FENE>(s, G, m, q2, dummy) * fast_sqrt(q2);
+    }
+}
+
+// 1 on slots that are a spring of an active replica, 0 on the others: the
+// update is Q + mask * increment in one FMA (exactly Q + increment where the
+// mask is 1), so a slot that holds Q = 0 and is no spring stays 0 without a
+// select. Used for up to 4 slots per lane; wider lanes have no registers for it
+// and select instead.
+template <typename T, int M> struct SlotMask {
+    T v[M];
 };
 
 template <typename T, int M>
-__device__ __forceinline__ SlotCoef<T, M> slot_coef(const GroupDev& G, const bool (&valid)[M]) {
-    const Co<T> c{G};
-    SlotCoef<T, M> k;
+__device__ __forceinline__ SlotMask<T, M> slot_mask(const bool (&valid)[M]) {
+    SlotMask<T, M> k;
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-        k.cF[m] = valid[m] ? c.cF() : (T)0;
-        k.sg[m] = valid[m] ? c.sigma() : (T)0;
-    }
+    for (int m = 0; m < M; ++m) k.v[m] = valid[m] ? (T)1 : (T)0;
     return k;
 }
 
 template <int M> struct MaskedSlots { static constexpr bool value = M <= 4; };
 
 // One Euler-Maruyama step of every slot of the lane. xi(m, x, y, z) yields
-// the normals of bead j0 + m (precomputed or generated on demand — the value
-// is the same). The update of slot m needs G and xi of slots m-1..m+1 only,
-// so both roll through three-slot windows; the lane's first/last slots meet
-// the neighbour lanes' through DPP. valid[m] masks slots that are not a
-// spring of an active replica.
-// xnext(e0, en) gives the next lane's bead-0 normals (by DPP from e0 unless the
-// caller has them at hand, e.g. in LDS).
-template <typename T, int M, bool FENE, bool TSF = false, typename NoiseFn, typename NextFn>
-__device__ __forceinline__ void physics_step_core(Lane<T, M>& s, NoiseFn&& xi, NextFn&& xnext,
-                                                  const GroupDev& G, const bool (&valid)[M],
-                                                  const SlotCoef<T, M>& kc, int& clamps, T* tsum = nullptr) {
+// the noise of bead j0 + m (precomputed or generated on demand — the value
+// is the same). The update of slot m needs the displacements of beads m and
+// m+1, hence G of slots m-1..m+1: both roll through the slots. The lane's first
+// bead needs the previous lane's last G, its last slot the next lane's first
+// displacement, by DPP. valid[m] and mask hold the slots that are a spring of an
+// active replica.
+template <typename T, int M, bool FENE, bool TSF = false, typename NoiseFn>
+__device__ __forceinline__ void physics_step_fn(Lane<T, M>& s, NoiseFn&& xi, const GroupDev& G,
+                                                const bool (&valid)[M], const SlotMask<T, M>& mask, int& clamps,
+                                                T* tsum = nullptr) {
     const Co<T> c{G};
     T f0x, f0y, f0z, flx, fly, flz;
     slot_force<T, M, FENE, TSF>(s, G, 0, f0x, f0y, f0z, clamps, tsum);
@@ -194,94 +267,78 @@ __device__ __forceinline__ void physics_step_core(Lane<T, M>& s, NoiseFn&& xi, N
     } else {
         flx = f0x; fly = f0y; flz = f0z;
     }
-    const T fpx = from_prev_lane(flx), fpy = from_prev_lane(fly), fpz = from_prev_lane(flz);
-    const T fnx = from_next_lane(f0x), fny = from_next_lane(f0y), fnz = from_next_lane(f0z);
-    T e0x, e0y, e0z, enx, eny, enz;
-    xi(0, e0x, e0y, e0z);
-    xnext(e0x, e0y, e0z, enx, eny, enz);
     const T kx = c.kx(), ky = c.ky(), kz = c.kz(), kxz = c.kxz();
-    T Px = fpx, Py = fpy, Pz = fpz;   // G of slot m-1
+    Polar<T> ex, ey, ez;
+    xi(0, ex, ey, ez);
     T Cx = f0x, Cy = f0y, Cz = f0z;   // G of slot m
-    T Ex = e0x, Ey = e0y, Ez = e0z;   // xi of bead m
+    // displacement of bead m
+    T Yx = fmadd(ex.r, ex.t, f0x - from_prev_lane(flx));
+    T Yy = fmadd(ey.r, ey.t, f0y - from_prev_lane(fly));
+    T Yz = fmadd(ez.r, ez.t, f0z - from_prev_lane(flz));
+    const T Lx = from_next_lane(Yx), Ly = from_next_lane(Yy), Lz = from_next_lane(Yz);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        T Nx, Ny, Nz, Xx, Xy, Xz;     // G of slot m+1, xi of bead m+1
+        T Nx, Ny, Nz, Zx, Zy, Zz;     // G of slot m+1, displacement of bead m+1
         if (m + 1 < M) {
             if (m + 1 == M - 1) { Nx = flx; Ny = fly; Nz = flz; }
             else slot_force<T, M, FENE, TSF>(s, G, m + 1 < M ? m + 1 : m, Nx, Ny, Nz, clamps, tsum);
-            xi(m + 1, Xx, Xy, Xz);
+            xi(m + 1, ex, ey, ez);
+            Zx = fmadd(ex.r, ex.t, Nx - Cx);
+            Zy = fmadd(ey.r, ey.t, Ny - Cy);
+            Zz = fmadd(ez.r, ez.t, Nz - Cz);
         } else {
-            Nx = fnx; Ny = fny; Nz = fnz;
-            Xx = enx; Xy = eny; Xz = enz;
+            Nx = Ny = Nz = (T)0;
+            Zx = Lx; Zy = Ly; Zz = Lz;
         }
-        const T lx = fmadd((T)-2, Cx, Nx + Px);
-        const T ly = fmadd((T)-2, Cy, Ny + Py);
-        const T lz = fmadd((T)-2, Cz, Nz + Pz);
-        constexpr bool masked = MaskedSlots<M>::value;
-        const T cF = masked ? kc.cF[m] : c.cF();
-        const T sg = masked ? kc.sg[m] : c.sigma();
-        const T ix = fmadd(kx, s.qx[m], fmadd(kxz, s.qz[m], fmadd(cF, lx, sg * (Xx - Ex))));
-        const T iy = fmadd(ky, s.qy[m], fmadd(cF, ly, sg * (Xy - Ey)));
-        const T iz = fmadd(kz, s.qz[m], fmadd(cF, lz, sg * (Xz - Ez)));
-        if constexpr (masked) {
-            s.qx[m] += ix;
-            s.qy[m] += iy;
-            s.qz[m] += iz;
+        const T ix = fmadd(kx, s.qx[m], fmadd(kxz, s.qz[m], Zx - Yx));
+        const T iy = fmadd(ky, s.qy[m], Zy - Yy);
+        const T iz = fmadd(kz, s.qz[m], Zz - Yz);
+        if constexpr (MaskedSlots<M>::value) {
+            s.qx[m] = fmadd(ix, mask.v[m], s.qx[m]);
+            s.qy[m] = fmadd(iy, mask.v[m], s.qy[m]);
+            s.qz[m] = fmadd(iz, mask.v[m], s.qz[m]);
         } else {
             s.qx[m] = valid[m] ? s.qx[m] + ix : (T)0;
             s.qy[m] = valid[m] ? s.qy[m] + iy : (T)0;
             s.qz[m] = valid[m] ? s.qz[m] + iz : (T)0;
         }
-        Px = Cx; Py = Cy; Pz = Cz;
         Cx = Nx; Cy = Ny; Cz = Nz;
-        Ex = Xx; Ey = Xy; Ez = Xz;
+        Yx = Zx; Yy = Zy; Yz = Zz;
     }
-}
-
-template <typename T, int M, bool FENE, bool TSF = false, typename NoiseFn>
-__device__ __forceinline__ void physics_step_fn(Lane<T, M>& s, NoiseFn&& xi, const GroupDev& G,
-                                                const bool (&valid)[M], const SlotCoef<T, M>& kc,
-                                                int& clamps, T* tsum = nullptr) {
-    physics_step_core<T, M, FENE, TSF>(
-        s, xi,
-        [](T ex, T ey, T ez, T& nx, T& ny, T& nz) {
-            nx = from_next_lane(ex);
-            ny = from_next_lane(ey);
-            nz = from_next_lane(ez);
-        },
-        G, valid, kc, clamps, tsum);
 }
 
 template <typename T, int M, bool FENE, bool TSF = false>
 __device__ __forceinline__ void physics_step(Lane<T, M>& s, const Noise<T, M>& e, const GroupDev& G,
-                                             const bool (&valid)[M], const SlotCoef<T, M>& kc, int& clamps,
+                                             const bool (&valid)[M], const SlotMask<T, M>& mask, int& clamps,
                                              T* tsum = nullptr) {
     physics_step_fn<T, M, FENE, TSF>(
-        s, [&](int m, T& x, T& y, T& z) { x = e.x[m]; y = e.y[m]; z = e.z[m]; }, G, valid, kc, clamps, tsum);
+        s, [&](int m, Polar<T>& x, Polar<T>& y, Polar<T>& z) { x = e.x[m]; y = e.y[m]; z = e.z[m]; }, G, valid, mask,
+        clamps, tsum);
 }
 
 // One full Euler-Maruyama step at global step n (noise + update).
-template <typename T, int M, bool FENE, bool TSF = false>
-__device__ __forceinline__ void em_step(Lane<T, M>& s, const GroupDev& G, const bool (&valid)[M],
-                                        const SlotCoef<T, M>& kc, uint32_t n, uint32_t bead0,
-                                        uint32_t replica, const RoundKeys& keys, int& clamps, T* tsum = nullptr) {
+template <typename T, int M, bool FENE, bool TSF = false, bool UNI = false>
+__device__ __forceinline__ void em_step(Lane<T, M>& s, const LaneCounters<M, UNI>& lc, const GroupDev& G,
+                                        const bool (&valid)[M], const SlotMask<T, M>& mask, uint32_t n,
+                                        const RoundKeys& keys, int& clamps, T* tsum = nullptr) {
+    const StepWords w = lc.words(n);
     physics_step_fn<T, M, FENE, TSF>(
         s,
-        [&](int m, T& x, T& y, T& z) {
-            normals3(philox10(n, bead0 + (uint32_t)m, replica, G.stream, keys), x, y, z);
+        [&](int m, Polar<T>& x, Polar<T>& y, Polar<T>& z) {
+            Polar<T> d;
+            polars4(lc.draw(m, w, keys), noise_amp<T>(G), x, y, z, d);
         },
-        G, valid, kc, clamps, tsum);
+        G, valid, mask, clamps, tsum);
 }
 
 // One step at global step n under map 1 (noise from and into the carry).
-template <typename T, int M, bool FENE, bool TSF = false>
-__device__ __forceinline__ void em_step_map1(Lane<T, M>& s, Carry<T, M>& cy, const GroupDev& G,
-                                             const bool (&valid)[M], const SlotCoef<T, M>& kc, uint32_t n,
-                                             uint32_t bead0, uint32_t replica, const RoundKeys& keys, int& clamps,
-                                             T* tsum = nullptr) {
+template <typename T, int M, bool FENE, bool TSF = false, bool UNI = false>
+__device__ __forceinline__ void em_step_map1(Lane<T, M>& s, Carry<T, M>& cy, const LaneCounters<M, UNI>& lc,
+                                             const GroupDev& G, const bool (&valid)[M], const SlotMask<T, M>& mask,
+                                             uint32_t n, const RoundKeys& keys, int& clamps, T* tsum = nullptr) {
     Noise<T, M> e;
-    gen_noise_map1<T, M>(e, cy, G, n, bead0, replica, keys);
-    physics_step<T, M, FENE, TSF>(s, e, G, valid, kc, clamps, tsum);
+    gen_noise_map1<T, M, UNI>(e, cy, lc, G, n, keys);
+    physics_step<T, M, FENE, TSF>(s, e, G, valid, mask, clamps, tsum);
 }
 
 // Noise map 2, for lanes of a multiple of four beads (the lane's first bead
@@ -296,33 +353,31 @@ __device__ __forceinline__ void em_step_map1(Lane<T, M>& s, Carry<T, M>& cy, con
 // (measured on 16 beads per lane: 2% faster than transforming all twelve
 // blocks up front, 4% faster than drawing and transforming each group at its
 // first bead).
-template <typename T, int M, bool FENE, bool TSF = false>
-__device__ __forceinline__ void em_step_map2(Lane<T, M>& s, const GroupDev& G, const bool (&valid)[M],
-                                             const SlotCoef<T, M>& kc, uint32_t n, uint32_t bead0,
-                                             uint32_t replica, const RoundKeys& keys, int& clamps,
-                                             T* tsum = nullptr) {
+template <typename T, int M, bool FENE, bool TSF = false, bool UNI = false>
+__device__ __forceinline__ void em_step_map2(Lane<T, M>& s, const LaneCounters<3 * M / 4, UNI>& lc, const GroupDev& G,
+                                             const bool (&valid)[M], const SlotMask<T, M>& mask, uint32_t n,
+                                             const RoundKeys& keys, int& clamps, T* tsum = nullptr) {
     static_assert(M % 4 == 0, "noise map 2 takes the beads of a lane in groups of four");
-    Words w[M / 4][3];
+    const StepWords sw = lc.words(n);
+    Words w[3 * M / 4];
 #pragma unroll
-    for (int g = 0; g < M / 4; ++g) {
-        const uint32_t b = 3u * ((bead0 >> 2) + (uint32_t)g);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) w[g][c] = philox10(n, b + (uint32_t)c, replica, G.stream, keys);
-    }
-    T gx[4], gy[4], gz[4];
+    for (int b = 0; b < 3 * M / 4; ++b) w[b] = lc.draw(b, sw, keys);
+    Polar<T> gx[4], gy[4], gz[4];
     physics_step_fn<T, M, FENE, TSF>(
         s,
-        [&](int m, T& x, T& y, T& z) {
+        [&](int m, Polar<T>& x, Polar<T>& y, Polar<T>& z) {
             if ((m & 3) == 0) {
-                normals4(w[m >> 2][0], gx[0], gx[1], gx[2], gx[3]);
-                normals4(w[m >> 2][1], gy[0], gy[1], gy[2], gy[3]);
-                normals4(w[m >> 2][2], gz[0], gz[1], gz[2], gz[3]);
+                const T cn = noise_amp<T>(G);
+                const int b = 3 * (m >> 2);
+                polars4(w[b], cn, gx[0], gx[1], gx[2], gx[3]);
+                polars4(w[b + 1], cn, gy[0], gy[1], gy[2], gy[3]);
+                polars4(w[b + 2], cn, gz[0], gz[1], gz[2], gz[3]);
             }
             x = gx[m & 3];
             y = gy[m & 3];
             z = gz[m & 3];
         },
-        G, valid, kc, clamps, tsum);
+        G, valid, mask, clamps, tsum);
 }
 
 // Tension f_j = H g_j |Q_j| (Eq. 4, zero rest length) of every slot.

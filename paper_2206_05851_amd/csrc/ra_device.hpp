@@ -73,6 +73,75 @@ __device__ __forceinline__ Words philox10(uint32_t c0, uint32_t c1, uint32_t c2,
     return philox10(c0, c1, c2, c3, round_keys(key0, key1));
 }
 
+// The chain kernels' blocks. Their step word c0 and stream word c3 are
+// wave-uniform, their bead word c1 and replica word c2 stay with the lane, so of
+// rounds 1-3 little is left for each block: what depends on the lane alone
+// (BlockLane, once per launch) and what depends on the step alone (StepWords,
+// once per step for all blocks of the wavefront) meet in 4 VALU instructions
+// with one replica per wavefront (UNI: the replica word uniform too), 6 with
+// several, against 12; rounds 4-10 are the 28 they were. The same words.
+struct BlockLane {
+    uint32_t h, l;     // M0 n0, n0 the block's first word after round 1
+};
+struct StepWords {
+    uint32_t a, b, c, d;
+};
+
+template <bool UNI>
+__device__ __forceinline__ StepWords step_words(uint32_t n, uint32_t replica, uint32_t stream, uint32_t key0,
+                                                uint32_t key1) {
+    constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * n;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ stream ^ key1);
+    StepWords w;
+    w.a = (uint32_t)p0 ^ (key1 + W1);
+    w.b = (uint32_t)p1 ^ (key0 + 2u * W0);
+    w.c = (uint32_t)(p1 >> 32) ^ (key0 + W0);
+    w.d = 0u;
+    if constexpr (UNI) {
+        const uint64_t q = (uint64_t)0xD2511F53u * (w.c ^ (uint32_t)((uint64_t)0xCD9E8D57u * replica));
+        w.c = (uint32_t)(q >> 32) ^ (key1 + 2u * W1);
+        w.d = (uint32_t)q ^ (key1 + 3u * W1);
+    }
+    return w;
+}
+
+__device__ __forceinline__ BlockLane block_lane(uint32_t bead, uint32_t replica, uint32_t key0) {
+    const uint32_t n0 = (uint32_t)(((uint64_t)0xCD9E8D57u * replica) >> 32) ^ bead ^ key0;
+    const uint64_t p = (uint64_t)0xD2511F53u * n0;
+    return BlockLane{(uint32_t)(p >> 32), (uint32_t)p};
+}
+
+// rl: lo(M1 replica), used with several replicas per wavefront only.
+template <bool UNI>
+__device__ __forceinline__ Words philox_block(const BlockLane& L, const StepWords& w, uint32_t rl, const RoundKeys& k) {
+    uint32_t c0, c1, c2, c3;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (L.h ^ w.a);           // rounds 2 and 3
+    c0 = (uint32_t)(p1 >> 32) ^ w.b;
+    c1 = (uint32_t)p1;
+    if constexpr (UNI) {
+        c2 = L.l ^ w.c;
+        const uint64_t a = (uint64_t)0xD2511F53u * c0, b = (uint64_t)0xCD9E8D57u * c2;   // round 4
+        c0 = xor3((uint32_t)(b >> 32), c1, k.k0[3]);
+        c2 = (uint32_t)(a >> 32) ^ w.d;
+        c1 = (uint32_t)b;
+        c3 = (uint32_t)a;
+    } else {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * (w.c ^ rl);
+        c2 = xor3((uint32_t)(p0 >> 32), L.l, k.k1[2]);
+        c3 = (uint32_t)p0;
+    }
+#pragma unroll
+    for (int r = UNI ? 4 : 3; r < 10; ++r) {
+        const uint64_t a = (uint64_t)0xD2511F53u * c0, b = (uint64_t)0xCD9E8D57u * c2;
+        c0 = xor3((uint32_t)(b >> 32), c1, k.k0[r]);
+        c2 = xor3((uint32_t)(a >> 32), c3, k.k1[r]);
+        c1 = (uint32_t)b;
+        c3 = (uint32_t)a;
+    }
+    return Words{c0, c1, c2, c3};
+}
+
 // Uniform in (0,1): the top 23 bits j of a word give (2j + 1) 2^-24 — an odd
 // integer below 2^24 times a power of two, hence exact in binary32 and binary64.
 // FP32: one v_alignbit_b32 forms the binary32 word of 1 + j 2^-23 (exponent
@@ -143,6 +212,37 @@ __device__ __forceinline__ void normals3(const Words& w, double& a, double& b, d
     c = r1 * c3;
 }
 
+// A normal times the step's noise amplitude, as a radius and a sine or cosine:
+// the update multiplies them into its sum (one FMA), and the amplitude rides in
+// the radius, r = sqrt(cn ln u) with cn = -2 sigma^2.
+template <typename T> struct Polar {
+    T r, t;
+};
+
+__device__ __forceinline__ void polars4(const Words& w, float cn, Polar<float>& a, Polar<float>& b, Polar<float>& c,
+                                        Polar<float>& d) {
+    const float u0 = u01_f32(w.x), u1 = u01_f32(w.y), u2 = u01_f32(w.z), u3 = u01_f32(w.w);
+    const float r0 = __builtin_amdgcn_sqrtf(cn * __builtin_amdgcn_logf(u0));
+    const float r1 = __builtin_amdgcn_sqrtf(cn * __builtin_amdgcn_logf(u2));
+    a = Polar<float>{r0, __builtin_amdgcn_cosf(u1)};
+    b = Polar<float>{r0, __builtin_amdgcn_sinf(u1)};
+    c = Polar<float>{r1, __builtin_amdgcn_cosf(u3)};
+    d = Polar<float>{r1, __builtin_amdgcn_sinf(u3)};
+}
+__device__ __forceinline__ void polars4(const Words& w, double cn, Polar<double>& a, Polar<double>& b,
+                                        Polar<double>& c, Polar<double>& d) {
+    const double u0 = u01_f64(w.x), u1 = u01_f64(w.y), u2 = u01_f64(w.z), u3 = u01_f64(w.w);
+    const double r0 = sqrt(cn * log(u0));
+    const double r1 = sqrt(cn * log(u2));
+    double s1, c1, s3, c3;
+    sincospi(2.0 * u1, &s1, &c1);
+    sincospi(2.0 * u3, &s3, &c3);
+    a = Polar<double>{r0, c1};
+    b = Polar<double>{r0, s1};
+    c = Polar<double>{r1, c3};
+    d = Polar<double>{r1, s3};
+}
+
 // ---------------------------------------------------------------------------
 // Whole-wavefront lane shifts by DPP (GFX9 wave_shr:1 / wave_shl:1). Lanes
 // whose source is outside the wave read 0 (bound_ctrl).
@@ -204,6 +304,30 @@ __device__ __forceinline__ double fene_g(double qx, double qy, double qz, double
     double s = q2 * inv_q0sq_d;
     if (s > 1.0 - FENE_DELTA) { s = 1.0 - FENE_DELTA; clamped += 1; }
     return 1.0 / (1.0 - s);
+}
+
+// cF g of the same law for the forward step: fB - |Q|^2 fA = (1 - s) / cF in one
+// FMA, and its reciprocal is the bond's force coefficient. The FP64 branch is
+// taken where s > 0.9, the same band.
+__device__ __forceinline__ float fene_force(float qx, float qy, float qz, float q2, float fA, float fB, float fT,
+                                            double fC_d, double inv_q0sq_d, int& clamped) {
+    const float t = __builtin_fmaf(-q2, fA, fB);
+    float h = fast_rcp(t);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(t < fT) != 0, 0)) {
+        if (t < fT) {
+            const double dx = qx, dy = qy, dz = qz;
+            double sd = (dx * dx + dy * dy + dz * dz) * inv_q0sq_d;
+            if (sd > 1.0 - FENE_DELTA) { sd = 1.0 - FENE_DELTA; clamped += 1; }
+            h = (float)(fC_d / (1.0 - sd));
+        }
+    }
+    return h;
+}
+__device__ __forceinline__ double fene_force(double, double, double, double q2, double cF, double inv_q0sq_d,
+                                             int& clamped) {
+    double s = q2 * inv_q0sq_d;
+    if (s > 1.0 - FENE_DELTA) { s = 1.0 - FENE_DELTA; clamped += 1; }
+    return cF / (1.0 - s);
 }
 
 }  // namespace ra

@@ -47,10 +47,12 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
     Lane<T, M> s;
     bool valid[M];
     load_lane<T, M>(s, valid, state, G, tg);
-    const SlotCoef<T, M> kc = slot_coef<T, M>(G, valid);
+    const SlotMask<T, M> mask = slot_mask<T, M>(valid);
     const int nm1 = G.N - 1;
     const uint32_t n0 = (uint32_t)n0_64;       // total steps stay below 2^32
-    const uint32_t bead0 = (uint32_t)tg.j0, rep = (uint32_t)tg.k;
+    using Blocks = LaneBlocks<M, NMAP>;
+    const LaneCounters<Blocks::value, UNIFORM_K> lc = lane_counters<Blocks::value, UNIFORM_K>(
+        Blocks::first((uint32_t)tg.j0), (uint32_t)tg.k, G.stream, a.key0, a.key1);
     // per-lane output cursors, bumped once per window / checkpoint
     const int64_t lane_off = G.smp_off + (int64_t)tg.k * nm1 + tg.j0;
     T* smp_w = (T*)a.samples + (int64_t)(n0 / (uint32_t)S) * smp_total + lane_off;
@@ -84,26 +86,30 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
     for (int m = 0; m < M; ++m) tpart[m] = (T)0;
     if constexpr (FUSED) {
         if (n0_64 % S == 0) {                // the launch starts a window
-            T f[M];
-            tensions<T, M, FENE>(s, G, f);
+            T u[M];
+            tsf_terms<T, M, FENE>(s, G, u);
 #pragma unroll
-            for (int m = 0; m < M; ++m) tpart[m] = -f[m];
+            for (int m = 0; m < M; ++m) tpart[m] = -u[m];
         }
     }
     // the window sum in global memory holds part of the current window: true
     // when the launch starts inside a window, and after every mid-window fold
     bool acc_live = (n0_64 % S) != 0;
-    // fend: the window-end tensions (window_end), which also start the next window's sum
-    auto flush_tsf = [&](bool window_end, const T (&fend)[M]) {
+    const double to_f = FUSED ? (sizeof(T) == 4 ? G.uH : G.uH_d) : 1.0;   // a fused term is cF g |Q|
+    // at a window's end the terms of its last state close the sum and start
+    // the next window's
+    auto flush_tsf = [&](bool window_end) {
         if constexpr (TSF) {
+            T u[M] = {};
+            if (FUSED && window_end) tsf_terms<T, M, FENE>(s, G, u);
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 if (valid[m]) {
-                    const double acc = (acc_live ? tacc_g[m] : 0.0) + (double)tpart[m];
-                    if (window_end) tsf_w[m] = (T)((acc + (FUSED ? (double)fend[m] : 0.0)) / (double)S);
+                    const double acc = (acc_live ? tacc_g[m] : 0.0) + to_f * ((double)tpart[m] + (double)u[m]);
+                    if (window_end) tsf_w[m] = (T)(acc / (double)S);
                     else tacc_g[m] = acc;
                 }
-                tpart[m] = (FUSED && window_end) ? -fend[m] : (T)0;
+                tpart[m] = (FUSED && window_end) ? -u[m] : (T)0;
             }
             acc_live = !window_end;
         }
@@ -131,45 +137,47 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
     // it, and a partial group is always stepped through the carry, so it
     // holds the current group's fourth normals.
     [[maybe_unused]] Carry<T, M> cy;
-    if constexpr (NMAP == 1) init_carry<T, M>(cy, G, n0, bead0, rep, keys);
-    auto run_steps_map1 = [&](uint32_t n, int len) {
+    if constexpr (NMAP == 1) init_carry<T, M, UNIFORM_K>(cy, lc, G, n0, keys);
+    auto run_steps_map1 = [&](auto n, int len) {   // generic: instantiated where it is called
         int i = 0;
         if constexpr (M <= 2) {
             for (; i < len && ((n + (uint32_t)i) & 3u) != 0u; ++i) {
-                em_step_map1<T, M, FENE, FUSED>(s, cy, G, valid, kc, n + (uint32_t)i, bead0, rep, keys, clamps, tsum);
+                em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
                 accumulate_tsf();
             }
             if (i + 4 <= len) {
                 Words w[3][M];
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                for (int q = 0; q < 3; ++q) {
+                    const StepWords sw = lc.words(n + (uint32_t)(i + q));
 #pragma unroll
-                    for (int m = 0; m < M; ++m)
-                        w[q][m] = philox10(n + (uint32_t)(i + q), bead0 + (uint32_t)m, rep, G.stream, keys);
+                    for (int m = 0; m < M; ++m) w[q][m] = lc.draw(m, sw, keys);
+                }
                 for (; i + 4 <= len; i += 4) {
                     asm volatile(".p2align 6");
                     Words nw[3][M];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
+                    for (int q = 0; q < 3; ++q) {
+                        const StepWords sw = lc.words(n + (uint32_t)(i + 4 + q));
 #pragma unroll
-                        for (int m = 0; m < M; ++m)
-                            nw[q][m] = philox10(n + (uint32_t)(i + 4 + q), bead0 + (uint32_t)m, rep, G.stream, keys);
+                        for (int m = 0; m < M; ++m) nw[q][m] = lc.draw(m, sw, keys);
+                    }
                     Noise<T, M> e3;
 #pragma unroll
                     for (int u = 0; u < 3; ++u) {
                         Noise<T, M> e;
 #pragma unroll
                         for (int m = 0; m < M; ++m) {
-                            T d;
-                            normals4(w[u][m], e.x[m], e.y[m], e.z[m], d);
+                            Polar<T> d;
+                            polars4(w[u][m], noise_amp<T>(G), e.x[m], e.y[m], e.z[m], d);
                             if (u == 0) e3.x[m] = d;
                             if (u == 1) e3.y[m] = d;
                             if (u == 2) e3.z[m] = d;
                         }
-                        physics_step<T, M, FENE, FUSED>(s, e, G, valid, kc, clamps, tsum);
+                        physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                         accumulate_tsf();
                     }
-                    physics_step<T, M, FENE, FUSED>(s, e3, G, valid, kc, clamps, tsum);
+                    physics_step<T, M, FENE, FUSED>(s, e3, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
@@ -182,22 +190,11 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
         // steps that starts aligned (the carry is refilled before it is read);
         // wider lanes step through the carry from the start
         for (; i < len; ++i) {
-            em_step_map1<T, M, FENE, FUSED>(s, cy, G, valid, kc, n + (uint32_t)i, bead0, rep, keys, clamps, tsum);
+            em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
             accumulate_tsf();
         }
     };
-    auto run_steps = [&](uint32_t n, int len) {   // len steps starting at global step n
-        if constexpr (NMAP == 1) {
-            run_steps_map1(n, len);
-            return;
-        }
-        if constexpr (NMAP == 2) {
-            for (int i = 0; i < len; ++i) {
-                em_step_map2<T, M, FENE, FUSED>(s, G, valid, kc, n + (uint32_t)i, bead0, rep, keys, clamps, tsum);
-                accumulate_tsf();
-            }
-            return;
-        }
+    auto run_steps_map0 = [&](auto n, int len) {
         int i = 0;
         if constexpr (U > 1) {
             // software pipeline: the noise of block b+1 is generated in the same
@@ -212,18 +209,19 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                 if (U <= len) {
                     Words w[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) w[u] = philox10(n + (uint32_t)u, bead0, rep, G.stream, keys);
+                    for (int u = 0; u < U; ++u) w[u] = lc.draw(0, lc.words(n + (uint32_t)u), keys);
                     for (; i + U <= len; i += U) {
                         asm volatile(".p2align 6");
                         Words nw[U];
 #pragma unroll
                         for (int u = 0; u < U; ++u)
-                            nw[u] = philox10(n + (uint32_t)(i + U + u), bead0, rep, G.stream, keys);
+                            nw[u] = lc.draw(0, lc.words(n + (uint32_t)(i + U + u)), keys);
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             Noise<T, M> e;
-                            normals3(w[u], e.x[0], e.y[0], e.z[0]);
-                            physics_step<T, M, FENE, FUSED>(s, e, G, valid, kc, clamps, tsum);
+                            Polar<T> d;
+                            polars4(w[u], noise_amp<T>(G), e.x[0], e.y[0], e.z[0], d);
+                            physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                             accumulate_tsf();
                         }
 #pragma unroll
@@ -233,7 +231,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
             } else if (U <= len) {
                 Noise<T, M> e[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) gen_noise<T, M>(e[u], G, n + (uint32_t)u, bead0, rep, keys);
+                for (int u = 0; u < U; ++u) gen_noise<T, M, UNIFORM_K>(e[u], lc, G, n + (uint32_t)u, keys);
                 for (; i + U <= len; i += U) {
                     // start the loop body on a 64-byte boundary: its speed depends on
                     // where its 4- and 8-byte instructions fall in the fetch lines
@@ -242,10 +240,10 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                     Noise<T, M> f[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u)
-                        gen_noise<T, M>(f[u], G, n + (uint32_t)(i + U + u), bead0, rep, keys);
+                        gen_noise<T, M, UNIFORM_K>(f[u], lc, G, n + (uint32_t)(i + U + u), keys);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        physics_step<T, M, FENE, FUSED>(s, e[u], G, valid, kc, clamps, tsum);
+                        physics_step<T, M, FENE, FUSED>(s, e[u], G, valid, mask, clamps, tsum);
                         accumulate_tsf();
                     }
 #pragma unroll
@@ -254,8 +252,20 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
             }
         }
         for (; i < len; ++i) {
-            em_step<T, M, FENE, FUSED>(s, G, valid, kc, n + (uint32_t)i, bead0, rep, keys, clamps, tsum);
+            em_step<T, M, FENE, FUSED, UNIFORM_K>(s, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
             accumulate_tsf();
+        }
+    };
+    auto run_steps = [&](uint32_t n, int len) {   // len steps starting at global step n
+        if constexpr (NMAP == 1) {
+            run_steps_map1(n, len);
+        } else if constexpr (NMAP == 2) {
+            for (int i = 0; i < len; ++i) {
+                em_step_map2<T, M, FENE, FUSED, UNIFORM_K>(s, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
+                accumulate_tsf();
+            }
+        } else {
+            run_steps_map0(n, len);
         }
     };
 
@@ -287,15 +297,14 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                     bad |= !__builtin_isfinite(f[m]);
                 }
             }
-            flush_tsf(true, f);
+            flush_tsf(true);
             to_flush = TSF_FLUSH;
             smp_w += smp_total;
             if constexpr (TSF) tsf_w += smp_total;
             if (bad) atomicOr(status, 2);
             to_smp = S;
         } else if (TSF && (to_flush == 0 || left == 0)) {
-            const T none[M] = {};
-            flush_tsf(false, none);
+            flush_tsf(false);
             to_flush = TSF_FLUSH;
         }
     }

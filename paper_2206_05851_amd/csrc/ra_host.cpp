@@ -204,6 +204,16 @@ GroupDev make_group(const ra_chain_desc& d, int M, int tag, int nmap) {
     G.inv_q0sq_d = d.spring == RA_FENE ? d.H / (d.b * d.kT) : 0.0;
     G.kx = (float)G.kx_d; G.ky = (float)G.ky_d; G.kz = (float)G.kz_d; G.kxz = (float)G.kxz_d;
     G.cF = (float)G.cF_d; G.sigma = (float)G.sigma_d; G.H = (float)G.H_d; G.inv_q0sq = (float)G.inv_q0sq_d;
+    // fA from the rounded fB, so that its rounding scales cF and nothing else
+    // (and bounded: a cF below 1e-30 moves no FP32 bond either way)
+    G.fB = (float)std::min(1.0 / G.cF_d, 1e30);
+    G.fC_d = 1.0 / (double)G.fB;
+    G.fA = (float)(G.inv_q0sq_d * (double)G.fB);
+    G.fT = (float)(0.1 * (double)G.fB);
+    G.uH = d.spring == RA_FENE ? G.H_d * (double)G.fB : G.H_d / (double)G.cF;
+    G.uH_d = G.H_d / G.cF_d;
+    G.cN_d = -2.0 * G.sigma_d * G.sigma_d;
+    G.cN = (float)(G.cN_d * 0.69314718055994530942);
     G.kT = d.kT; G.zeta = d.zeta; G.dt = d.dt; G.b = d.b; G.rate = d.rate;
     G.dtz_d = d.dt / d.zeta;
     G.r0_d = d.spring == RA_HARMONIC ? d.rest_length : 0.0;

@@ -20,6 +20,11 @@ struct GroupDev {
     float cF;                // H * dt / zeta
     float sigma;             // noise_scale * sqrt(2 kT dt / zeta)
     float H, inv_q0sq;       // tension f = H g |Q|; s = |Q|^2 * inv_q0sq
+    // the forward step's forms: cF g = 1 / (fB - |Q|^2 fA), fB = 1 / cF and fA = fB / Q0^2;
+    // s > 0.9 below fT; fC = 1 / fB in FP64; uH = H / cF turns a sum of cF g |Q| into
+    // tensions; cN = -2 sigma^2 (times ln 2 in FP32, whose logarithm is log2)
+    float fA, fB, fT, cN;
+    double fC_d, uH, uH_d, cN_d;
     double kx_d, ky_d, kz_d, kxz_d, cF_d, sigma_d, H_d, inv_q0sq_d;
     double kT, zeta, dt, b;  // for Bell rates, events and gradients
     double rate;
