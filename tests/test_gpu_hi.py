@@ -73,6 +73,26 @@ def test_hi_kernel_matches_oracle(name, mk, dt, precision):
     assert e[0] < tol and e[1] < tol and e[2] < tol
 
 
+@pytest.mark.parametrize("N", [2, 3, 5, 6, 16, 21, 22, 32, 43, 54])
+@pytest.mark.parametrize("precision", [32, 64])
+def test_hi_tile_edges_match_oracle_and_any_context(N, precision):
+    # 3 N around multiples of the 16-row blocks and of the 64 rows of a
+    # wavefront; beads closer than 2 a and farther (both branches of Eq. 3). 20
+    # steps at 1e-3: FP32 rounding of about 1e-6 per step on bonds of about 1.
+    # A longer chain in the context (another register tile) changes no bit.
+    g = wl.group(N, 3, 1e-3, wl.HOOKEAN, 1.0, 0.0, wl.SHEAR, 0.3, hi_radius=0.4, stream_id=3)
+    p = _parent(g, N)
+    announce("hi edges N=%d precision %d" % (N, precision))
+    rep = run_gpu([g], [p], 5, 20, 10, precision=precision)
+    smp = rep.samples()[0].cpu().numpy()
+    rep.sync_status()
+    osmp = run_oracle([g], [p], 5, 20, 10).samples()[0]
+    assert rel_err(smp, osmp, 1.0) < (1e-4 if precision == 32 else 1e-10)
+    other = wl.group(60, 1, 1e-3, wl.HOOKEAN, 1.0, hi_radius=0.3, stream_id=9)
+    both = run_gpu([g, other], [p, _parent(other, 1)], 5, 20, 10, precision=precision)
+    assert np.array_equal(both.samples()[0].cpu().numpy(), smp)
+
+
 def test_hi_differs_from_free_draining_and_batches_bitwise():
     g = wl.group(12, 6, 1e-3, wl.HOOKEAN, 1.0, hi_radius=0.45, stream_id=2)
     g2 = wl.group(7, 3, 1e-3, wl.HOOKEAN, 1.0, hi_radius=0.3, stream_id=5)
