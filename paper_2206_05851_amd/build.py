@@ -18,8 +18,9 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libra.so")
 BUILD = os.path.join(PKG, "_build")
 
-SOURCES = ["ra_fwd_lane.hip", "ra_fwd_wide.hip", "ra_fwd_f64.hip", "ra_kernels.hip", "ra_adjoint.hip", "ra_rsf.hip",
-           "ra_pair.hip", "ra_hi.hip", "ra_static.hip", "ra_host.cpp", "ra_tune.cpp"]
+SOURCES = ["ra_fwd_lane.hip", "ra_fwd_wide.hip", "ra_fwd_f64.hip", "ra_fwd_split.hip", "ra_fwd_split_dual.hip",
+           "ra_kernels.hip", "ra_adjoint.hip", "ra_rsf.hip", "ra_pair.hip", "ra_hi.hip", "ra_static.hip",
+           "ra_host.cpp", "ra_tune.cpp"]
 ARCH = os.environ.get("RA_OFFLOAD_ARCH", "gfx950")
 
 

@@ -29,6 +29,8 @@ namespace ra {
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+template <bool V> struct Bool { static constexpr bool value = V; };
+
 template <typename T> struct Co;
 template <> struct Co<float> {
     const GroupDev& G;

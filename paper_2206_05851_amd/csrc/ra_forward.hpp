@@ -23,15 +23,71 @@ namespace ra {
 // Noise run-ahead per beads-per-lane: with one bead per lane the wave has
 // little independent work per step, so U steps of noise (U independent Philox
 // chains per lane) are generated before the U physics steps consume them.
+// Noise from other wavefronts of the workgroup (split forward, fwd_split_kernel):
+// a ring of two chunks of BLOCKS Philox blocks in LDS, transformed (radius and
+// sines as polars4 gives them) by the producing wavefronts. Each chunk starts
+// with one barrier of the workgroup.
+template <typename T, int M, int NMAP> struct NoiseRing {
+    static constexpr bool on = true;
+    static constexpr int BLOCKS = M * (int)sizeof(T) <= 16 ? 12 : 6;
+    static constexpr int STEPS = NMAP == 1 ? BLOCKS / 3 * 4 : BLOCKS;   // steps of a chunk
+    static constexpr int BYTES = 2 * BLOCKS * M * 6 * WAVE * (int)sizeof(T);
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    typedef T V4 __attribute__((ext_vector_type(4)));
+    T* base;                                       // [2][BLOCKS][M][6 WAVE]
+
+    // one lane's six values: 16-byte accesses in FP32 (four and two), FP64 (two each)
+    __device__ __forceinline__ T* row(int buf, int block, int m) const {
+        return base + ((buf * BLOCKS + block) * M + m) * (6 * WAVE);
+    }
+    __device__ __forceinline__ void put(int buf, int block, int m, const Polar<T>& a, const Polar<T>& b,
+                                        const Polar<T>& c, const Polar<T>& d) const {
+        const int lane = threadIdx.x & (WAVE - 1);
+        T* r = row(buf, block, m);
+        if constexpr (sizeof(T) == 4) {
+            ((V4*)r)[lane] = V4{a.r, a.t, b.t, c.r};
+            ((V2*)(r + 4 * WAVE))[lane] = V2{c.t, d.t};
+        } else {
+            ((V2*)r)[lane] = V2{a.r, a.t};
+            ((V2*)(r + 2 * WAVE))[lane] = V2{b.t, c.r};
+            ((V2*)(r + 4 * WAVE))[lane] = V2{c.t, d.t};
+        }
+    }
+    __device__ __forceinline__ void get(int buf, int block, int m, Polar<T>& a, Polar<T>& b, Polar<T>& c,
+                                        Polar<T>& d) const {
+        const int lane = threadIdx.x & (WAVE - 1);
+        const T* r = row(buf, block, m);
+        V2 p, q;
+        if constexpr (sizeof(T) == 4) {
+            const V4 v = ((const V4*)r)[lane];
+            p = V2{v.x, v.y};
+            q = V2{v.z, v.w};
+        } else {
+            p = ((const V2*)r)[lane];
+            q = ((const V2*)(r + 2 * WAVE))[lane];
+        }
+        const V2 h = ((const V2*)(r + 4 * WAVE))[lane];
+        a = Polar<T>{p.x, p.y};
+        b = Polar<T>{p.x, q.x};
+        c = Polar<T>{q.y, h.x};
+        d = Polar<T>{q.y, h.y};
+    }
+};
+struct OwnNoise {
+    static constexpr bool on = false;
+    static constexpr int STEPS = 1;
+    template <typename... A> __device__ void get(A&&...) const {}
+};
+
 template <int M> struct RunAhead { static constexpr int U = M == 1 ? 4 : (M == 2 ? 2 : 1); };
 
 // Fused persistent forward over all n_steps of one work item. The step loop is
 // cut into segments between events (window end, checkpoint), so the inner
 // loop holds nothing but noise generation and the bond update (plus the
 // per-step tension sum when TSF is on).
-template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP>
+template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP, typename Ring = OwnNoise>
 __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDev& G, int gidx, int k_first,
-                                                 int64_t n0_64) {
+                                                 int64_t n0_64, const Ring& ring = Ring{}) {
     constexpr int U = RunAhead<M>::U;
     // Kernel arguments are read once into locals: the step lambdas below must
     // not take the address of the by-value argument block (that would copy it
@@ -256,8 +312,100 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
             accumulate_tsf();
         }
     };
-    auto run_steps = [&](uint32_t n, int len) {   // len steps starting at global step n
+    // split forward: steps from the ring, the next step's entries read during a
+    // step. Under noise map 1 the ring starts at a multiple of 4 and the steps
+    // before it, three at most, draw their own noise.
+    int at = 0, buf = 0;   // steps taken of the current chunk, its half of the ring
+    auto run_steps_ring = [&](auto n, int len) {
+        int i = 0;
         if constexpr (NMAP == 1) {
+            if (n < ((n0 + 3u) & ~3u))
+                for (; i < len && ((n + (uint32_t)i) & 3u) != 0u; ++i) {
+                    em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
+                    accumulate_tsf();
+                }
+        }
+        // noise of step `st` of the chunk; its fourth normals into the carry (map 1)
+        auto fetch = [&](Noise<T, M>& e, int st) {
+            if constexpr (NMAP == 1) {
+                const int r = st & 3;
+                if (r == 3) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) { e.x[m] = cy.c0[m]; e.y[m] = cy.c1[m]; e.z[m] = cy.c2[m]; }
+                    return;
+                }
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    Polar<T> d;
+                    ring.get(buf, (st >> 2) * 3 + r, m, e.x[m], e.y[m], e.z[m], d);
+                    carry_slot((uint32_t)r, d, cy.c0[m], cy.c1[m], cy.c2[m]);
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    Polar<T> d;
+                    ring.get(buf, st, m, e.x[m], e.y[m], e.z[m], d);
+                }
+            }
+        };
+        while (i < len) {
+            if (at == 0) __syncthreads();          // the chunk is written
+            const int cnt = min(len - i, Ring::STEPS - at);
+            int j = 0;
+            if constexpr (NMAP == 1) {
+                // whole groups of four: three blocks, all reads at the top
+                if ((at & 3) == 0)
+                    for (; j + 4 <= cnt; j += 4) {
+                        Noise<T, M> e[3], e3;
+#pragma unroll
+                        for (int u = 0; u < 3; ++u)
+#pragma unroll
+                            for (int m = 0; m < M; ++m) {
+                                Polar<T>& d = u == 0 ? e3.x[m] : u == 1 ? e3.y[m] : e3.z[m];
+                                ring.get(buf, ((at + j) >> 2) * 3 + u, m, e[u].x[m], e[u].y[m], e[u].z[m], d);
+                            }
+#pragma unroll
+                        for (int u = 0; u < 3; ++u) {
+                            physics_step<T, M, FENE, FUSED>(s, e[u], G, valid, mask, clamps, tsum);
+                            accumulate_tsf();
+                        }
+                        physics_step<T, M, FENE, FUSED>(s, e3, G, valid, mask, clamps, tsum);
+                        accumulate_tsf();
+                    }
+                for (; j < cnt; ++j) {
+                    Noise<T, M> e;
+                    fetch(e, at + j);
+                    physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
+                    accumulate_tsf();
+                }
+            } else {
+                Noise<T, M> e, f;
+                fetch(e, at);
+                for (; j + 2 <= cnt; j += 2) {
+                    fetch(f, at + j + 1);
+                    physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
+                    accumulate_tsf();
+                    fetch(e, j + 2 < cnt ? at + j + 2 : at);
+                    physics_step<T, M, FENE, FUSED>(s, f, G, valid, mask, clamps, tsum);
+                    accumulate_tsf();
+                }
+                if (j < cnt) {
+                    physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
+                    accumulate_tsf();
+                }
+            }
+            i += cnt;
+            at += cnt;
+            if (at == Ring::STEPS) {
+                at = 0;
+                buf ^= 1;
+            }
+        }
+    };
+    auto run_steps = [&](uint32_t n, int len) {   // len steps starting at global step n
+        if constexpr (Ring::on) {
+            run_steps_ring(n, len);
+        } else if constexpr (NMAP == 1) {
             run_steps_map1(n, len);
         } else if constexpr (NMAP == 2) {
             for (int i = 0; i < len; ++i) {

@@ -61,6 +61,7 @@ struct ra_ctx {
     int64_t step = 0;
     bool initialised = false;
     bool recloned = false;          // a re-clone since the last init (no adjoint)
+    int max_m = 1;                  // most beads per lane of any group
     int hi_nmax = 0;                // largest N of an HI context (sizes the kernel's LDS)
     std::map<int64_t, hipGraphExec_t> graphs;
     std::string err;
@@ -373,6 +374,7 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
         c->max_group_elems = std::max<int64_t>(c->max_group_elems, (int64_t)G.R * G.N * 3);
         par_off[i] = par;
         par += 3 * (int64_t)G.N;
+        c->max_m = std::max(c->max_m, G.M);
         c->hgroups.push_back(G);
         for (int j0 = 0; j0 < nm1; j0 += WAVE) c->htiles.push_back(ColTile{i, j0});
     }
@@ -552,7 +554,7 @@ static ra_status enqueue_forward(ra_ctx* c, int64_t n_steps, hipStream_t st) {
         a.n_steps = std::min(chunk, n_steps - done);
         if (c->family == 2) HIPCHK(c, launch_forward_pair(a, c->run.precision, c->wpb, st));
         else if (c->family == 3) HIPCHK(c, launch_forward_hi(a, c->run.precision, c->hi_nmax, st));
-        else HIPCHK(c, launch_forward(a, c->run.precision, c->family, c->wpb, c->run.noise_map, st));
+        else HIPCHK(c, launch_forward(a, c->run.precision, c->family, c->wpb, c->max_m, c->run.noise_map, st));
         HIPCHK(c, launch_advance(c->dstep, a.n_steps, st));
     }
     return RA_OK;
@@ -571,7 +573,9 @@ static ra_status enqueue_forward_dual(ra_ctx* ca, int64_t n_a, ra_ctx* cb, int64
     if (ca->family == 2) HIPCHK(ca, launch_forward_pair_dual(a, b, ca->run.precision, ca->wpb, st));
     else if (ca->family == 3)
         HIPCHK(ca, launch_forward_hi_dual(a, b, ca->run.precision, std::max(ca->hi_nmax, cb->hi_nmax), st));
-    else HIPCHK(ca, launch_forward_dual(a, b, ca->run.precision, ca->family, ca->wpb, ca->run.noise_map, st));
+    else
+        HIPCHK(ca, launch_forward_dual(a, b, ca->run.precision, ca->family, ca->wpb, std::max(ca->max_m, cb->max_m),
+                                       ca->run.noise_map, st));
     HIPCHK(ca, launch_advance2(ca->dstep, n_a, cb->dstep, n_b, st));
     return RA_OK;
 }

@@ -341,9 +341,24 @@ static dim3 grid1d(int64_t n, int block) {
     return dim3((unsigned)b);
 }
 
-hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves_per_block, int nmap,
+// Whether n_items work items take the split forward (ra_split.hpp): few enough that
+// the chip has issue slots left beside one wavefront per item. Measured
+// against the one-wavefront kernels, 500 steps, time ratio (above 1: split faster)
+// at 256 / 512 / 768 / 1024 / 1536 items: FP32 one bead per lane 1.36 / 1.19 / 1.10 /
+// 1.02 / 1.02 (noise map 1: 1.31 / 1.33 / 1.18 / 1.10 / 1.14; at 2048 0.95), two
+// 1.58 / 1.35 / 0.95, three and four 1.78 / 1.03 / 0.75 (their rings leave one or two
+// workgroups per CU); FP64 2.7-3.2 / 1.6-1.7 / 1.1-1.3 / 0.83-1.02.
+static bool split_forward(int n_items, int precision, int family, int max_m) {
+    return family == 4 && n_items <= (precision == 64 ? 768 : max_m == 1 ? 1536 : 512);
+}
+
+hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves_per_block, int max_m, int nmap,
                           hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
+    if (split_forward(a.n_items, precision, family, max_m)) {
+        launch_forward_split(a, precision, max_m, nmap, st);
+        return hipGetLastError();
+    }
     const int wpb = waves_per_block;
     dim3 grid((a.n_items + wpb - 1) / wpb), block(WAVE * wpb);
     if (precision == 64) launch_forward_f64(a, nmap, grid, block, st);
@@ -353,8 +368,12 @@ hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves
 }
 
 hipError_t launch_forward_dual(const FwdArgs& a, const FwdArgs& b, int precision, int family, int waves_per_block,
-                               int nmap, hipStream_t st) {
+                               int max_m, int nmap, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
+    if (a.n_items + b.n_items > 0 && split_forward(a.n_items + b.n_items, precision, family, max_m)) {
+        launch_forward_split_dual(a, b, precision, max_m, nmap, st);
+        return hipGetLastError();
+    }
     const int wpb = waves_per_block;
     const int ba = (a.n_items + wpb - 1) / wpb, bb = (b.n_items + wpb - 1) / wpb;
     if (ba + bb == 0) return hipSuccess;

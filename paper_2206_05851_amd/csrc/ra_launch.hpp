@@ -63,9 +63,14 @@ struct AdjArgs {
     double* partial;           // per item [3]: d/d(rate, H, b)
 };
 
-// nmap: noise map of the context (1 selects the kernels compiled for map 1)
-hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves_per_block, int nmap,
+// nmap: noise map of the context (1 selects the kernels compiled for map 1);
+// max_m: most beads per lane of any group
+hipError_t launch_forward(const FwdArgs& a, int precision, int family, int waves_per_block, int max_m, int nmap,
                           hipStream_t st);
+// family 4 (1-4 beads per lane, at most max_m) with the noise drawn by further
+// wavefronts of the item's workgroup; the same bits
+void launch_forward_split(const FwdArgs& a, int precision, int max_m, int nmap, hipStream_t st);
+void launch_forward_split_dual(const FwdArgs& a, const FwdArgs& b, int precision, int max_m, int nmap, hipStream_t st);
 // one kernel family each, noise map nmap (blocks_a of the grid run context a)
 void launch_forward_lane(const FwdArgs& a, int nmap, dim3 grid, dim3 block, hipStream_t st);
 void launch_forward_wide(const FwdArgs& a, int nmap, dim3 grid, dim3 block, hipStream_t st);
@@ -110,7 +115,7 @@ hipError_t launch_grad_reduce(const int32_t* item_begin, int n_groups, const dou
 hipError_t launch_forward_pair(const FwdArgs& a, int precision, int waves_per_block, hipStream_t st);
 // two contexts (same kernel family) in one launch: blocks of a first, then b
 hipError_t launch_forward_dual(const FwdArgs& a, const FwdArgs& b, int precision, int family, int waves_per_block,
-                               int nmap, hipStream_t st);
+                               int max_m, int nmap, hipStream_t st);
 hipError_t launch_forward_pair_dual(const FwdArgs& a, const FwdArgs& b, int precision, int waves_per_block,
                                     hipStream_t st);
 hipError_t launch_forward_hi_dual(const FwdArgs& a, const FwdArgs& b, int precision, int max_beads, hipStream_t st);

@@ -196,7 +196,7 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     const int64_t chunk = (int64_t)1 << 30;   // the kernel counts steps in 32-bit ints
     for (int64_t done = 0; done < n_steps; done += chunk) {
         a.n_steps = std::min(chunk, n_steps - done);
-        SCHK(launch_forward(a, run->precision, family, wpb, run->noise_map, st));
+        SCHK(launch_forward(a, run->precision, family, wpb, M, run->noise_map, st));
         SCHK(launch_advance(step, a.n_steps, st));
     }
     SCHK(launch_reduce(groups, tiles, n_tiles, W, samples, smp_total, nm1, mean, stdv, run->precision, st));

@@ -490,3 +490,56 @@ def test_autotuner_tiles_bit_equal_and_cache_round_trip(tmp_path, monkeypatch):
 def torch_equal(x, y):
     import torch
     return bool(torch.equal(x, y))
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("N,M,P", [(2, 1, 32), (10, 1, 6), (50, 1, 1), (64, 1, 1), (65, 2, 1), (37, 2, 3),
+                                   (128, 2, 1), (150, 3, 1), (192, 3, 1), (200, 4, 1), (256, 4, 1)])
+@pytest.mark.parametrize("nmap", [0, 1])
+def test_split_forward_equals_one_wave_forward(N, M, P, nmap, precision):
+    # few work items run with the noise drawn by further wavefronts, many with one
+    # wavefront per item: the first replicas of a batch past every limit (1537 items)
+    # and of a small batch must agree to the bit, the first also with the oracle.
+    # Calls of 1-67 steps start off the 4-step grid, end inside a chunk of noise and
+    # at its edges; windows of 13 end anywhere.
+    from paper_2206_05851_amd import ra
+    spring, b, tsf = (wl.FENE, 60.0, False) if (N + nmap) % 2 else (wl.HOOKEAN, 0.0, True)
+    parent = wl.equilibrium_parent(N, spring, 1.0, b, seed=N)
+    few = 5 * P + 1
+    calls = (1, 2, 67, 12, 24, 3, 21)   # 130
+    out = {}
+    for R in (few, 1537 * P):
+        g = wl.group(N, R, 1e-4, spring, 1.0, b, wl.SHEAR, 3.0, stream_id=5)
+        announce("split forward N=%d M=%d R=%d nmap=%d precision=%d" % (N, M, R, nmap, precision))
+        rep = ra.Replicas([g], 23, precision=precision, sample_every=13, max_windows=10, tsf=tsf, noise_map=nmap,
+                          tile_policy=1000 + M)
+        rep.init_chains([parent])
+        for c in calls:
+            rep.step(c)
+        assert rep.tile_info() == ([M], [P])
+        out[R] = [x.cpu().numpy() for x in [rep.samples()[0][:, :few], rep.bonds()[0][:few]]
+                  + ([rep.samples(tsf=True)[1][0][:, :few]] if tsf else [])]
+        rep.sync_status()
+    for x, y in zip(out[few], out[1537 * P]):
+        assert np.array_equal(x, y)
+    o = run_oracle([wl.group(N, few, 1e-4, spring, 1.0, b, wl.SHEAR, 3.0, stream_id=5)], [parent], 23, 130, 13,
+                   noise_map=nmap)
+    assert rel_err(out[few][0], o.samples()[0]) < (TOL32 if precision == 32 else TOL64)
+
+
+def test_split_forward_mixed_tiles_match_each_group_alone():
+    # one batch of all four widths (its kernel holds every tile) against
+    # single-group contexts (kernels of that width only), checkpoints on
+    from paper_2206_05851_amd import ra
+    groups = [wl.group(N, R, 1e-4, wl.FENE, 1.0, 70.0, wl.PLANAR, 0.5, stream_id=i)
+              for i, (N, R) in enumerate([(20, 9), (100, 4), (180, 3), (230, 2)])]
+    parents = [wl.equilibrium_parent(g["n_beads"], wl.FENE, 1.0, 70.0, seed=30 + i) for i, g in enumerate(groups)]
+    announce("split forward mixed tiles")
+    rep = run_gpu(groups, parents, 29, 90, 15, checkpoint_every=10, max_steps=90)
+    smp = [s.cpu().numpy() for s in rep.samples()]
+    assert rep.tile_info()[0] == [1, 2, 3, 4]
+    rep.sync_status()
+    for i, (g, p) in enumerate(zip(groups, parents)):
+        one = run_gpu([g], [p], 29, 90, 15)
+        assert np.array_equal(one.samples()[0].cpu().numpy(), smp[i])
+        one.sync_status()
