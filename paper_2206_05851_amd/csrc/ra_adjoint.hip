@@ -8,7 +8,10 @@
 //   dJ/dtheta += lambda^{n+1} . dPhi/dtheta + direct dJ/dtheta at samples.
 // The forward stored Q every K steps; each K-step segment is recomputed
 // from its checkpoint with the same step function (bitwise-identical
-// trajectory) into a per-wavefront HBM buffer, then swept backwards.
+// trajectory) into a per-wavefront HBM buffer, then swept backwards. Many
+// wavefronts are bound by that buffer's traffic, so its rows hold the tile's lanes
+// only (4096 replicas of 100 beads, 50 of 64 lanes, 2000 steps, segments of 100:
+// 25.2 GB in 4.98 ms with whole rows, 19.7 GB in 4.43 ms).
 //
 // Bond form: Phi_j = Q_j + dt kappa Q_j + cF [G_{j+1} - 2 G_j + G_{j-1}] + noise,
 // G_j = g_j Q_j. The Laplacian is symmetric, so
@@ -45,27 +48,6 @@ __device__ __forceinline__ void factor_gs(float qx, float qy, float qz, const Gr
                 s = (float)sd;
             }
         }
-    }
-}
-
-template <int M>
-__device__ __forceinline__ void seg_store(float* seg, int step, const Lane<float, M>& s, int lane) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        float* p = seg + ((int64_t)(step * M + m) * 3) * WAVE + lane;
-        p[0] = s.qx[m];
-        p[WAVE] = s.qy[m];
-        p[2 * WAVE] = s.qz[m];
-    }
-}
-template <int M>
-__device__ __forceinline__ void seg_load(const float* seg, int step, Lane<float, M>& s, int lane) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const float* p = seg + ((int64_t)(step * M + m) * 3) * WAVE + lane;
-        s.qx[m] = p[0];
-        s.qy[m] = p[WAVE];
-        s.qz[m] = p[2 * WAVE];
     }
 }
 
@@ -191,8 +173,8 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
     float* const seg = a.segbuf + a.seg_off[item];
     double* const partial = a.partial + 3 * item;
     const TileGeom tg = tile_geom(G, k_first, M);
-    const int lane = threadIdx.x & (WAVE - 1);
-    Lane<float, M> s, q, qn;
+    const Rows<M> rows(G);
+    Lane<float, M> s;
     bool valid[M];
     float lx[M], ly[M], lz[M];
 #pragma unroll
@@ -210,18 +192,58 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
 #pragma unroll
         for (int m = 0; m < M; ++m) cF[m] = valid[m] ? G.cF : 0.0f;
     };
-    constexpr int STRIDE = M * 3 * WAVE;      // floats per stored state
+    const int STRIDE = 3 * M * G.P * G.L;     // floats per stored state
     const AdjArgs* ap = &a;                   // for inject(); not touched in the step loops
+    // Reverse over the steps hi .. lo: the states Q^lo .. Q^hi at base, base + stride,
+    // ..., and s = Q^{hi + 1}. States are read AHEAD - 1 steps before their use: with
+    // one step the loads' latency bounds a sweep of few wavefronts (1000 items of
+    // 40-77 beads, 500 kept states: the widest tile's launch 340 us, all of them 269).
+    constexpr int AHEAD = M <= 2 ? 4 : 3;
+    auto sweep = [&](const float* base, int64_t stride, int lo, int hi) {
+        Lane<float, M> ring[AHEAD];
+        ring[AHEAD - 1] = s;
+        const float* p = base + (hi - lo) * stride;
+        int at = hi;
+        auto load = [&](Lane<float, M>& q) {          // past the lowest state: that one again
+            rows.load(q, p);
+            if (at > lo) p -= stride;
+            --at;
+        };
+#pragma unroll
+        for (int d = 0; d < AHEAD - 1; ++d) load(ring[d]);
+        // rr = (n + 1) mod S, w = window of state n + 1 when rr == 0
+        int rr = (hi + 1) % S, w = (hi + 1) / S - 1;
+        RevSums rs{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // FP32 partials of at most 128 steps
+        for (int n0 = hi; n0 >= lo; n0 -= AHEAD) {
+#pragma unroll
+            for (int d = 0; d < AHEAD; ++d) {
+                const int n = n0 - d;
+                if (n < lo) break;
+                Lane<float, M>& after = ring[(d + AHEAD - 1) % AHEAD];   // Q^{n+1}
+                if (rr == 0) {
+                    double dH = 0.0, db = 0.0;
+                    inject<M, FENE>(after, valid, G, *ap, tg, w, lx, ly, lz, dH, db);
+                    gH += dH;
+                    gb += db;
+                    --w;
+                }
+                load(after);
+                reverse_step<M, FENE>(ring[d], cF, G, lx, ly, lz, rs);
+                if ((n & 127) == 0) {
+                    rev_flush(rs, G, gr, gH, gb);
+                    rs = RevSums{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                }
+                rr = rr == 0 ? S - 1 : rr - 1;
+            }
+        }
+        rev_flush(rs, G, gr, gH, gb);
+    };
     const int n_seg = (int)((n_end + K - 1) / K);
     if (K == 1 && n_end > 0) {
         // Every state is a checkpoint: no recompute. The state after the last
-        // step is rebuilt by one step from the last checkpoint; the sweep then
-        // reads Q^n from checkpoint n (one step ahead), in the same order and
-        // expressions as the segment loop below with segments of one step.
-        const float* cp = ckpt + (int64_t)(n_end - 1) * ckpt_total;
-        load_ckpt<float, M>(qn, valid, cp, G, tg);
+        // step is rebuilt by one step from the last checkpoint.
+        load_ckpt<float, M>(s, valid, ckpt + (n_end - 1) * ckpt_total, G, tg);
         set_slots();
-        s = qn;
         if constexpr (NMAP == 1) {
             Carry<float, M> cy;
             init_carry<float, M, false>(cy, lc, G, (uint32_t)(n_end - 1), keys);
@@ -231,30 +253,7 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
         } else {
             em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)(n_end - 1), keys, dummy);
         }
-        int rr = (int)(n_end % S);
-        int w = (int)(n_end / S) - 1;
-        RevSums rs{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        for (int n = (int)n_end - 1; n >= 0; --n) {
-            q = qn;
-            cp -= ckpt_total;
-            if (n > 0) load_ckpt<float, M>(qn, valid, cp, G, tg);
-            if (rr == 0) {
-                double dH = 0.0, db = 0.0;
-                inject<M, FENE>(s, valid, G, *ap, tg, w, lx, ly, lz, dH, db);
-                gH += dH;
-                gb += db;
-                --w;
-            }
-            reverse_step<M, FENE>(q, cF, G, lx, ly, lz, rs);
-            // FP32 partials over at most 128 steps, as the segments below hold
-            // theirs over one checkpoint interval
-            if ((n & 127) == 0) {
-                rev_flush(rs, G, gr, gH, gb);
-                rs = RevSums{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            }
-            s = q;
-            rr = rr == 0 ? S - 1 : rr - 1;
-        }
+        sweep(ckpt, ckpt_total, 0, (int)n_end - 1);
     }
     for (int sgi = (K == 1 && n_end > 0) ? -1 : n_seg - 1; sgi >= 0; --sgi) {
         const int s0 = sgi * K;
@@ -271,7 +270,7 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                 // three blocks per slot drawn first, each step's transform just
                 // before the step (the same normals as the carry gives)
                 for (; n < s1 && (n & 3) != 0; ++n) {
-                    seg_store<M>(wp, 0, s, lane);
+                    rows.store(s, wp);
                     wp += STRIDE;
                     em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
                 }
@@ -295,89 +294,82 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                             if (u == 1) e3.y[m] = d;
                             if (u == 2) e3.z[m] = d;
                         }
-                        seg_store<M>(wp, 0, s, lane);
+                        rows.store(s, wp);
                         wp += STRIDE;
                         physics_step<float, M, FENE>(s, e, G, valid, mask, dummy);
                     }
-                    seg_store<M>(wp, 0, s, lane);
+                    rows.store(s, wp);
                     wp += STRIDE;
                     physics_step<float, M, FENE>(s, e3, G, valid, mask, dummy);
                 }
             }
             for (; n < s1; ++n) {
-                seg_store<M>(wp, 0, s, lane);
+                rows.store(s, wp);
                 wp += STRIDE;
                 em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else if constexpr (NMAP == 2) {
             for (int n = s0; n < s1; ++n) {
-                seg_store<M>(wp, 0, s, lane);
+                rows.store(s, wp);
                 wp += STRIDE;
                 em_step_map2<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else {
             for (int n = s0; n < s1; ++n) {
-                seg_store<M>(wp, 0, s, lane);
+                rows.store(s, wp);
                 wp += STRIDE;
                 em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         }
-        // s = Q^{s1}; sweep n = s1-1 .. s0, injecting at states n+1 that were sampled.
-        // rr = (n + 1) mod S, w = window of state n + 1 when rr == 0
-        int rr = s1 % S;
-        int w = s1 / S - 1;
-        RevSums rs{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // FP32 partials of this segment
-        const float* rp = seg + (int64_t)(s1 - 1 - s0) * STRIDE;
-        seg_load<M>(rp, 0, qn, lane);           // Q^{s1-1}, loaded one step ahead
-        for (int n = s1 - 1; n >= s0; --n) {
-            q = qn;
-            if (n > s0) seg_load<M>(rp - STRIDE, 0, qn, lane);
-            rp -= STRIDE;
-            if (rr == 0) {
-                double dH = 0.0, db = 0.0;
-                inject<M, FENE>(s, valid, G, *ap, tg, w, lx, ly, lz, dH, db);
-                gH += dH;
-                gb += db;
-                --w;
-            }
-            reverse_step<M, FENE>(q, cF, G, lx, ly, lz, rs);
-            s = q;
-            rr = rr == 0 ? S - 1 : rr - 1;
-        }
-        rev_flush(rs, G, gr, gH, gb);
+        sweep(seg, STRIDE, s0, s1 - 1);
     }
     (void)spr_total;
     (void)lam_mu;
     gr = wave_sum(gr);
     gH = wave_sum(gH);
     gb = wave_sum(gb);
-    if (lane == 0) {
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
         partial[0] = gr;
         partial[1] = gH;
         partial[2] = gb;
     }
 }
 
-// One kernel per beads-per-lane M, launched over the contiguous range of the
-// (M-sorted) work list that uses it, so each M gets its own register budget.
 template <int M, int NMAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M <= 2 ? 4 : 1)))
+__device__ __forceinline__ void adjoint_item(const AdjArgs& a, const GroupDev& G, int item, int k_first) {
+    if constexpr (M <= 4) {
+        // the group's constants as a local value: read through the reference,
+        // the recompute loop re-loads them from memory every step
+        const GroupDev Gl = G;
+        if (Gl.spring == 1) run_adjoint<M, true, NMAP>(a, Gl, item, k_first);
+        else run_adjoint<M, false, NMAP>(a, Gl, item, k_first);
+    } else {   // noise map 1 is not compiled for wider lanes (rejected on the host)
+        static_assert(NMAP != 1, "noise map 1 is compiled for 1-4 beads per lane");
+        if (G.spring == 1) run_adjoint<M, true, NMAP>(a, G, item, k_first);
+        else run_adjoint<M, false, NMAP>(a, G, item, k_first);
+    }
+}
+
+// A contiguous range of the work list (sorted by beads per lane, the most first).
+// MAX_M 2 holds the tiles of one and two beads per lane, 4 those of one to four, any
+// other MAX_M that width alone, each with a register budget of its own.
+template <int MAX_M, int NMAP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAX_M <= 2 ? 4 : 1)))
 void adjoint_kernel(AdjArgs a, int item_begin, int item_end) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int item = item_begin + (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
     if (item >= item_end) return;
     const Item it = a.items[item];
     const GroupDev& G = a.groups[it.g];
-    if constexpr (M <= 4) {
-        // the group's constants as a local value: read through the reference,
-        // the recompute loop re-loads them from memory every step
-        const GroupDev Gl = G;
-        if (Gl.spring == 1) run_adjoint<M, true, NMAP>(a, Gl, item, it.k0);
-        else run_adjoint<M, false, NMAP>(a, Gl, item, it.k0);
-    } else {   // noise map 1 is not compiled for wider lanes (rejected on the host)
-        static_assert(NMAP != 1, "noise map 1 is compiled for 1-4 beads per lane");
-        if (G.spring == 1) run_adjoint<M, true, NMAP>(a, G, item, it.k0);
-        else run_adjoint<M, false, NMAP>(a, G, item, it.k0);
+    if constexpr (MAX_M == 2 || MAX_M == 4) {
+        if (G.M == 1) adjoint_item<1, NMAP>(a, G, item, it.k0);
+        else if (G.M == 2) adjoint_item<2, NMAP>(a, G, item, it.k0);
+        else if constexpr (MAX_M == 4) {
+            if (G.M == 3) adjoint_item<3, NMAP>(a, G, item, it.k0);
+            else adjoint_item<4, NMAP>(a, G, item, it.k0);
+        }
+    } else {
+        adjoint_item<MAX_M, NMAP>(a, G, item, it.k0);
     }
 }
 
@@ -429,43 +421,45 @@ __global__ __launch_bounds__(GR_THREADS) void grad_reduce_kernel(const int32_t* 
     if (t < 3) grad[3 * g + t] = sh[t][0];
 }
 
-hipError_t launch_adjoint(const AdjArgs& a, int M, int item_begin, int item_end, int waves_per_block, int nmap,
+hipError_t launch_adjoint(const AdjArgs& a, int max_m, int item_begin, int item_end, int waves_per_block, int nmap,
                           hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     const int n = item_end - item_begin;
     if (n <= 0) return hipSuccess;
     const int wpb = waves_per_block;
     dim3 grid((n + wpb - 1) / wpb), block(WAVE * wpb);
+#define RA_ADJ(M_, NMAP_) \
+    hipLaunchKernelGGL((adjoint_kernel<M_, NMAP_>), grid, block, 0, st, a, item_begin, item_end); \
+    break
     if (nmap == 1) {
-        switch (M) {
-        case 1: hipLaunchKernelGGL((adjoint_kernel<1, 1>), grid, block, 0, st, a, item_begin, item_end); break;
-        case 2: hipLaunchKernelGGL((adjoint_kernel<2, 1>), grid, block, 0, st, a, item_begin, item_end); break;
-        case 3: hipLaunchKernelGGL((adjoint_kernel<3, 1>), grid, block, 0, st, a, item_begin, item_end); break;
-        case 4: hipLaunchKernelGGL((adjoint_kernel<4, 1>), grid, block, 0, st, a, item_begin, item_end); break;
+        switch (max_m) {
+        case 1: RA_ADJ(1, 1);
+        case 2: RA_ADJ(2, 1);
+        case 3:
+        case 4: RA_ADJ(4, 1);
         default: return hipErrorInvalidValue;
         }
-        return hipGetLastError();
-    }
-    if (nmap == 2) {   // whole groups of four beads per lane: 8, 12 or 16
-        switch (M) {
-        case 8: hipLaunchKernelGGL((adjoint_kernel<8, 2>), grid, block, 0, st, a, item_begin, item_end); break;
-        case 12: hipLaunchKernelGGL((adjoint_kernel<12, 2>), grid, block, 0, st, a, item_begin, item_end); break;
-        case 16: hipLaunchKernelGGL((adjoint_kernel<16, 2>), grid, block, 0, st, a, item_begin, item_end); break;
+    } else if (nmap == 2) {   // whole groups of four beads per lane: 8, 12 or 16
+        switch (max_m) {
+        case 8: RA_ADJ(8, 2);
+        case 12: RA_ADJ(12, 2);
+        case 16: RA_ADJ(16, 2);
         default: return hipErrorInvalidValue;
         }
-        return hipGetLastError();
+    } else {
+        switch (max_m) {
+        case 1: RA_ADJ(1, 0);
+        case 2: RA_ADJ(2, 0);
+        case 3:
+        case 4: RA_ADJ(4, 0);
+        case 6: RA_ADJ(6, 0);
+        case 8: RA_ADJ(8, 0);
+        case 12: RA_ADJ(12, 0);
+        case 16: RA_ADJ(16, 0);
+        default: return hipErrorInvalidValue;
+        }
     }
-    switch (M) {
-    case 1: hipLaunchKernelGGL((adjoint_kernel<1, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 2: hipLaunchKernelGGL((adjoint_kernel<2, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 3: hipLaunchKernelGGL((adjoint_kernel<3, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 4: hipLaunchKernelGGL((adjoint_kernel<4, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 6: hipLaunchKernelGGL((adjoint_kernel<6, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 8: hipLaunchKernelGGL((adjoint_kernel<8, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 12: hipLaunchKernelGGL((adjoint_kernel<12, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    case 16: hipLaunchKernelGGL((adjoint_kernel<16, 0>), grid, block, 0, st, a, item_begin, item_end); break;
-    default: return hipErrorInvalidValue;
-    }
+#undef RA_ADJ
     return hipGetLastError();
 }
 

@@ -467,19 +467,38 @@ __device__ __forceinline__ T* ckpt_item(T* base, const GroupDev& G, int k_first)
     return base + G.ck_off + (int64_t)(k_first / G.P) * (M * 3 * G.P * G.L);
 }
 
-template <typename T, int M>
-__device__ __forceinline__ void store_ckpt(const Lane<T, M>& s, T* __restrict__ dst, const GroupDev& G) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int U = G.P * G.L;
-    if (lane < U) {
+// FP32 rows through a buffer resource of exactly their size: the lanes past U get
+// an offset out of it, so their stores are dropped and their loads give 0 without
+// a branch in the step loops.
+template <int M> struct Rows {
+    int offset, row;                // bytes: this lane's first value, one row
+    __device__ __forceinline__ explicit Rows(const GroupDev& G) {
+        const int lane = threadIdx.x & (WAVE - 1), U = G.P * G.L;
+        row = 4 * U;
+        offset = lane < U ? 4 * lane : 3 * M * row;
+    }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float* p) const {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 3 * M * row, 0x00020000);
+    }
+    __device__ __forceinline__ void store(const Lane<float, M>& s, float* p) const {
+        const auto r = rsrc(p);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            dst[(3 * m) * U + lane] = s.qx[m];
-            dst[(3 * m + 1) * U + lane] = s.qy[m];
-            dst[(3 * m + 2) * U + lane] = s.qz[m];
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.qx[m]), r, offset, 3 * m * row, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.qy[m]), r, offset, (3 * m + 1) * row, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s.qz[m]), r, offset, (3 * m + 2) * row, 0);
         }
     }
-}
+    __device__ __forceinline__ void load(Lane<float, M>& s, const float* p) const {
+        const auto r = rsrc(p);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            s.qx[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, offset, 3 * m * row, 0));
+            s.qy[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, offset, (3 * m + 1) * row, 0));
+            s.qz[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, offset, (3 * m + 2) * row, 0));
+        }
+    }
+};
 
 template <typename T, int M>
 __device__ __forceinline__ void load_ckpt(Lane<T, M>& s, bool (&valid)[M], const T* __restrict__ src,

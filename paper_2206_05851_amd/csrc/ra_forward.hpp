@@ -85,7 +85,7 @@ template <int M> struct RunAhead { static constexpr int U = M == 1 ? 4 : (M == 2
 // cut into segments between events (window end, checkpoint), so the inner
 // loop holds nothing but noise generation and the bond update (plus the
 // per-step tension sum when TSF is on).
-template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP, typename Ring = OwnNoise>
+template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP, bool EVERY, typename Ring = OwnNoise>
 __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDev& G, int gidx, int k_first,
                                                  int64_t n0_64, const Ring& ring = Ring{}) {
     constexpr int U = RunAhead<M>::U;
@@ -170,6 +170,16 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
             acc_live = !window_end;
         }
     };
+    constexpr bool CKPT = sizeof(T) == 4;                 // checkpoints are FP32 only
+    auto checkpoint = [&]() {
+        if constexpr (CKPT) {
+            Rows<M>(G).store(s, ck_w);
+            ck_w += ckpt_total;
+        }
+    };
+    auto keep = [&]() {
+        if constexpr (EVERY) checkpoint();
+    };
     int clamps = 0;
     // the separate pass: the tensions of the state after each step
     auto accumulate_tsf = [&]() {
@@ -198,6 +208,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
         int i = 0;
         if constexpr (M <= 2) {
             for (; i < len && ((n + (uint32_t)i) & 3u) != 0u; ++i) {
+                keep();
                 em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
                 accumulate_tsf();
             }
@@ -230,9 +241,11 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                             if (u == 1) e3.y[m] = d;
                             if (u == 2) e3.z[m] = d;
                         }
+                        keep();
                         physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                         accumulate_tsf();
                     }
+                    keep();
                     physics_step<T, M, FENE, FUSED>(s, e3, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
 #pragma unroll
@@ -246,6 +259,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
         // steps that starts aligned (the carry is refilled before it is read);
         // wider lanes step through the carry from the start
         for (; i < len; ++i) {
+            keep();
             em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
             accumulate_tsf();
         }
@@ -277,6 +291,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                             Noise<T, M> e;
                             Polar<T> d;
                             polars4(w[u], noise_amp<T>(G), e.x[0], e.y[0], e.z[0], d);
+                            keep();
                             physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                             accumulate_tsf();
                         }
@@ -299,6 +314,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                         gen_noise<T, M, UNIFORM_K>(f[u], lc, G, n + (uint32_t)(i + U + u), keys);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
+                        keep();
                         physics_step<T, M, FENE, FUSED>(s, e[u], G, valid, mask, clamps, tsum);
                         accumulate_tsf();
                     }
@@ -308,6 +324,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
             }
         }
         for (; i < len; ++i) {
+            keep();
             em_step<T, M, FENE, FUSED, UNIFORM_K>(s, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
             accumulate_tsf();
         }
@@ -321,6 +338,7 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
         if constexpr (NMAP == 1) {
             if (n < ((n0 + 3u) & ~3u))
                 for (; i < len && ((n + (uint32_t)i) & 3u) != 0u; ++i) {
+                    keep();
                     em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
                     accumulate_tsf();
                 }
@@ -366,15 +384,18 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                             }
 #pragma unroll
                         for (int u = 0; u < 3; ++u) {
+                            keep();
                             physics_step<T, M, FENE, FUSED>(s, e[u], G, valid, mask, clamps, tsum);
                             accumulate_tsf();
                         }
+                        keep();
                         physics_step<T, M, FENE, FUSED>(s, e3, G, valid, mask, clamps, tsum);
                         accumulate_tsf();
                     }
                 for (; j < cnt; ++j) {
                     Noise<T, M> e;
                     fetch(e, at + j);
+                    keep();
                     physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
                 }
@@ -383,13 +404,16 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
                 fetch(e, at);
                 for (; j + 2 <= cnt; j += 2) {
                     fetch(f, at + j + 1);
+                    keep();
                     physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
                     fetch(e, j + 2 < cnt ? at + j + 2 : at);
+                    keep();
                     physics_step<T, M, FENE, FUSED>(s, f, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
                 }
                 if (j < cnt) {
+                    keep();
                     physics_step<T, M, FENE, FUSED>(s, e, G, valid, mask, clamps, tsum);
                     accumulate_tsf();
                 }
@@ -421,17 +445,16 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
     int to_flush = TSF_FLUSH;
     uint32_t n = n0;
     while (left > 0) {
-        if (to_ck == 0) {                      // checkpoint before step n
-            store_ckpt<T, M>(s, ck_w, G);
-            ck_w += ckpt_total;
+        if (!EVERY && to_ck == 0) {            // checkpoint before step n
+            checkpoint();
             to_ck = K;
         }
-        int len = min(left, min(to_smp, to_ck));
+        int len = min(left, EVERY ? to_smp : min(to_smp, to_ck));
         if constexpr (TSF) len = min(len, to_flush);
         run_steps(n, len);
         n += (uint32_t)len;
         left -= len;
-        to_ck -= len;
+        to_ck -= EVERY ? 0 : len;
         to_smp -= len;
         to_flush -= len;
         if (to_smp == 0) {                     // window end after step n - 1
@@ -468,29 +491,33 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
 // for wider lanes, whose register budget has no room for the carry), noise
 // map 2 for 8, 12 and 16 beads per lane only, each in kernels of its own, so
 // each map gets its own register allocation.
-template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP>
+template <typename T, int M, bool FENE, bool UNIFORM_K, bool TSF, int NMAP, bool EVERY>
 __device__ __forceinline__ void run_forward(const FwdArgs& a, const GroupDev& Gm, int k_first, int64_t n0_64) {
     const int gidx = (int)(&Gm - a.groups);
     if constexpr (M <= 4) {
         const GroupDev G = Gm;
-        run_forward_impl<T, M, FENE, UNIFORM_K, TSF, NMAP>(a, G, gidx, k_first, n0_64);
+        run_forward_impl<T, M, FENE, UNIFORM_K, TSF, NMAP, EVERY>(a, G, gidx, k_first, n0_64);
     } else {
         static_assert(NMAP != 1, "noise map 1 is compiled for 1-4 beads per lane");
-        run_forward_impl<T, M, FENE, UNIFORM_K, TSF, NMAP>(a, Gm, gidx, k_first, n0_64);
+        run_forward_impl<T, M, FENE, UNIFORM_K, TSF, NMAP, EVERY>(a, Gm, gidx, k_first, n0_64);
     }
 }
 
 // TSFK: 0 compiles the variants without TSF, 1 those with TSF (kernels of
 // their own, so the time-average sums do not raise the register budget of
 // runs without them), 2 both, chosen per context at run time (the RSF
-// cycle's dual launch: the parent keeps TSF, the replicas do not).
+// cycle's dual launch: the parent keeps TSF, the replicas do not). 3: no TSF, and a
+// state kept before every step (K = 1), stored inside the step loops: as segments
+// of one step between checkpoints the loops lose their run-ahead (1000 items of
+// 40-77 beads, 500 steps: 488 us, and 381 with it). In kernels of its own, as it
+// raises the registers of the others (a mixed batch: 5.87 ms, with it 6.28).
 template <typename T, int M, int NMAP, int TSFK>
 __device__ __forceinline__ void dispatch_spring(const FwdArgs& a, const GroupDev& G, int k_first, int64_t n0) {
     const bool tsf = a.tsf != nullptr;
-#define RA_FWD(FENE_, UK_, TSF_) run_forward<T, M, FENE_, UK_, TSF_, NMAP>(a, G, k_first, n0)
+#define RA_FWD(FENE_, UK_, TSF_) run_forward<T, M, FENE_, UK_, TSF_, NMAP, TSFK == 3>(a, G, k_first, n0)
 #define RA_TSF(FENE_, UK_)                                        \
     do {                                                          \
-        if constexpr (TSFK == 0) RA_FWD(FENE_, UK_, false);       \
+        if constexpr (TSFK == 0 || TSFK == 3) RA_FWD(FENE_, UK_, false);       \
         else if constexpr (TSFK == 1) RA_FWD(FENE_, UK_, true);   \
         else if (tsf) RA_FWD(FENE_, UK_, true);                   \
         else RA_FWD(FENE_, UK_, false);                           \
@@ -575,8 +602,17 @@ void fwd_dual_kernel(FwdArgs a, FwdArgs b, int blocks_a) {
 // ---------------------------------------------------------------------------
 template <typename T, int FAMILY, int WPE, int NMAP>
 static void launch_fwd_tsf(const FwdArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    if (a.tsf) hipLaunchKernelGGL((fwd_kernel<T, FAMILY, WPE, NMAP, 1>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fwd_kernel<T, FAMILY, WPE, NMAP, 0>), grid, block, 0, st, a);
+    if (a.tsf) {
+        hipLaunchKernelGGL((fwd_kernel<T, FAMILY, WPE, NMAP, 1>), grid, block, 0, st, a);
+        return;
+    }
+    if constexpr (FAMILY == 4 && sizeof(T) == 4) {
+        if (a.K == 1) {
+            hipLaunchKernelGGL((fwd_kernel<T, FAMILY, WPE, NMAP, 3>), grid, block, 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((fwd_kernel<T, FAMILY, WPE, NMAP, 0>), grid, block, 0, st, a);
 }
 
 template <typename T, int FAMILY, int WPE, int NMAP>

@@ -12,8 +12,17 @@ __global__ __launch_bounds__(split_threads<T>()) void fwd_split_kernel(FwdArgs a
 template <typename T, int NMAP, int MAX_M> static void launch_split_m(const FwdArgs& a, hipStream_t st) {
     constexpr int lds = split_lds_bytes<T, NMAP, MAX_M>();
     const dim3 grid((unsigned)a.n_items), block(split_threads<T>());
-    if (a.tsf) hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 1, MAX_M>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 0, MAX_M>), grid, block, lds, st, a);
+    if (a.tsf) {
+        hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 1, MAX_M>), grid, block, lds, st, a);
+        return;
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (a.K == 1) {
+            hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 3, MAX_M>), grid, block, lds, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 0, MAX_M>), grid, block, lds, st, a);
 }
 
 template <typename T, int NMAP> static void launch_split(const FwdArgs& a, int max_m, hipStream_t st) {

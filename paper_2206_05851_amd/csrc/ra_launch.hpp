@@ -58,7 +58,7 @@ struct AdjArgs {
     int64_t n_end;             // steps since init covered by the adjoint
     const double* lam_mu;      // dJ/d mean [W][spr_total]
     int64_t spr_total;
-    float* segbuf;             // per item: K states of the wave's lanes
+    float* segbuf;             // per item: K states in checkpoint rows
     const int64_t* seg_off;    // per item offset into segbuf (floats)
     double* partial;           // per item [3]: d/d(rate, H, b)
 };
@@ -103,7 +103,7 @@ hipError_t launch_pos_to_bonds(const GroupDev* groups, int n_groups, int64_t max
                                double* out, int precision, hipStream_t st);
 hipError_t launch_debug_noise(const uint32_t* ctr, int64_t n, uint32_t key0, uint32_t key1, uint32_t* words,
                               float* n32, double* n64, hipStream_t st);
-hipError_t launch_adjoint(const AdjArgs& a, int M, int item_begin, int item_end, int waves_per_block, int nmap,
+hipError_t launch_adjoint(const AdjArgs& a, int max_m, int item_begin, int item_end, int waves_per_block, int nmap,
                           hipStream_t st);
 hipError_t launch_lam_mu(const GroupDev* groups, int n_groups, int64_t n_windows, const double* mean,
                          const double* grad_mean, const double* grad_rates, double k0, double xd,

@@ -53,7 +53,7 @@ __device__ __forceinline__ void produce(const FwdArgs& a, const GroupDev& G, int
     }
 }
 
-// TSFK as in dispatch_spring: 0 and 1 compile one variant, 2 both.
+// TSFK as in dispatch_spring.
 template <typename T, int M, int NMAP, int TSFK>
 __device__ __forceinline__ void split_tile(const FwdArgs& a, const GroupDev& Gm, int k_first, int64_t n0, int wave,
                                            T* lds) {
@@ -64,8 +64,8 @@ __device__ __forceinline__ void split_tile(const FwdArgs& a, const GroupDev& Gm,
         constexpr bool UK = decltype(Uk)::value;
         auto consume = [&](auto Tsf) {
             constexpr bool TSF = decltype(Tsf)::value;
-            if (G.spring == 1) run_forward_impl<T, M, true, UK, TSF, NMAP>(a, G, gidx, k_first, n0, ring);
-            else run_forward_impl<T, M, false, UK, TSF, NMAP>(a, G, gidx, k_first, n0, ring);
+            if (G.spring == 1) run_forward_impl<T, M, true, UK, TSF, NMAP, TSFK == 3>(a, G, gidx, k_first, n0, ring);
+            else run_forward_impl<T, M, false, UK, TSF, NMAP, TSFK == 3>(a, G, gidx, k_first, n0, ring);
         };
         if (wave > 0) {
             produce<T, M, UK, NMAP>(a, G, k_first, n0, wave - 1, ring);

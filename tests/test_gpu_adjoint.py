@@ -190,3 +190,39 @@ def test_adjoint_full_size_against_oracle_fd_with_crn():
         fd = (J({key: th * (1 + h)}) - J({key: th * (1 - h)})) / (2 * h * th)
         announce("d/d%s adjoint %.6e oracle fd %.6e" % (key, grad[p], fd))
         assert abs(grad[p] - fd) <= 1e-3 * max(abs(fd), 1e-3 * np.max(np.abs(grad))), key
+
+
+@pytest.mark.parametrize("R,noise_map,K,S,steps", [(5, 0, 1, 7, 35), (5, 1, 1, 7, 30), (5, 1, 3, 9, 29), (5, 0, 5, 4, 23),
+                                                   (5, 0, 1, 1, 3), (520, 0, 1, 13, 26), (520, 1, 4, 13, 26),
+                                                   (1100, 1, 1, 10, 20), (1100, 0, 6, 10, 20)])
+def test_adjoint_of_mixed_widths_equals_each_group_alone(R, noise_map, K, S, steps):
+    # 1-4 beads per lane in one batch: one launch over all items up to 2048 of them
+    # (R = 5, 520), one per kernel above (R = 1100), states kept at every step
+    # or recomputed, segments shorter and longer than the sweep's read-ahead and
+    # ending off the windows; against contexts of one group. The sums differ by
+    # FP32 order at most (tiles may differ): as between checkpoint intervals.
+    import torch
+    Ns = (20, 100, 180, 230)
+    groups = [wl.group(N, R, 1e-4, wl.FENE if i % 2 else wl.HOOKEAN, 1.2, 70.0 if i % 2 else 0.0, wl.SHEAR, 3.0,
+                       stream_id=i) for i, N in enumerate(Ns)]
+    parents = [wl.equilibrium_parent(g["n_beads"], g["spring"], 1.2, g["b"], seed=40 + i)
+               for i, g in enumerate(groups)]
+    W = steps // S
+    gm = torch.from_numpy(np.random.default_rng(4).normal(size=(W, sum(Ns) - 4))).cuda()
+
+    def grad(gs, ps, cot):
+        rep = run_gpu(gs, ps, 31, steps, S, checkpoint_every=K, max_steps=steps, noise_map=noise_map)
+        mean, _ = rep.average_forces()
+        g = rep.backward(mean, cot.contiguous()).cpu().numpy()
+        smp = [x.cpu().numpy() for x in rep.samples()]
+        rep.sync_status()
+        return g, smp
+
+    announce("adjoint mixed widths R=%d map=%d K=%d" % (R, noise_map, K))
+    g_all, smp_all = grad(groups, parents, gm)
+    o = 0
+    for i, N in enumerate(Ns):
+        g_one, smp_one = grad([groups[i]], [parents[i]], gm[:, o:o + N - 1])
+        assert np.array_equal(smp_all[i], smp_one[0])
+        assert np.max(np.abs(g_all[i] - g_one[0]) / np.maximum(np.abs(g_one[0]), 1e-3 * np.max(np.abs(g_one)))) < 1e-5
+        o += N - 1
