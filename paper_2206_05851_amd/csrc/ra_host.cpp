@@ -321,12 +321,10 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
         }
         c->hi_nmax = nmax;
     }
-    for (int i = 0; i < n_groups; ++i) {
-        int forced = run->tile_policy > 1000 ? run->tile_policy - 1000 : 0;
-        Ms[i] = (pair || hi) ? 1
-                             : choose_beads_per_lane(groups[i].n_beads, groups[i].n_replicas, family, forced,
-                                                     run->noise_map);
-    }
+    if (pair || hi) Ms.assign(n_groups, 1);
+    else
+        Ms = choose_tiles(groups, n_groups, family, run->precision,
+                          run->tile_policy > 1000 ? run->tile_policy - 1000 : 0, run->noise_map);
     if (run->tile_policy == 1 && !run->plain && !pair && !hi) {
         int wpb = run->waves_per_block;   // 0: the tuner chooses the workgroup size too
         ra_status st = autotune_tiles(c->descs, *run, family, wpb, c->stream, Ms, why);

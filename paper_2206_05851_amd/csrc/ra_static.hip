@@ -118,7 +118,7 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     if (run->noise_map == 2 && family != 16)
         return fail_static(RA_EINVAL, "ra_run_static: noise_map 2 needs n_beads > 256 at precision 32");
     const int forced = run->tile_policy > 1000 ? run->tile_policy - 1000 : 0;
-    const int M = choose_beads_per_lane(d.n_beads, d.n_replicas, family, forced, run->noise_map);
+    const int M = choose_tiles(&d, 1, family, run->precision, forced, run->noise_map)[0];
     GroupDev G = make_group(d, M, 0, run->noise_map);
     const int64_t nm1 = d.n_beads - 1;
     G.state_off = 0;

@@ -25,7 +25,7 @@ static bool legal(int n_beads, int M) { return (n_beads + M - 1) / M <= 64; }
 
 bool map_allows(int nmap, int M) { return nmap != 2 || M % 4 == 0; }
 
-int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap) {
+static int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap, int widest) {
     const auto& cand = family_beads_per_lane(family);
     if (forced > 0 && legal(n_beads, forced) && map_allows(nmap, forced))
         for (int m : cand)
@@ -34,12 +34,60 @@ int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, i
     long long best_cost = 0;
     for (int M : cand) {
         if (!legal(n_beads, M) || !map_allows(nmap, M)) continue;
+        if (best > 0 && M > widest) break;
         const int L = (n_beads + M - 1) / M;
         const int P = 64 / L;
         const long long cost = (long long)M * ((n_replicas + P - 1) / P);
         if (best < 0 || cost < best_cost) { best = M; best_cost = cost; }
     }
     return best < 0 ? cand.back() : best;
+}
+
+// Time of a launch of few items, the widest with M beads per lane: measured, us
+// per 400 steps, up to 256, 512, 768, 1024, 1536 and 2048 items (the split forward's
+// workgroups go one to a CU, the others' wavefronts one to a SIMD).
+static double few_items_cost(int M, int64_t n_items, int precision) {
+    static constexpr int items[6] = {256, 512, 768, 1024, 1536, 2048};
+    static constexpr double f32[4][6] = {{61, 74, 85, 100, 143, 147},
+                                         {90, 115, 170, 184, 260, 265},
+                                         {119, 223, 226, 230, 357, 367},
+                                         {143, 272, 281, 290, 450, 455}};
+    static constexpr double f64[6] = {100, 195, 290, 355, 590, 600};   // times M
+    int i = 0;
+    while (n_items > items[i]) ++i;
+    return precision == 64 ? M * f64[i] : f32[M - 1][i];
+}
+
+std::vector<int> choose_tiles(const ra_chain_desc* groups, int n_groups, int family, int precision, int forced,
+                              int nmap) {
+    auto tiles = [&](int widest, int64_t& n_items, int& max_m) {
+        std::vector<int> Ms(n_groups);
+        n_items = 0;
+        max_m = 1;
+        for (int i = 0; i < n_groups; ++i) {
+            const int N = groups[i].n_beads, R = groups[i].n_replicas;
+            Ms[i] = choose_beads_per_lane(N, R, family, forced, nmap, widest);
+            const int P = std::max(1, 64 / ((N + Ms[i] - 1) / Ms[i]));
+            n_items += (R + P - 1) / P;
+            max_m = std::max(max_m, Ms[i]);
+        }
+        return Ms;
+    };
+    int64_t n_items;
+    int max_m;
+    std::vector<int> best = tiles(64, n_items, max_m);
+    if (forced > 0 || family != 4 || n_items > 2048) return best;
+    double cost = few_items_cost(max_m, n_items, precision);
+    for (int widest = max_m - 1; widest >= 1; --widest) {
+        std::vector<int> Ms = tiles(widest, n_items, max_m);
+        if (n_items > 2048) break;
+        const double t = few_items_cost(max_m, n_items, precision);
+        if (t <= cost) {
+            cost = t;
+            best = Ms;
+        }
+    }
+    return best;
 }
 
 namespace {

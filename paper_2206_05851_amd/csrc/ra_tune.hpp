@@ -17,8 +17,15 @@ const std::vector<int>& family_beads_per_lane(int family);
 // wins, ties going to the smaller M (more wavefronts in flight). `forced`
 // (> 0) is used when it is legal for N and the noise map. Noise map 2 takes
 // only multiples of four (map_allows).
+// Work lists of at most 2048 items at 1-4 beads per lane do not fill the chip, and
+// the widest tile's step is what takes the time, not the lane slots: there the
+// widest M allowed is lowered as far as a table of measured times says it pays
+// (40 beads, 300 replicas, 400 steps: M = 2 chosen by slots 88 us, M = 1 74; 77
+// beads, 300 replicas, gradient with every state kept: M = 4 162 + 222 us, M = 2
+// 118 + 141). A step's results do not depend on the tile.
 bool map_allows(int nmap, int M);
-int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap);
+std::vector<int> choose_tiles(const ra_chain_desc* groups, int n_groups, int family, int precision, int forced,
+                              int nmap);
 
 // Times every legal M for each distinct (N, spring) of the batch with a short
 // run of the fused kernel that fills every SIMD four times and keeps the

@@ -543,3 +543,20 @@ def test_split_forward_mixed_tiles_match_each_group_alone():
         one = run_gpu([g], [p], 29, 90, 15)
         assert np.array_equal(one.samples()[0].cpu().numpy(), smp[i])
         one.sync_status()
+
+
+@pytest.mark.parametrize("N,R,precision,M", [(40, 300, 32, 1), (40, 1000, 32, 1), (40, 1500, 32, 2), (77, 300, 32, 2),
+                                             (77, 20000, 32, 4), (40, 50, 64, 1), (77, 150, 64, 2), (130, 40, 32, 3)])
+def test_tile_of_few_items_is_narrow_and_keeps_the_bits(N, R, precision, M):
+    # work lists that do not fill the chip take the narrowest tile that pays;
+    # any forced tile gives the same bits
+    g = wl.group(N, R, 1e-4, wl.FENE, 1.0, 80.0, wl.SHEAR, 20.0)
+    parent = wl.equilibrium_parent(N, wl.FENE, 1.0, 80.0, seed=9)
+    announce("tile of few items N=%d R=%d precision=%d" % (N, R, precision))
+    rep = run_gpu([g], [parent], 5, 20, 10, precision=precision)
+    assert rep.tile_info()[0] == [M]
+    wide = run_gpu([g], [parent], 5, 20, 10, precision=precision, tile_policy=1004)
+    assert wide.tile_info()[0] == [4]
+    assert np.array_equal(rep.samples()[0].cpu().numpy(), wide.samples()[0].cpu().numpy())
+    rep.sync_status()
+    wide.sync_status()
