@@ -239,6 +239,7 @@ template <char OP> __device__ __forceinline__ float paced(float x) {
     if constexpr (OP == 'l') asm("s_nop 0\n\tv_log_f32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
     else if constexpr (OP == 'q') asm("s_nop 0\n\tv_sqrt_f32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
     else if constexpr (OP == 's') asm("s_nop 0\n\tv_sin_f32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
+    else if constexpr (OP == 'r') asm("s_nop 0\n\tv_rcp_f32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
     else asm("s_nop 0\n\tv_cos_f32 %0, %1\n\ts_nop 0" : "=v"(r) : "v"(x));
     return r;
 }

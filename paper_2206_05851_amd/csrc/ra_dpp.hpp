@@ -51,4 +51,23 @@ __device__ __forceinline__ T wave_scan_incl(T v) {
     return v;
 }
 
+// The same of three values in step, so that each shift's wait is filled by the
+// other two.
+template <typename T>
+__device__ __forceinline__ void wave_scan_incl(T& x, T& y, T& z) {
+    auto step = [&](auto shift) {
+        const T dx = shift(x), dy = shift(y), dz = shift(z);
+        x += dx;
+        y += dy;
+        z += dz;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    step([](T v) { return dpp_or0<DPP_ROW_SHR + 1>(v); });
+    step([](T v) { return dpp_or0<DPP_ROW_SHR + 2>(v); });
+    step([](T v) { return dpp_or0<DPP_ROW_SHR + 4>(v); });
+    step([](T v) { return dpp_or0<DPP_ROW_SHR + 8>(v); });
+    step([](T v) { return dpp_or0<DPP_ROW_BCAST15, 0xA>(v); });
+    step([](T v) { return dpp_or0<DPP_ROW_BCAST31, 0xC>(v); });
+}
+
 }  // namespace ra

@@ -3,6 +3,14 @@
 // and FENE laws) plus Lennard-Jones self-association between non-adjacent
 // beads, free-draining (Eq. 1 with the self term Eq. 2 only).
 //
+// Bound by the issue of the pair loop (13 instructions and a reciprocal per pair and
+// lane), and with few items by its latency in a single wavefront: up to four
+// wavefronts step one item together (fwd_pair_shared_kernel), one run of the
+// partners each. 50 beads, FP32, us a step: 50 replicas 2.31 -> 1.18, 512 2.30 -> 1.38,
+// 1000 2.31 -> 2.12, 2048 3.24 -> 3.34 (four sums in place of one, so that the bits
+// stay the same for any number of wavefronts); FP64: 50 replicas 4.74 -> 2.16, 1024
+// 4.95 -> 4.90, 2048 9.55 -> 8.08.
+//
 // One bead per lane, P = floor(64/N) replicas per wavefront (N <= 64). The
 // state stays the bond vectors Q_j (as in the chain kernels, so FP32 keeps
 // bond-scale precision however far the chain drifts in the flow); the bead
@@ -80,8 +88,96 @@ __device__ __forceinline__ T segment_scan(T v, int i) {
     return v;
 }
 
-template <typename T, int SPRING, bool LJ>
-__device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, int k_first, T (*xs)[4]) {
+// LJ sums of one bead, in units of rmin: s = rmin^2 / r^2 is the reciprocal of the
+// scaled r^2, and the pair term is s (s^6 - s^3) dx'. `row` is the bead's own row of
+// the doubled table: partner i + t is row t.
+// The reciprocal is paced (see paced()): a single wavefront per SIMD shares its item
+// with others unless there are more items than SIMDs.
+template <typename T> struct PairSum {
+    T x, y, z;
+    __device__ __forceinline__ static float rcp(float v) { return paced<'r'>(v); }
+    __device__ __forceinline__ static double rcp(double v) { return fast_rcp(v); }
+    __device__ __forceinline__ void add(T px, T py, T pz, const T* r, bool use) {
+        const T dx = px - r[0], dy = py - r[1], dz = pz - r[2];
+        const T s = rcp(fmadd(dx, dx, fmadd(dy, dy, dz * dz)));
+        const T s3 = s * s * s;
+        // a select, not a product: drops the Inf/NaN of a coincident bonded neighbour
+        const T h = use ? s * fmadd(s3, s3, -s3) : (T)0;
+        x = fmadd(h, dx, x);
+        y = fmadd(h, dy, y);
+        z = fmadd(h, dz, z);
+    }
+    __device__ __forceinline__ PairSum operator+(const PairSum& o) const { return {x + o.x, y + o.y, z + o.z}; }
+};
+
+// The partners t = 2 .. N - 2 (never the bead itself or a bonded neighbour) are cut
+// into blocks of four, independent reciprocal chains, and the blocks into PARTS
+// runs; the last run also takes the wrap-around pair of beads 0 and N - 1 (N >= 3),
+// which the bead table meets at t = 1 and t = N - 1. A bead's force is the sum over
+// the runs in fixed order, whichever wavefronts take them.
+constexpr int PARTS = 4;
+
+template <typename T>
+__device__ __forceinline__ PairSum<T> pair_part(int part, T px, T py, T pz, const T* row, int i, int N) {
+    PairSum<T> l{(T)0, (T)0, (T)0};
+    const int nm1 = N - 1;
+    const int blocks = N > 3 ? N / 4 : 0;                // ceil((N - 3) / 4)
+    if (part == PARTS - 1 && N >= 3) l.add(px, py, pz, row + 4 * (i == 0 ? nm1 : 1), i == 0 || i == nm1);
+    int t = 2 + 4 * (blocks * part / PARTS);
+    const int end = 2 + 4 * (blocks * (part + 1) / PARTS);
+    const int whole = min(end, 2 + ((nm1 - 2) & ~3));
+    if constexpr (sizeof(T) == 4) {
+        for (; t < whole; t += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) l.add(px, py, pz, row + 4 * (t + u), true);
+        }
+    } else if (t < whole) {
+        // FP64: the next block's rows are read before this one's arithmetic, where the
+        // reciprocal is a division (1000 replicas of 50 beads, one wavefront each: 4.82
+        // against 5.86 us a step; FP32, slower: 3.23 against 2.65)
+        T r[2][4][3];
+        auto load = [&](T (&q)[4][3], int t4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) q[u][d] = row[4 * (t4 + u) + d];
+        };
+        auto sum = [&](const T (&q)[4][3]) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) l.add(px, py, pz, q[u], true);
+        };
+        load(r[0], t);
+        for (;;) {
+            if (t + 4 < whole) load(r[1], t + 4);
+            sum(r[0]);
+            t += 4;
+            if (t >= whole) break;
+            if (t + 4 < whole) load(r[0], t + 4);
+            sum(r[1]);
+            t += 4;
+            if (t >= whole) break;
+        }
+    }
+    if (t < end) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) l.add(px, py, pz, row + 4 * (t + u < nm1 ? t + u : t), t + u < nm1);
+    }
+    return l;
+}
+
+// LDS of a workgroup whose PARTS wavefronts step one work item together.
+template <typename T> struct PairShare {
+    alignas(16) T part[2][PARTS][WAVE][4];      // sums of each wavefront's partners, by step parity
+    alignas(16) T noise[2 * PARTS][WAVE][4];    // normals of the coming steps, one step per wavefront
+};
+
+// WAVES = 1: one wavefront per work item. WAVES = PARTS: all wavefronts hold the
+// state and step it alike; each sums one run of the partners and draws every fourth
+// step's noise. One barrier a step: the sums are written before and read after it,
+// the noise of a step is read before it.
+template <typename T, int SPRING, bool LJ, int WAVES>
+__device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, int k_first, T (*xs)[4], int wave,
+                                         PairShare<T>* sh) {
     // the group's constants as a local value: read through the reference,
     // the step loop re-loads them from memory every iteration
     const GroupDev G = Gm;
@@ -128,8 +224,29 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
     int64_t w = (int64_t)(n0 / (uint32_t)S);
     int clamps = 0;
     const int n_steps = (int)a.n_steps;
+    auto draw = [&](uint32_t n, T& x, T& y, T& z) {
+        normals3(philox10(n, (uint32_t)i, (uint32_t)k, G.stream, keys), x, y, z);
+    };
+    // this wavefront's share of the PARTS steps from st
+    auto share_noise = [&](int st) {
+        T* e = sh->noise[(st + wave) & (2 * WAVES - 1)][lane];
+        draw(n0 + (uint32_t)(st + wave), e[0], e[1], e[2]);
+    };
+    if constexpr (WAVES > 1) {
+        share_noise(0);
+        __syncthreads();
+    }
+    const bool writes = WAVES == 1 || wave == 0;
     for (int st = 0; st < n_steps; ++st) {
         const uint32_t n = n0 + (uint32_t)st;
+        T ex, ey, ez;
+        if constexpr (WAVES > 1) {
+            if ((st & (WAVES - 1)) == 0) share_noise(st + WAVES);
+            const T* e = sh->noise[st & (2 * WAVES - 1)][lane];
+            ex = e[0];
+            ey = e[1];
+            ez = e[2];
+        }
         T gx, gy, gz;
         pair_spring_force<T, SPRING>(qx, qy, qz, G, gx, gy, gz, clamps);
         // net force on bead i: spring i pulls toward i+1, spring i-1 pulls back
@@ -141,9 +258,10 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
             // else the segmented scan by lane shuffles
             T sx, sy, sz;
             if (one_seg) {
-                sx = wave_scan_incl(qx);
-                sy = wave_scan_incl(qy);
-                sz = wave_scan_incl(qz);
+                sx = qx;
+                sy = qy;
+                sz = qz;
+                wave_scan_incl(sx, sy, sz);
             } else {
                 sx = segment_scan(qx, i);
                 sy = segment_scan(qy, i);
@@ -163,111 +281,35 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // Partners i + t (mod N) of the replica, read from the doubled
-            // table at rows i + t (no wrap test). t = 2 .. N - 2 are never
-            // bonded neighbours nor the bead itself, so that loop carries no
-            // mask; t = 1 and t = N - 1 meet the bonded neighbours except across
-            // the wrap-around (bead N-1 with bead 0), where the pair counts
-            // for N >= 3. In units of rmin: s = rmin^2 / r^2 is the reciprocal
-            // of the scaled r^2, and the pair term is s (s^6 - s^3) dx'.
             const T* row = xs[tb + i];
-            T lx = (T)0, ly = (T)0, lz = (T)0;
-            const bool wrap_first = N >= 3 && i == nm1, wrap_last = N >= 3 && i == 0;
-            {
-                const T dx = px - row[4 * 1], dy = py - row[4 * 1 + 1], dz = pz - row[4 * 1 + 2];
-                const T s = fast_rcp(fmadd(dx, dx, fmadd(dy, dy, dz * dz)));
-                const T s3 = s * s * s;
-                // a select, not a product: drops the Inf/NaN of a coincident
-                // bonded neighbour
-                const T h = wrap_first ? s * fmadd(s3, s3, -s3) : (T)0;
-                lx = h * dx;
-                ly = h * dy;
-                lz = h * dz;
-            }
-            // t = 2 .. N - 1 in blocks of 8 (independent reciprocal chains for
-            // the single wavefront per SIMD, all eight LDS reads in flight):
-            // whole blocks of t < N - 1 unmasked, then one block that holds
-            // t = N - 1 (the wrap-around pair of bead 0) and reads row N - 1
-            // with weight 0 past it
-            int t0 = 2;
-            auto load8 = [&](T (&bx)[8], T (&by)[8], T (&bz)[8], int tb0) {
+            using Sum = PairSum<T>;
+            auto part_sum = [&](int p) { return pair_part<T>(p, px, py, pz, row, i, N); };
+            Sum l;
+            if constexpr (WAVES == 1) {
+                const Sum a0 = part_sum(0), a1 = part_sum(1), a2 = part_sum(2), a3 = part_sum(3);
+                l = (a0 + a1) + (a2 + a3);
+            } else {
+                T(*part)[WAVE][4] = sh->part[st & 1];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const T* r = row + 4 * (tb0 + u);
-                    bx[u] = r[0];
-                    by[u] = r[1];
-                    bz[u] = r[2];
+                for (int q = 0; q < PARTS / WAVES; ++q) {
+                    const int w = wave * (PARTS / WAVES) + q;
+                    const Sum own = part_sum(w);
+                    part[w][lane][0] = own.x;
+                    part[w][lane][1] = own.y;
+                    part[w][lane][2] = own.z;
                 }
-            };
-            auto pairs8 = [&](const T (&bx)[8], const T (&by)[8], const T (&bz)[8]) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const T dx = px - bx[u], dy = py - by[u], dz = pz - bz[u];
-                    const T s = fast_rcp(fmadd(dx, dx, fmadd(dy, dy, dz * dz)));
-                    const T s3 = s * s * s;
-                    const T h = s * fmadd(s3, s3, -s3);
-                    lx = fmadd(h, dx, lx);
-                    ly = fmadd(h, dy, ly);
-                    lz = fmadd(h, dz, lz);
-                }
-            };
-            if constexpr (sizeof(T) == 4) {
-                // FP32: whole blocks with their reads at the top. The pipelined
-                // form below was slower here (37.9 against 33.6 ms for
-                // collapsed50's 15,000 steps) and faster in FP64 (14.5 against
-                // 17.3 ms for 3,000 steps), where the reciprocal is a division.
-                for (; t0 + 8 <= nm1; t0 += 8) {
-                    T ax[8], ay[8], az[8];
-                    load8(ax, ay, az, t0);
-                    pairs8(ax, ay, az);
-                }
-            } else if (t0 + 8 <= nm1) {
-                // FP64: software pipeline over whole blocks, two register
-                // buffers in turn, so that the next block's eight reads are
-                // issued before this block's arithmetic
-                T ax[8], ay[8], az[8], bx[8], by[8], bz[8];
-                load8(ax, ay, az, t0);
-                for (;;) {
-                    const bool more_b = t0 + 16 <= nm1;
-                    if (more_b) load8(bx, by, bz, t0 + 8);
-                    pairs8(ax, ay, az);
-                    t0 += 8;
-                    if (!more_b) break;
-                    const bool more_a = t0 + 16 <= nm1;
-                    if (more_a) load8(ax, ay, az, t0 + 8);
-                    pairs8(bx, by, bz);
-                    t0 += 8;
-                    if (!more_a) break;
-                }
+                __syncthreads();
+                auto get = [&](int w) { return Sum{part[w][lane][0], part[w][lane][1], part[w][lane][2]}; };
+                l = (get(0) + get(1)) + (get(2) + get(3));
             }
-            if (t0 <= nm1) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int t = t0 + u;
-                    const T* r = row + 4 * (t < nm1 ? t : nm1);
-                    const bool use = t < nm1 || (t == nm1 && wrap_last);
-                    const T dx = px - r[0], dy = py - r[1], dz = pz - r[2];
-                    const T s = fast_rcp(fmadd(dx, dx, fmadd(dy, dy, dz * dz)));
-                    const T s3 = s * s * s;
-                    // a select: drops the Inf/NaN of a coincident bonded neighbour
-                    const T h = use ? s * fmadd(s3, s3, -s3) : (T)0;
-                    lx = fmadd(h, dx, lx);
-                    ly = fmadd(h, dy, ly);
-                    lz = fmadd(h, dz, lz);
-                }
-            }
-            lx *= ljf;
-            ly *= ljf;
-            lz *= ljf;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            Fx += lx;
-            Fy += ly;
-            Fz += lz;
+            Fx += l.x * ljf;
+            Fy += l.y * ljf;
+            Fz += l.z * ljf;
         }
-        T ex, ey, ez;
-        normals3(philox10(n, (uint32_t)i, (uint32_t)k, G.stream, keys), ex, ey, ez);
+        if constexpr (WAVES == 1) draw(n, ex, ey, ez);
         const T Fnx = from_next_lane(Fx), Fny = from_next_lane(Fy), Fnz = from_next_lane(Fz);
         const T enx = from_next_lane(ex), eny = from_next_lane(ey), enz = from_next_lane(ez);
         const T ix = fmadd(kx, qx, fmadd(kxz, qz, fmadd(dtz, Fnx - Fx, sg * (enx - ex))));
@@ -283,21 +325,20 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
             if (tsf) acc += (double)f;
             if (window_end) {
                 bool bad = false;
-                if (bond_ok) {
+                if (bond_ok && writes) {
                     const int64_t o = w * smp_total + G.smp_off + sidx;
                     ((T*)a.samples)[o] = f;
                     bad = !__builtin_isfinite((double)f);
-                    if (tsf) {
-                        ((T*)a.tsf)[o] = (T)(acc / (double)S);
-                        acc = 0.0;
-                    }
+                    if (tsf) ((T*)a.tsf)[o] = (T)(acc / (double)S);
                 }
+                acc = 0.0;
                 if (bad) atomicOr(a.status, 2);
                 to_smp = S;
                 ++w;
             }
         }
     }
+    if (!writes) return;
     if (bond_ok) {
         const int64_t o = G.state_off + sidx * 3;
         state[o] = qx;
@@ -308,20 +349,20 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
     flush_clamps(clamps, a.clamps + gidx);
 }
 
-template <typename T>
-__device__ __forceinline__ void pair_item(const FwdArgs& a, int item, T (*xs)[4]) {
+template <typename T, int WAVES>
+__device__ __forceinline__ void pair_item(const FwdArgs& a, int item, T (*xs)[4], int wave, PairShare<T>* sh) {
     if (item >= a.n_items) return;
-    if (*(const volatile int*)a.status & 1) return;   // invalid parent: no work
+    if (*(const volatile int*)a.status & 1) return;   // invalid parent: no work (whole block)
     const Item it = a.items[item];
     const GroupDev& G = a.groups[it.g];
-    const bool lj = G.lj12u_d > 0.0;
-    switch (G.spring * 2 + (lj ? 1 : 0)) {
-    case 0: run_pair<T, 0, false>(a, G, it.k0, xs); break;
-    case 1: run_pair<T, 0, true>(a, G, it.k0, xs); break;
-    case 2: run_pair<T, 1, false>(a, G, it.k0, xs); break;
-    case 3: run_pair<T, 1, true>(a, G, it.k0, xs); break;
-    case 4: run_pair<T, 2, false>(a, G, it.k0, xs); break;
-    default: run_pair<T, 2, true>(a, G, it.k0, xs); break;
+    if (G.lj12u_d > 0.0) {
+        if (G.spring == 0) run_pair<T, 0, true, WAVES>(a, G, it.k0, xs, wave, sh);
+        else if (G.spring == 1) run_pair<T, 1, true, WAVES>(a, G, it.k0, xs, wave, sh);
+        else run_pair<T, 2, true, WAVES>(a, G, it.k0, xs, wave, sh);
+    } else if (wave == 0 || WAVES == 1) {             // springs alone: nothing to share
+        if (G.spring == 0) run_pair<T, 0, false, 1>(a, G, it.k0, xs, wave, sh);
+        else if (G.spring == 1) run_pair<T, 1, false, 1>(a, G, it.k0, xs, wave, sh);
+        else run_pair<T, 2, false, 1>(a, G, it.k0, xs, wave, sh);
     }
 }
 
@@ -329,7 +370,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void fwd_pair_kernel(FwdArgs a) {
     __shared__ T xs[4][2 * WAVE][4];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    pair_item<T>(a, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave, xs[wave]);
+    pair_item<T, 1>(a, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave, xs[wave], wave, nullptr);
 }
 
 // Two contexts in one launch (see fwd_dual_kernel): blocks [0, blocks_a) run a.
@@ -338,13 +379,53 @@ __global__ __launch_bounds__(256) void fwd_pair_dual_kernel(FwdArgs a, FwdArgs b
     __shared__ T xs[4][2 * WAVE][4];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wpb = (int)(blockDim.x >> 6);
-    if ((int)blockIdx.x < blocks_a) pair_item<T>(a, (int)blockIdx.x * wpb + wave, xs[wave]);
-    else pair_item<T>(b, ((int)blockIdx.x - blocks_a) * wpb + wave, xs[wave]);
+    const bool first = (int)blockIdx.x < blocks_a;
+    const int block = first ? (int)blockIdx.x : (int)blockIdx.x - blocks_a;
+    pair_item<T, 1>(first ? a : b, block * wpb + wave, xs[wave], wave, nullptr);
+}
+
+// Few work items: one workgroup each; items [0, a.n_items) are a's, the rest b's.
+template <typename T, int WAVES>
+__global__ __launch_bounds__(WAVE * WAVES) void fwd_pair_shared_kernel(FwdArgs a, FwdArgs b) {
+    __shared__ T xs[WAVES][2 * WAVE][4];
+    __shared__ PairShare<T> sh;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool first = (int)blockIdx.x < a.n_items;
+    pair_item<T, WAVES>(first ? a : b, first ? (int)blockIdx.x : (int)blockIdx.x - a.n_items, xs[wave], wave, &sh);
+}
+
+// Wavefronts per work item. Measured, us a step at 512 / 768 / 1024 / 1280 / 1536
+// items with four, two and one: FP32, 50 beads 1.40 1.76 2.16 2.78 3.11, 1.91 1.94 2.15
+// 2.63 3.14, 2.54 2.58 2.68 3.32 3.33; 24 beads 1.41 1.73 2.08, 1.50 1.60 1.74 2.04 2.32,
+// 1.93 1.97 2.01 2.37 2.37; FP64, 50 beads 3.20 4.87 6.11, 4.48 4.62 5.10 7.18,
+// 4.77 4.91 4.97 7.93. Four share the work best while a CU holds two items; from
+// there the state that each steps for itself costs more than their overlap gives.
+static int pair_waves(int n_items, int precision) {
+    if (n_items <= 512) return 4;
+    return n_items <= (precision == 64 ? 768 : 1280) ? 2 : 1;
+}
+
+template <typename T> static void launch_shared(const FwdArgs& a, const FwdArgs& b, int waves, hipStream_t st) {
+    const dim3 grid((unsigned)(a.n_items + b.n_items)), block(WAVE * waves);
+    if (waves == 4) hipLaunchKernelGGL((fwd_pair_shared_kernel<T, 4>), grid, block, 0, st, a, b);
+    else hipLaunchKernelGGL((fwd_pair_shared_kernel<T, 2>), grid, block, 0, st, a, b);
+}
+
+static hipError_t launch_pair_shared(const FwdArgs& a, const FwdArgs& b, int precision, int waves, hipStream_t st) {
+    if (precision == 64) launch_shared<double>(a, b, waves, st);
+    else launch_shared<float>(a, b, waves, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_forward_pair(const FwdArgs& a, int precision, int waves_per_block, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     if (a.n_items <= 0 || a.n_steps <= 0) return hipSuccess;
+    const int shared = pair_waves(a.n_items, precision);
+    if (shared > 1) {
+        FwdArgs none = a;
+        none.n_items = 0;
+        return launch_pair_shared(a, none, precision, shared, st);
+    }
     const int wpb = waves_per_block;
     dim3 grid((a.n_items + wpb - 1) / wpb), block(WAVE * wpb);
     if (precision == 64) hipLaunchKernelGGL(fwd_pair_kernel<double>, grid, block, 0, st, a);
@@ -358,6 +439,8 @@ hipError_t launch_forward_pair_dual(const FwdArgs& a, const FwdArgs& b, int prec
     const int wpb = waves_per_block;
     const int ba = (a.n_items + wpb - 1) / wpb, bb = (b.n_items + wpb - 1) / wpb;
     if (ba + bb == 0) return hipSuccess;
+    const int shared = pair_waves(a.n_items + b.n_items, precision);
+    if (shared > 1) return launch_pair_shared(a, b, precision, shared, st);
     dim3 grid((unsigned)(ba + bb)), block(WAVE * wpb);
     if (precision == 64) hipLaunchKernelGGL(fwd_pair_dual_kernel<double>, grid, block, 0, st, a, b, ba);
     else hipLaunchKernelGGL(fwd_pair_dual_kernel<float>, grid, block, 0, st, a, b, ba);

@@ -148,3 +148,33 @@ def test_pair_full_size_collapsed50_first_window_per_replica():
     err = rel_err(smp[0, :4], orr.samples()[0][0], _floor(g))
     announce("collapsed50 window 0 replicas 0-3 rel err %.2e" % err)
     assert err < 1e-4
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("N", [2, 3, 4, 5, 7, 8, 12, 32, 33, 50, 63, 64])
+def test_pair_wavefronts_per_item_keep_the_bits(N, precision):
+    # four, two and one wavefronts per work item (up to 512, up to 1280 or 768, and
+    # more items): the first replicas agree to the bit. Calls of 1-9 steps end
+    # inside and at the edges of a round of shared noise.
+    from paper_2206_05851_amd import ra
+    spring, H, b = [(wl.HARMONIC, 50.0, 0.0), (wl.FENE, 3.0, 20.0), (wl.HOOKEAN, 2.0, 0.0)][N % 3]
+    P = 64 // N
+    few = 2 * P + 1
+    out = []
+    for items in (3, 600, 1300):
+        R = few if items == 3 else items * P
+        g = wl.group(N, R, 1e-5, spring, H, b, wl.SHEAR, 5.0, rest_length=2.0 if spring == wl.HARMONIC else 0.0,
+                     lj_eps=0.7, lj_rmin=2.0 if spring == wl.HARMONIC else 1.0, stream_id=3)
+        p = _parent(g, 11)
+        announce("pair wavefronts N=%d precision=%d items=%d" % (N, precision, items))
+        rep = ra.Replicas([g], 13, precision=precision, sample_every=7, max_windows=5, tsf=True)
+        rep.init_chains([p])
+        for c in (1, 2, 3, 4, 5, 9, 8, 3):   # 35
+            rep.step(c)
+        smp, tsf = rep.samples(tsf=True)
+        out.append([x.cpu().numpy() for x in (smp[0][:, :few], tsf[0][:, :few], rep.bonds()[0][:few])])
+        rep.sync_status()
+        assert np.all(np.isfinite(out[-1][2]))
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.array_equal(x, y)
