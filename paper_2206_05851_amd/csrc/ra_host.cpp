@@ -507,13 +507,16 @@ ra_status ra_init_chains(ra_ctx* c, const double* parent_xyz) {
     if (!parent_xyz) return fail(c, RA_EINVAL, "parent_xyz is null");
     const int ng = (int)c->descs.size();
     // device-side resets are kernels ordered on the context's stream
-    HIPCHK(c, launch_reset(c->status, c->clamps, ng, c->dstep, c->stream));
-    const bool plain = c->run.plain != 0;
     c->cur = 0;
-    HIPCHK(c, launch_clone(c->dgroups, ng, c->max_group_elems, parent_xyz, c->dpar_off,
-                           plain ? c->pos[0] : c->state, c->tsf_acc, c->status, c->run.precision, plain,
-                           c->stream));
-    HIPCHK(c, launch_src_from_xyz(c->dgroups, ng, parent_xyz, c->dpar_off, c->src, c->stream));
+    if (c->run.plain) {
+        HIPCHK(c, launch_reset(c->status, c->clamps, ng, c->dstep, c->stream));
+        HIPCHK(c, launch_clone_plain(c->dgroups, ng, c->max_group_elems, parent_xyz, c->dpar_off, c->pos[0],
+                                     c->tsf_acc, c->status, c->run.precision, c->stream));
+        HIPCHK(c, launch_src_from_xyz(c->dgroups, ng, parent_xyz, c->dpar_off, c->src, c->stream));
+    } else {
+        HIPCHK(c, launch_init(c->dgroups, ng, c->max_group_elems, parent_xyz, c->dpar_off, c->state, c->tsf_acc,
+                              c->status, c->clamps, c->dstep, c->src, c->run.precision, c->stream));
+    }
     c->step = 0;
     c->initialised = true;
     c->recloned = false;
@@ -658,10 +661,10 @@ ra_status ra_average_forces(ra_ctx* c, double* mean, double* stdv, double* tsf_m
     if (n_windows) *n_windows = W;
     if (mean || stdv)
         HIPCHK(c, launch_reduce(c->dgroups, c->dtiles, (int)c->htiles.size(), W, c->samples, c->smp_total,
-                                c->spr_total, mean, stdv, c->run.precision, c->stream));
+                                c->spr_total, mean, stdv, c->run.precision, nullptr, c->stream));
     if (tsf_mean || tsf_std)
         HIPCHK(c, launch_reduce(c->dgroups, c->dtiles, (int)c->htiles.size(), W, c->tsf, c->smp_total,
-                                c->spr_total, tsf_mean, tsf_std, c->run.precision, c->stream));
+                                c->spr_total, tsf_mean, tsf_std, c->run.precision, nullptr, c->stream));
     return RA_OK;
 }
 

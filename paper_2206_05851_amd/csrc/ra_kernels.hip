@@ -1,6 +1,7 @@
 // ra_kernels.hip — gfx950 kernels of the replica-averaged BD library outside
 // the fused step loops: clone, plain path, replica reduction, Bell rates,
 // inspection; and the launchers that pick a forward kernel (ra_forward.hpp).
+#include "ra_clone.hpp"
 #include "ra_chain.hpp"
 #include "ra_launch.hpp"
 
@@ -25,29 +26,44 @@ __global__ void reset_kernel(int32_t* status, unsigned long long* clamps, int n_
 // ---------------------------------------------------------------------------
 // Clone (RSF, Sec. II): Q_j = parent_{j+1} - parent_j in FP64, then rounded to
 // the state precision, for every replica; the parent is validated here.
+// In the same launch the first wavefront of block (0, g) writes group g's clone source,
+// and with one group, where no other block needs the status word, block 0 also
+// does reset_kernel's work (a launch in a row costs 2-5 us each: a window of 50
+// replicas 110.3 -> 108.7 us).
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void clone_kernel(const GroupDev* __restrict__ groups, const double* __restrict__ parent,
-                             const int64_t* __restrict__ par_off, T* __restrict__ state,
-                             double* __restrict__ tsf_acc, int32_t* status) {
+__global__ __launch_bounds__(256) void clone_kernel(const GroupDev* __restrict__ groups,
+                                                    const double* __restrict__ parent,
+                                                    const int64_t* __restrict__ par_off, T* __restrict__ state,
+                                                    double* __restrict__ tsf_acc, int32_t* status,
+                                                    unsigned long long* clamps, int64_t* step,
+                                                    double* __restrict__ src) {
     const GroupDev& G = groups[blockIdx.y];
     const int nm1 = G.N - 1;
     const int64_t total = (int64_t)G.R * nm1;
     const double* p = parent + par_off[blockIdx.y];
+    if (blockIdx.x == 0) {
+        bool bad = false;
+        for (int j = threadIdx.x; j < nm1; j += blockDim.x) bad |= !clone_bond(p, j, G).ok;
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) {
+            if (gridDim.y == 1) {
+                *status = bad ? 1 : 0;
+                *step = 0;
+                *clamps = 0ull;
+            } else if (bad) {
+                atomicOr(status, 1);
+            }
+        }
+        if (threadIdx.x < WAVE) clone_source(p, src + par_off[blockIdx.y], G.N);
+    }
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = e / nm1;
-        const int j = (int)(e - k * nm1);
-        const double qx = p[3 * (j + 1)] - p[3 * j];
-        const double qy = p[3 * (j + 1) + 1] - p[3 * j + 1];
-        const double qz = p[3 * (j + 1) + 2] - p[3 * j + 2];
-        bool bad = !(__builtin_isfinite(qx) && __builtin_isfinite(qy) && __builtin_isfinite(qz));
-        if (G.spring == 1 && !((qx * qx + qy * qy + qz * qz) * G.inv_q0sq_d < 1.0)) bad = true;
-        if (bad && k == 0) atomicOr(status, 1);
+        const CloneBond q = clone_bond(p, (int)(e % nm1), G);
         const int64_t o = G.state_off + e * 3;
-        state[o] = (T)qx;
-        state[o + 1] = (T)qy;
-        state[o + 2] = (T)qz;
+        state[o] = (T)q.x;
+        state[o + 1] = (T)q.y;
+        state[o + 2] = (T)q.z;
         if (tsf_acc) tsf_acc[G.smp_off + e] = 0.0;
     }
 }
@@ -203,7 +219,8 @@ __global__ __launch_bounds__(WAVE * RED_WAVES) void reduce_kernel(const GroupDev
                                                                const ColTile* __restrict__ tiles,
                                                                const T* __restrict__ smp, int64_t smp_total,
                                                                int64_t spr_total, double* __restrict__ mean,
-                                                               double* __restrict__ stdv) {
+                                                               double* __restrict__ stdv,
+                                                               const int32_t* __restrict__ nan_if) {
     __shared__ double part[RED_WAVES][WAVE];
     const ColTile tile = tiles[blockIdx.x];
     const int64_t w = blockIdx.y;
@@ -244,8 +261,9 @@ __global__ __launch_bounds__(WAVE * RED_WAVES) void reduce_kernel(const GroupDev
 #pragma unroll
         for (int v = 0; v < RED_WAVES; ++v) sst += part[v][lane];
         const int64_t o = w * spr_total + G.spr_off + j;
-        if (mean) mean[o] = mu;
-        if (stdv) stdv[o] = G.R > 1 ? sqrt(sst / (double)(G.R - 1)) : 0.0;
+        const bool nan = nan_if && *nan_if != 0;
+        if (mean) mean[o] = nan ? __builtin_nan("") : mu;
+        if (stdv) stdv[o] = nan ? __builtin_nan("") : G.R > 1 ? sqrt(sst / (double)(G.R - 1)) : 0.0;
     }
 }
 
@@ -396,26 +414,37 @@ hipError_t launch_reset(int32_t* status, unsigned long long* clamps, int n_group
     return hipGetLastError();
 }
 
-hipError_t launch_clone(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
-                        const int64_t* par_off, void* state, double* tsf_acc, int32_t* status, int precision,
-                        bool plain, hipStream_t st) {
+// Fused path: everything that starts a run, in one launch or, with several groups,
+// after a reset.
+hipError_t launch_init(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
+                       const int64_t* par_off, void* state, double* tsf_acc, int32_t* status,
+                       unsigned long long* clamps, int64_t* step, double* src, int precision, hipStream_t st) {
+    (void)hipGetLastError();   // report only this launch's own error
+    if (n_groups > 1) {
+        const hipError_t e = launch_reset(status, clamps, n_groups, step, st);
+        if (e != hipSuccess) return e;
+    }
+    dim3 grid((unsigned)std::min<int64_t>((max_elems + 255) / 256, 4096), (unsigned)n_groups), block(256);
+    if (precision == 64)
+        hipLaunchKernelGGL(clone_kernel<double>, grid, block, 0, st, groups, parent, par_off, (double*)state, tsf_acc,
+                           status, clamps, step, src);
+    else
+        hipLaunchKernelGGL(clone_kernel<float>, grid, block, 0, st, groups, parent, par_off, (float*)state, tsf_acc,
+                           status, clamps, step, src);
+    return hipGetLastError();
+}
+
+hipError_t launch_clone_plain(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
+                              const int64_t* par_off, void* pos, double* tsf_acc, int32_t* status, int precision,
+                              hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     dim3 grid((unsigned)std::min<int64_t>((max_elems + 255) / 256, 4096), (unsigned)n_groups), block(256);
-    if (plain) {
-        if (precision == 64)
-            hipLaunchKernelGGL(clone_pos_kernel<double>, grid, block, 0, st, groups, parent, par_off,
-                               (double*)state, tsf_acc, status);
-        else
-            hipLaunchKernelGGL(clone_pos_kernel<float>, grid, block, 0, st, groups, parent, par_off,
-                               (float*)state, tsf_acc, status);
-    } else {
-        if (precision == 64)
-            hipLaunchKernelGGL(clone_kernel<double>, grid, block, 0, st, groups, parent, par_off,
-                               (double*)state, tsf_acc, status);
-        else
-            hipLaunchKernelGGL(clone_kernel<float>, grid, block, 0, st, groups, parent, par_off,
-                               (float*)state, tsf_acc, status);
-    }
+    if (precision == 64)
+        hipLaunchKernelGGL(clone_pos_kernel<double>, grid, block, 0, st, groups, parent, par_off, (double*)pos,
+                           tsf_acc, status);
+    else
+        hipLaunchKernelGGL(clone_pos_kernel<float>, grid, block, 0, st, groups, parent, par_off, (float*)pos, tsf_acc,
+                           status);
     return hipGetLastError();
 }
 
@@ -463,16 +492,16 @@ hipError_t launch_plain_sample(const GroupDev* groups, int g, int64_t n_threads,
 
 hipError_t launch_reduce(const GroupDev* groups, const ColTile* tiles, int n_tiles, int64_t n_windows,
                          const void* smp, int64_t smp_total, int64_t spr_total, double* mean, double* stdv,
-                         int precision, hipStream_t st) {
+                         int precision, const int32_t* nan_if, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     if (n_tiles == 0 || n_windows == 0) return hipSuccess;
     dim3 grid((unsigned)n_tiles, (unsigned)n_windows), block(WAVE * RED_WAVES);
     if (precision == 64)
         hipLaunchKernelGGL(reduce_kernel<double>, grid, block, 0, st, groups, tiles, (const double*)smp,
-                           smp_total, spr_total, mean, stdv);
+                           smp_total, spr_total, mean, stdv, nan_if);
     else
         hipLaunchKernelGGL(reduce_kernel<float>, grid, block, 0, st, groups, tiles, (const float*)smp,
-                           smp_total, spr_total, mean, stdv);
+                           smp_total, spr_total, mean, stdv, nan_if);
     return hipGetLastError();
 }
 

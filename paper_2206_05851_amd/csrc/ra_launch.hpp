@@ -83,9 +83,12 @@ void launch_forward_dual_f64(const FwdArgs& a, const FwdArgs& b, int blocks_a, i
                              hipStream_t st);
 hipError_t launch_advance(int64_t* step, int64_t n, hipStream_t st);
 hipError_t launch_reset(int32_t* status, unsigned long long* clamps, int n_groups, int64_t* step, hipStream_t st);
-hipError_t launch_clone(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
-                        const int64_t* par_off, void* state, double* tsf_acc, int32_t* status, int precision,
-                        bool plain, hipStream_t st);
+hipError_t launch_init(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
+                       const int64_t* par_off, void* state, double* tsf_acc, int32_t* status,
+                       unsigned long long* clamps, int64_t* step, double* src, int precision, hipStream_t st);
+hipError_t launch_clone_plain(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
+                              const int64_t* par_off, void* pos, double* tsf_acc, int32_t* status, int precision,
+                              hipStream_t st);
 hipError_t launch_plain_step(const GroupDev* groups, int g, int64_t n_threads, bool fene, const void* rin,
                              void* rout, const int32_t* status, uint32_t n, uint32_t key0, uint32_t key1,
                              unsigned long long* clamps, int precision, hipStream_t st);
@@ -94,7 +97,7 @@ hipError_t launch_plain_sample(const GroupDev* groups, int g, int64_t n_threads,
                                int32_t* status, int precision, hipStream_t st);
 hipError_t launch_reduce(const GroupDev* groups, const ColTile* tiles, int n_tiles, int64_t n_windows,
                          const void* smp, int64_t smp_total, int64_t spr_total, double* mean, double* stdv,
-                         int precision, hipStream_t st);
+                         int precision, const int32_t* nan_if, hipStream_t st);   // *nan_if != 0: all NaN
 hipError_t launch_bell(const GroupDev* groups, int n_groups, int64_t n_windows, const double* mean,
                        int64_t spr_total, double k0, double xd, double* rates, double* rate_sum,
                        uint8_t* events, int S, uint32_t key0, uint32_t key1, hipStream_t st);

@@ -11,6 +11,7 @@
 //     (R_Gz, Sec. IV).
 // None of these is on the per-step path; they run once per window or per
 // analysis call, with fixed summation orders so results are reproducible.
+#include "ra_clone.hpp"
 #include "ra_device.hpp"
 #include "ra_launch.hpp"
 
@@ -20,12 +21,6 @@ namespace ra {
 // Wave helpers (FP64): fixed-shape butterfly sum and an inclusive Hillis-Steele
 // scan over the 64 lanes.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return v;
-}
-
 __device__ __forceinline__ double wave_incl_scan_d(double v, int lane) {
 #pragma unroll
     for (int off = 1; off < WAVE; off <<= 1) {
@@ -81,23 +76,13 @@ __device__ void com_frame_from_bonds(const T* bonds, int N, double* out, int lan
     }
 }
 
-// Clone source from FP64 bead positions: src = parent - centre of mass.
+// Clone source from FP64 bead positions.
 __global__ __launch_bounds__(64) void src_from_xyz_kernel(const GroupDev* __restrict__ groups,
                                                           const double* __restrict__ parent,
                                                           const int64_t* __restrict__ par_off,
                                                           double* __restrict__ src) {
-    const GroupDev& G = groups[blockIdx.x];
-    const int lane = threadIdx.x;
-    const double* p = parent + par_off[blockIdx.x];
-    double* o = src + par_off[blockIdx.x];
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    for (int i = lane; i < G.N; i += WAVE) { sx += p[3 * i]; sy += p[3 * i + 1]; sz += p[3 * i + 2]; }
-    const double cx = wave_sum_d(sx) / G.N, cy = wave_sum_d(sy) / G.N, cz = wave_sum_d(sz) / G.N;
-    for (int i = lane; i < G.N; i += WAVE) {
-        o[3 * i] = p[3 * i] - cx;
-        o[3 * i + 1] = p[3 * i + 1] - cy;
-        o[3 * i + 2] = p[3 * i + 2] - cz;
-    }
+    const int64_t o = par_off[blockIdx.x];
+    clone_source(parent + o, src + o, groups[blockIdx.x].N);
 }
 
 // ---------------------------------------------------------------------------

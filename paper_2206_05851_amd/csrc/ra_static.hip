@@ -12,6 +12,7 @@
 #include <string>
 
 #include "ra.h"
+#include "ra_clone.hpp"
 #include "ra_launch.hpp"
 #include "ra_tune.hpp"
 #include "ra_types.hpp"
@@ -50,34 +51,38 @@ hipError_t scratch_address(void** out) {
     return hipSuccess;
 }
 
-// Clears the call's counters (status, guard count, step) and writes the
-// group descriptor, the work list (wavefront i: replicas [i P, i P + P)) and
-// the reduction's column tiles into the scratch array: the previous call's
-// contents are never read.
-__global__ void static_setup_kernel(GroupDev G, GroupDev* groups, Item* items, int n_items, ColTile* tiles,
-                                    int n_tiles, int32_t* status, unsigned long long* clamps, int64_t* step,
-                                    int64_t* par_off) {
+// Clears the call's counters (guard count, step), validates the parent (status),
+// clones it and writes the group descriptor, the work list (wavefront i: replicas
+// [i P, i P + P)) and the reduction's column tiles into the scratch array: the
+// previous call's contents are never read. One launch: 20 replicas of 50 beads for
+// 75 steps are bound by launches (six and the steps 41.4 us, three 31.0).
+template <typename T>
+__global__ __launch_bounds__(256) void static_setup_kernel(GroupDev G, GroupDev* groups, Item* items, int n_items,
+                                                           ColTile* tiles, int n_tiles, int32_t* status,
+                                                           unsigned long long* clamps, int64_t* step,
+                                                           const double* __restrict__ parent, T* __restrict__ state) {
     const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     const int stride = (int)(gridDim.x * blockDim.x);
-    if (t == 0) {
-        groups[0] = G;
-        *status = 0;
-        *clamps = 0ull;
-        *step = 0;
-        par_off[0] = 0;
+    const int nm1 = G.N - 1;
+    if (blockIdx.x == 0) {
+        bool bad = false;
+        for (int j = threadIdx.x; j < nm1; j += blockDim.x) bad |= !clone_bond(parent, j, G).ok;
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) {
+            groups[0] = G;
+            *status = bad ? 1 : 0;
+            *clamps = 0ull;
+            *step = 0;
+        }
     }
     for (int i = t; i < n_items; i += stride) items[i] = Item{0, i * G.P};
     for (int i = t; i < n_tiles; i += stride) tiles[i] = ColTile{0, i * WAVE};
-}
-
-// An invalid parent (no steps were run) or a non-finite tension: every output
-// element becomes NaN, the in-band error of this entry point.
-__global__ void static_poison_kernel(const int32_t* status, double* mean, double* stdv, int64_t n) {
-    if (*(const volatile int32_t*)status == 0) return;
-    const double nan = __builtin_nan("");
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        if (mean) mean[e] = nan;
-        if (stdv) stdv[e] = nan;
+    const int64_t total = (int64_t)G.R * nm1;
+    for (int64_t e = t; e < total; e += stride) {
+        const CloneBond q = clone_bond(parent, (int)(e % nm1), G);
+        state[3 * e] = (T)q.x;
+        state[3 * e + 1] = (T)q.y;
+        state[3 * e + 2] = (T)q.z;
     }
 }
 
@@ -118,14 +123,8 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     if (run->noise_map == 2 && family != 16)
         return fail_static(RA_EINVAL, "ra_run_static: noise_map 2 needs n_beads > 256 at precision 32");
     const int forced = run->tile_policy > 1000 ? run->tile_policy - 1000 : 0;
-    const int M = choose_tiles(&d, 1, family, run->precision, forced, run->noise_map)[0];
-    GroupDev G = make_group(d, M, 0, run->noise_map);
+    int M = choose_tiles(&d, 1, family, run->precision, forced, run->noise_map)[0];
     const int64_t nm1 = d.n_beads - 1;
-    G.state_off = 0;
-    G.smp_off = 0;
-    G.spr_off = 0;
-    G.pos_off = 0;
-    const int n_items = (d.n_replicas + G.P - 1) / G.P;
     const int n_tiles = (int)((nm1 + WAVE - 1) / WAVE);
     const size_t esz = run->precision == 64 ? 8 : 4;
     const int64_t state_total = (int64_t)d.n_replicas * nm1 * 3;
@@ -134,21 +133,35 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     // scratch layout, every part on a 256-byte boundary
     size_t off = 0;
     const size_t o_groups = off;  off = align256(off + sizeof(GroupDev));
-    const size_t o_items = off;   off = align256(off + sizeof(Item) * (size_t)n_items);
     const size_t o_tiles = off;   off = align256(off + sizeof(ColTile) * (size_t)n_tiles);
     const size_t o_status = off;  off = align256(off + sizeof(int32_t));
     const size_t o_clamps = off;  off = align256(off + sizeof(unsigned long long));
     const size_t o_step = off;    off = align256(off + sizeof(int64_t));
-    const size_t o_paroff = off;  off = align256(off + sizeof(int64_t));
+    off = align256(off + sizeof(int64_t));   // unused: the limit stays where it was
     const size_t o_state = off;   off = align256(off + esz * (size_t)state_total);
-    const size_t o_smp = off;
+    const size_t o_items = off;
     const double smp_bytes = (double)esz * (double)smp_total * (double)W;
-    if ((double)off + smp_bytes > (double)STATIC_SCRATCH_BYTES) {
+    auto items_of = [&](int m) {
+        const int P = std::max(1, WAVE / ((d.n_beads + m - 1) / m));
+        return (d.n_replicas + P - 1) / P;
+    };
+    auto scratch_bytes = [&](int m) { return (double)(off + align256(sizeof(Item) * (size_t)items_of(m))) + smp_bytes; };
+    // a narrow tile's longer work list does not lower the limit
+    if (scratch_bytes(M) > (double)STATIC_SCRATCH_BYTES)
+        M = choose_beads_per_lane(d.n_beads, d.n_replicas, family, forced, run->noise_map);
+    if (scratch_bytes(M) > (double)STATIC_SCRATCH_BYTES) {
         char b[200];
         std::snprintf(b, sizeof b, "ra_run_static: needs %.0f bytes of scratch (state, samples, descriptors); "
-                      "the limit is %zu", (double)off + smp_bytes, STATIC_SCRATCH_BYTES);
+                      "the limit is %zu", scratch_bytes(M), STATIC_SCRATCH_BYTES);
         return fail_static(RA_EINVAL, b);
     }
+    GroupDev G = make_group(d, M, 0, run->noise_map);
+    G.state_off = 0;
+    G.smp_off = 0;
+    G.spr_off = 0;
+    G.pos_off = 0;
+    const int n_items = (d.n_replicas + G.P - 1) / G.P;
+    const size_t o_smp = off + align256(sizeof(Item) * (size_t)n_items);
 
     void* base_v = nullptr;
     hipError_t e = scratch_address(&base_v);
@@ -160,7 +173,6 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     int32_t* status = (int32_t*)(base + o_status);
     unsigned long long* clamps = (unsigned long long*)(base + o_clamps);
     int64_t* step = (int64_t*)(base + o_step);
-    int64_t* par_off = (int64_t*)(base + o_paroff);
     void* state = base + o_state;
     void* samples = base + o_smp;
     hipStream_t st = (hipStream_t)hip_stream;
@@ -171,12 +183,14 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
         if (e_ != hipSuccess) return fail_static(RA_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
     (void)hipGetLastError();   // report only this call's own errors
-    const int setup_blocks = std::min(1024, std::max(1, (n_items + 255) / 256));
-    hipLaunchKernelGGL(static_setup_kernel, dim3(setup_blocks), dim3(256), 0, st, G, groups, items, n_items, tiles,
-                       n_tiles, status, clamps, step, par_off);
+    const int setup_blocks = (int)std::min<int64_t>(1024, (smp_total + 255) / 256);
+    if (run->precision == 64)
+        hipLaunchKernelGGL(static_setup_kernel<double>, dim3(setup_blocks), dim3(256), 0, st, G, groups, items, n_items,
+                           tiles, n_tiles, status, clamps, step, parent_xyz, (double*)state);
+    else
+        hipLaunchKernelGGL(static_setup_kernel<float>, dim3(setup_blocks), dim3(256), 0, st, G, groups, items, n_items,
+                           tiles, n_tiles, status, clamps, step, parent_xyz, (float*)state);
     SCHK(hipGetLastError());
-    SCHK(launch_clone(groups, 1, (int64_t)d.n_replicas * d.n_beads * 3, parent_xyz, par_off, state, nullptr, status,
-                      run->precision, false, st));
     FwdArgs a{};
     a.groups = groups;
     a.items = items;
@@ -197,13 +211,11 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     for (int64_t done = 0; done < n_steps; done += chunk) {
         a.n_steps = std::min(chunk, n_steps - done);
         SCHK(launch_forward(a, run->precision, family, wpb, M, run->noise_map, st));
-        SCHK(launch_advance(step, a.n_steps, st));
+        if (done + a.n_steps < n_steps) SCHK(launch_advance(step, a.n_steps, st));
     }
-    SCHK(launch_reduce(groups, tiles, n_tiles, W, samples, smp_total, nm1, mean, stdv, run->precision, st));
-    const int64_t n_out = W * nm1;
-    hipLaunchKernelGGL(static_poison_kernel, dim3((unsigned)std::min<int64_t>((n_out + 255) / 256, 1024)), dim3(256),
-                       0, st, status, mean, stdv, n_out);
-    SCHK(hipGetLastError());
+    // an invalid parent (no steps were run) or a non-finite tension: every output
+    // element becomes NaN, the in-band error of this entry point
+    SCHK(launch_reduce(groups, tiles, n_tiles, W, samples, smp_total, nm1, mean, stdv, run->precision, status, st));
 #undef SCHK
     return RA_OK;
 }

@@ -25,7 +25,7 @@ static bool legal(int n_beads, int M) { return (n_beads + M - 1) / M <= 64; }
 
 bool map_allows(int nmap, int M) { return nmap != 2 || M % 4 == 0; }
 
-static int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap, int widest) {
+int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap, int widest) {
     const auto& cand = family_beads_per_lane(family);
     if (forced > 0 && legal(n_beads, forced) && map_allows(nmap, forced))
         for (int m : cand)

@@ -24,6 +24,7 @@ const std::vector<int>& family_beads_per_lane(int family);
 // beads, 300 replicas, gradient with every state kept: M = 4 162 + 222 us, M = 2
 // 118 + 141). A step's results do not depend on the tile.
 bool map_allows(int nmap, int M);
+int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, int nmap, int widest = 64);
 std::vector<int> choose_tiles(const ra_chain_desc* groups, int n_groups, int family, int precision, int forced,
                               int nmap);
 

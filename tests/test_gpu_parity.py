@@ -560,3 +560,35 @@ def test_tile_of_few_items_is_narrow_and_keeps_the_bits(N, R, precision, M):
     assert np.array_equal(rep.samples()[0].cpu().numpy(), wide.samples()[0].cpu().numpy())
     rep.sync_status()
     wide.sync_status()
+
+
+@pytest.mark.parametrize("n_groups", [1, 2])
+@pytest.mark.parametrize("precision", [32, 64])
+def test_init_validates_the_parent_and_clears_the_last_run(n_groups, precision):
+    # with one group the launch that clones also clears the status and step; a FENE
+    # bond past full extension (in the last group, past its first 256 bonds or not)
+    # or a NaN marks the run, and the next init starts clean
+    from paper_2206_05851_amd import ra
+    Ns = [20, 250 if precision == 64 else 700][-n_groups:]
+    groups = [wl.group(N, 5, 1e-4, wl.FENE, 1.0, 50.0, wl.SHEAR, 2.0, stream_id=i) for i, N in enumerate(Ns)]
+    good = [wl.equilibrium_parent(N, wl.FENE, 1.0, 50.0, seed=i) for i, N in enumerate(Ns)]
+    ref = None
+    for bad_value in (None, 1e3, np.nan, None):
+        parents = [p.copy() for p in good]
+        if bad_value is not None:
+            parents[-1][Ns[-1] - 1, 1] += bad_value
+        announce("init groups=%d precision=%d bad=%s" % (n_groups, precision, bad_value))
+        if ref is None:
+            rep = ra.Replicas(groups, 3, precision=precision, sample_every=5, max_windows=2)
+        rep.init_chains(parents)
+        rep.step(10)
+        smp = [x.cpu().numpy() for x in rep.samples()]
+        if bad_value is not None:
+            with pytest.raises(ra.RAError):
+                rep.sync_status()
+            continue
+        rep.sync_status()
+        if ref is None:
+            ref = smp
+        else:
+            assert all(np.array_equal(x, y) for x, y in zip(ref, smp))
