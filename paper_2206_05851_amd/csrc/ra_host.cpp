@@ -565,8 +565,8 @@ static ra_status enqueue_forward(ra_ctx* c, int64_t n_steps, hipStream_t st) {
 static ra_status enqueue_forward(ra_ctx* c, int64_t n_steps) { return enqueue_forward(c, n_steps, c->stream); }
 
 // n_a steps of context a and n_b steps of context b in one launch on a's
-// stream (same kernel family, precision and waves per block), then both
-// step-counter advances.
+// stream (same kernel family, precision and waves per block).
+// A re-clone of ca from cb follows and sets both step counters (reclone_kernel).
 static ra_status enqueue_forward_dual(ra_ctx* ca, int64_t n_a, ra_ctx* cb, int64_t n_b) {
     FwdArgs a = fwd_args(ca), b = fwd_args(cb);
     a.n_steps = n_a;
@@ -578,7 +578,6 @@ static ra_status enqueue_forward_dual(ra_ctx* ca, int64_t n_a, ra_ctx* cb, int64
     else
         HIPCHK(ca, launch_forward_dual(a, b, ca->run.precision, ca->family, ca->wpb, std::max(ca->max_m, cb->max_m),
                                        ca->run.noise_map, st));
-    HIPCHK(ca, launch_advance2(ca->dstep, n_a, cb->dstep, n_b, st));
     return RA_OK;
 }
 
@@ -753,7 +752,8 @@ static bool step_fits(const ra_ctx* c, int64_t n_steps, std::string& why) {
     return true;
 }
 
-ra_status ra_reclone(ra_ctx* c, const ra_ctx* parent) {
+// parent_steps: steps of the parent's last launch that its device counter still lacks
+static ra_status enqueue_reclone(ra_ctx* c, const ra_ctx* parent, int64_t parent_steps) {
     if (!c) return fail(nullptr, RA_EINVAL, "null context");
     ra_status st = check_parent(c, parent);
     if (st != RA_OK) return st;
@@ -762,11 +762,14 @@ ra_status ra_reclone(ra_ctx* c, const ra_ctx* parent) {
     const int ng = (int)c->hgroups.size();
     // one launch: replica states, clone source, and the device step counter
     HIPCHK(c, launch_reclone(c->dgroups, parent->dgroups, ng, c->max_group_elems, parent->state, c->state, c->tsf_acc,
-                             c->status, c->dpar_off, c->src, c->dstep, c->step, c->run.precision, c->stream));
+                             c->status, c->dpar_off, c->src, c->dstep, c->step, parent->dstep, parent_steps,
+                             c->run.precision, c->stream));
     c->initialised = true;
     c->recloned = true;
     return RA_OK;
 }
+
+ra_status ra_reclone(ra_ctx* c, const ra_ctx* parent) { return enqueue_reclone(c, parent, 0); }
 
 ra_status ra_rsf_cycle(ra_ctx* c, ra_ctx* parent, int64_t n_windows, int64_t parent_steps) {
     if (!c) return fail(nullptr, RA_EINVAL, "null context");
@@ -803,7 +806,7 @@ ra_status ra_rsf_cycle(ra_ctx* c, ra_ctx* parent, int64_t n_windows, int64_t par
         if (st != RA_OK) return fail(c, st, "parent: " + parent->err);
         parent->step += parent_steps;
         for (int64_t w = 0; w < n_windows; ++w) {
-            st = ra_reclone(c, parent);
+            st = enqueue_reclone(c, parent, w > 0 ? parent_steps : 0);
             if (st != RA_OK) return st;
             const bool both = w + 1 < n_windows;
             st = both ? enqueue_forward_dual(c, S, parent, parent_steps) : enqueue_forward(c, S);
