@@ -467,9 +467,23 @@ __device__ __forceinline__ T* ckpt_item(T* base, const GroupDev& G, int k_first)
     return base + G.ck_off + (int64_t)(k_first / G.P) * (M * 3 * G.P * G.L);
 }
 
-// FP32 rows through a buffer resource of exactly their size: the lanes past U get
-// an offset out of it, so their stores are dropped and their loads give 0 without
-// a branch in the step loops.
+template <typename T, int M>
+__device__ __forceinline__ void store_ckpt(const Lane<T, M>& s, T* __restrict__ dst, const GroupDev& G) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int U = G.P * G.L;
+    if (lane < U) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            dst[(3 * m) * U + lane] = s.qx[m];
+            dst[(3 * m + 1) * U + lane] = s.qy[m];
+            dst[(3 * m + 2) * U + lane] = s.qz[m];
+        }
+    }
+}
+
+// The same in FP32 through a buffer resource of exactly the rows' size: the lanes past
+// U get an offset out of it, so their stores are dropped and their loads give 0
+// without a branch in the step loops.
 template <int M> struct Rows {
     int offset, row;                // bytes: this lane's first value, one row
     __device__ __forceinline__ explicit Rows(const GroupDev& G) {
