@@ -55,24 +55,27 @@ VALU_PEAK_LANE_SLOTS = 256 * 4 * 16 * 2.4e9
 # Algorithmic lane-slots per replica*bead*step of the FENE forward step: the
 # gfx950 VALU instructions the step needs, one slot each, the same count for
 # every tile layout. Transcendentals (v_log, v_sqrt, v_sin, v_cos, v_rcp) are
-# not counted: they execute on the transcendental unit beside the VALU (on
-# large1000 the kernel issues 1.05x more VALU instructions than 4-cycle slots
-# exist in its active cycles; without the transcendentals, 0.95x).
-#   Philox4x32-10: 10 rounds x (2 v_mad_u64_u32 + 2 v_bitop3_b32)           = 40
+# not counted: they execute on the transcendental unit beside the VALU (an
+# earlier large1000 kernel issued 1.05x more VALU instructions than 4-cycle slots
+# exist in its active cycles; without the transcendentals, 0.95x). The peak is the
+# rate of one wavefront's stream per SIMD: adds, products, FMAs and logic of
+# two wavefronts can issue together, integer products, compares, selects, DPP
+# and FP64 cannot.
+#   Philox4x32-10: 4 for rounds 1-3 (their words of the step and of the bead
+#     are drawn apart), 7 rounds x (2 v_mad_u64_u32 + 2 v_bitop3_b32)          = 32
 #   uniform maps: 4 words x (v_alignbit_b32 + subtract)                        =  8
-#   Box-Muller, 3 normals: 2 log scalings + 3 radius products                  =  5
+#   Box-Muller: 2 log scalings (the amplitude is in the scale)                 =  2
 #     (beside them on the transcendental unit: 2 log, 2 sqrt, 3 sin/cos)
-#   FENE bond update: |Q|^2 (3), s, 1 - s, guard compare, g Q (3), neighbour
-#     Laplacian by DPP (9), noise difference by DPP (3), flow + EM increment
-#     (8), add (3)                                                            = 31
+#   FENE bond update: |Q|^2 (3), 1 - s, guard compare, force (3), its difference
+#     over the bead (3), radius x sine added (3), difference of the bead
+#     displacements (3), flow (4), add (3)                                    = 24
 #     (beside them: the reciprocal 1/(1 - s))
 # With noise map 1 a Philox block gives four normals and serves 4/3 bead-steps:
-#   Philox 40 x 3/4 = 30; uniform maps 8 x 3/4 = 6; Box-Muller with both outputs
-#   of the second pair (2 log scalings + 4 radius products) x 3/4 = 4.5;
-#   FENE bond update 31.
+#   Philox 32 x 3/4 = 24; uniform maps 8 x 3/4 = 6; log scalings 2 x 3/4 = 1.5;
+#   FENE bond update 24. (An earlier form of the step needed 84 and 71.5.)
 # Noise map 2 (beads in groups of four, three blocks per group and step) draws
 # and transforms the same 3/4 block per bead-step as map 1.
-SLOTS_PER_BEAD_STEP = {0: 40 + 8 + 5 + 31, 1: 30 + 6 + 4.5 + 31, 2: 30 + 6 + 4.5 + 31}
+SLOTS_PER_BEAD_STEP = {0: 32 + 8 + 2 + 24, 1: 24 + 6 + 1.5 + 24, 2: 24 + 6 + 1.5 + 24}
 # HBM bytes per launch of the headline's forward kernel, read with rocprofv3
 # counters (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 KiB, both factors from a 1 GiB
 # device copy in the same runs). Valid only for the kernel they were taken on:
@@ -80,8 +83,8 @@ SLOTS_PER_BEAD_STEP = {0: 40 + 8 + 5 + 31, 1: 30 + 6 + 4.5 + 31, 2: 30 + 6 + 4.5
 # launch tile (beads per lane, replicas per wavefront, kernel family) and the
 # noise map are recorded with the figure, and traffic is reported as null when
 # any of them differs.
-FWD_TRAFFIC = {"sha256": "4db2b2d7ac6e4b9e7fead47e53ba5fac9fdcdb728271da68bd6cfff70a7bbcf5", "noise_map": 2,
-               "tile": (16, 1, 16), "bytes": (48764.958 * 2.0 + 2655974.031) * 1024}
+FWD_TRAFFIC = {"sha256": "2d1aaed9014de8b9c2af1dae69891dfeff021719728b0186737188bbab48ae0c", "noise_map": 2,
+               "tile": (16, 1, 16), "bytes": (48753.5 * 2.0 + 2655976.406) * 1024}
 FWD_SOURCES = ("ra_fwd_wide.hip", "ra_forward.hpp", "ra_chain.hpp", "ra_device.hpp", "ra_types.hpp", "ra_launch.hpp")
 
 
@@ -95,13 +98,13 @@ def fwd_sources_digest(files=FWD_SOURCES):
 
 
 # The pair kernel's lane-slots per replica*bead*step on collapsed50 (N = 50):
-# non-transcendental VALU instructions per wavefront-step (one bead per lane)
-# of fwd_pair_dual_kernel<float>, from rocprofv3 --pmc SQ_INSTS_VALU
-# SQ_INSTS_VALU_TRANS_F32 SQ_WAVES: (636,828,191 - 43,547,252) / 1001 wavefronts
-# / 750 steps. It holds for the pair kernel sources with this digest only.
+# non-transcendental VALU instructions per replica-step (one bead per lane, two
+# wavefronts per replica) of fwd_pair_shared_kernel<float, 2>, from rocprofv3 --pmc
+# SQ_INSTS_VALU SQ_INSTS_VALU_TRANS_F32 SQ_WAVES: (732,517,773 - 45,066,518) / 1001
+# replicas / 750 steps. It holds for the pair kernel sources with this digest only.
 PAIR_SOURCES = ("ra_pair.hip", "ra_chain.hpp", "ra_device.hpp", "ra_dpp.hpp")
-PAIR_SLOTS = {"sha256": "ad605e15eed9f61ce0d2c49a4d6ed60cbfd68a769bb007705ed98ffad3646d11",
-              "slots": (636828191.0 - 43547252.0) / 1001 / 750}
+PAIR_SLOTS = {"sha256": "30fd29552ee7f10cb4b486fab8663ff9f3f061971bb159b03832015963e8e455",
+              "slots": (732517773.0 - 45066518.0) / 1001 / 750}
 FP32_VECTOR_PEAK = 157.3e12   # FLOP/s, packed FP32 included
 
 

@@ -79,8 +79,9 @@ typedef enum { RA_QUIESCENT = 0, RA_UNIAXIAL = 1, RA_PLANAR = 2, RA_SHEAR = 3 } 
  * = 6 pi eta a), D_ij the RPY tensor of Eq. 3, drift dt D F / kT and random
  * displacement sqrt(2 dt) L xi with D = L L^T (Cholesky) every step; any spring
  * law and LJ; one workgroup per replica (N <= 64 within the device's LDS per
- * workgroup: 3N(3N+1)/2 + 1024 elements); a context holds only HI groups or
- * none; no adjoint, no plain path.
+ * workgroup: max(3N(3N+1)/2, 16 B (40 + 4 B)) + 1024 + max(12 N, 192) elements,
+ * B = ceil(3N/16) rounded up to an even number); a context holds only HI groups
+ * or none; no adjoint, no plain path.
  * Flow: uniaxial kappa = rate*diag(1,-1/2,-1/2); planar rate*diag(1,-1,0);
  * shear v_x = rate * z (the paper's convention, Sec. II). */
 typedef struct {
