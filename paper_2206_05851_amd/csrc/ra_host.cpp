@@ -55,7 +55,7 @@ struct ra_ctx {
     int64_t* dstep = nullptr;
     double* src = nullptr;          // [sum_g N_g][3] centre-of-mass frame of the clone source
     int64_t* drep_off = nullptr;    // [n_groups + 1] first replica of each group
-    unsigned long long* event_queue = nullptr;   // [n_groups][2] work queues of ra_mftu_events
+    unsigned long long* event_queue = nullptr;   // [n_groups][2] work queues of ra_mftu_events, behind clamps
     int64_t n_reps = 0;
     hipEvent_t ev_parent = nullptr, ev_reclone = nullptr;   // RSF cycle across two streams
     int64_t step = 0;
@@ -255,8 +255,7 @@ void ra_destroy(ra_ctx* c) {
     // pos[1] points into the pos[0] allocation and is not freed on its own
     void* ptrs[] = {c->dgroups, c->ditems, c->dtiles, c->dpar_off, c->ditem_begin, c->state, c->pos[0],
                     c->samples, c->tsf, c->tsf_acc, c->ckpt, c->segbuf, c->dseg_off,
-                    c->partial, c->lam_mu, c->status, c->clamps, c->dstep, c->src, c->drep_off,
-                    c->event_queue};
+                    c->partial, c->lam_mu, c->status, c->clamps, c->dstep, c->src, c->drep_off};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->ev_parent) (void)hipEventDestroy(c->ev_parent);
@@ -428,11 +427,11 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
     ALLOC(c->dtiles, c->htiles.size());
     ALLOC(c->dpar_off, n_groups);
     ALLOC(c->status, 1);
-    ALLOC(c->clamps, n_groups);
+    ALLOC(c->clamps, 3 * n_groups);
+    c->event_queue = c->clamps + n_groups;
     ALLOC(c->dstep, 1);
     ALLOC(c->src, par);
     ALLOC(c->drep_off, n_groups + 1);
-    ALLOC(c->event_queue, 2 * n_groups);
     if (run->plain) {
         ALLOC(p8, 2 * c->pos_total * esz);
         c->pos[0] = p8;
