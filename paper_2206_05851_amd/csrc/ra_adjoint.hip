@@ -9,9 +9,12 @@
 // The forward stored Q every K steps; each K-step segment is recomputed
 // from its checkpoint with the same step function (bitwise-identical
 // trajectory) into a per-wavefront HBM buffer, then swept backwards. Many
-// wavefronts are bound by that buffer's traffic, so its rows hold the tile's lanes
-// only (4096 replicas of 100 beads, 50 of 64 lanes, 2000 steps, segments of 100:
-// 25.2 GB in 4.98 ms with whole rows, 19.7 GB in 4.43 ms).
+// wavefronts are bound by that buffer's traffic, so there its rows hold the tile's
+// lanes only (4096 replicas of 100 beads, 50 of 64 lanes, 2000 steps, segments of 100:
+// 25.2 GB in 4.98 ms with whole rows, 19.7 GB in 4.43 ms). Few are bound by the
+// issue of one wavefront, and wide lanes by their registers: their rows are whole,
+// at fixed distances from one address (300 replicas of 100 beads, 200 steps, segments
+// of 5, noise map 1: packed 183 us, whole 172).
 //
 // Bond form: Phi_j = Q_j + dt kappa Q_j + cF [G_{j+1} - 2 G_j + G_{j-1}] + noise,
 // G_j = g_j Q_j. The Laplacian is symmetric, so
@@ -48,6 +51,22 @@ __device__ __forceinline__ void factor_gs(float qx, float qy, float qz, const Gr
                 s = (float)sd;
             }
         }
+    }
+}
+
+// A state as rows of the whole wavefront, [slot][xyz][64].
+template <bool STORE, int M>
+__device__ __forceinline__ void wave_rows(Lane<float, M>& s, float* p) {
+    p += threadIdx.x & (WAVE - 1);
+    auto move = [](float& v, float& at) {
+        if constexpr (STORE) at = v;
+        else v = at;
+    };
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        move(s.qx[m], p[3 * m * WAVE]);
+        move(s.qy[m], p[(3 * m + 1) * WAVE]);
+        move(s.qz[m], p[(3 * m + 2) * WAVE]);
     }
 }
 
@@ -163,7 +182,7 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-template <int M, bool FENE, int NMAP>
+template <int M, bool FENE, int NMAP, bool MANY>
 __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G, int item, int k_first) {
     // kernel arguments into locals (the loops must not address the argument block)
     const int S = a.S, K = a.K;
@@ -192,51 +211,114 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
 #pragma unroll
         for (int m = 0; m < M; ++m) cF[m] = valid[m] ? G.cF : 0.0f;
     };
-    const int STRIDE = 3 * M * G.P * G.L;     // floats per stored state
+    // Rows of a stored state: of the tile's lanes, or of the whole wavefront, which then
+    // sit at fixed distances from one address.
+    constexpr bool PACKED = M <= 4 && MANY;
+    const int STRIDE = PACKED ? 3 * M * G.P * G.L : 3 * M * WAVE;
     const AdjArgs* ap = &a;                   // for inject(); not touched in the step loops
+    auto sampled = [&](const Lane<float, M>& q, int w) {
+        double dH = 0.0, db = 0.0;
+        inject<M, FENE>(q, valid, G, *ap, tg, w, lx, ly, lz, dH, db);
+        gH += dH;
+        gb += db;
+    };
     // Reverse over the steps hi .. lo: the states Q^lo .. Q^hi at base, base + stride,
-    // ..., and s = Q^{hi + 1}. States are read AHEAD - 1 steps before their use: with
-    // one step the loads' latency bounds a sweep of few wavefronts (1000 items of
-    // 40-77 beads, 500 kept states: the widest tile's launch 340 us, all of them 269).
-    constexpr int AHEAD = M <= 2 ? 4 : 3;
-    auto sweep = [&](const float* base, int64_t stride, int lo, int hi) {
+    // ..., read by `read`, and s = Q^{hi + 1}; rs: FP32 partials of at most 128 steps.
+    // States are read ahead: with one step the loads' latency bounds a sweep of few
+    // wavefronts (1000 items of 40-77 beads, 500 kept states: the widest tile's launch
+    // 340 us, all of them 269).
+    // CUT: between the sampled states and the 128-step sums the loops hold the steps and
+    // nothing else. 200 steps, us, both looked for at each step / cut: 100 replicas of 50
+    // beads, noise map 1, every state kept 49 / 41, recomputed in segments of 100 88 / 76.
+    // Wide lanes take one step per turn, as unrolled steps do not fit the instruction
+    // cache: 4 replicas of 1000 beads, every state kept, three steps unrolled 800, one
+    // 455, segments of 20 1204 / 980. Two to four beads per lane spill registers in the
+    // cut's loops, and many wavefronts hide what the cut saves and lose by its registers
+    // (5000 replicas of 50 beads, every state kept: 127, cut 149).
+    auto sweep = [&](const float* base, int64_t stride, int lo, int hi, auto read) {
+        constexpr bool CUT = (M == 1 && !MANY) || M > 4;
+        constexpr int AHEAD = M <= 2 ? 4 : M <= 4 ? 3 : 1;
         Lane<float, M> ring[AHEAD];
-        ring[AHEAD - 1] = s;
         const float* p = base + (hi - lo) * stride;
         int at = hi;
-        auto load = [&](Lane<float, M>& q) {          // past the lowest state: that one again
-            rows.load(q, p);
-            if (at > lo) p -= stride;
+        auto load = [&](Lane<float, M>& q) {          // past the lowest state: that one again, or none
+            if (M <= 4 || at >= lo) read(q, p);
+            if (M > 4 || at > lo) p -= stride;
             --at;
         };
+        RevSums rs{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (CUT) {                          // ring: Q^n, Q^{n - 1}, ..
 #pragma unroll
-        for (int d = 0; d < AHEAD - 1; ++d) load(ring[d]);
-        // rr = (n + 1) mod S, w = window of state n + 1 when rr == 0
-        int rr = (hi + 1) % S, w = (hi + 1) / S - 1;
-        RevSums rs{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // FP32 partials of at most 128 steps
-        for (int n0 = hi; n0 >= lo; n0 -= AHEAD) {
-#pragma unroll
-            for (int d = 0; d < AHEAD; ++d) {
-                const int n = n0 - d;
-                if (n < lo) break;
-                Lane<float, M>& after = ring[(d + AHEAD - 1) % AHEAD];   // Q^{n+1}
-                if (rr == 0) {
-                    double dH = 0.0, db = 0.0;
-                    inject<M, FENE>(after, valid, G, *ap, tg, w, lx, ly, lz, dH, db);
-                    gH += dH;
-                    gb += db;
-                    --w;
+            for (int d = 0; d < AHEAD; ++d) load(ring[d]);
+            int to_sample = (hi + 1) % S, w = (hi + 1) / S - 1;   // steps to the next sampled state, its window
+            for (int n = hi; n >= lo;) {
+                if (to_sample == 0) {
+                    sampled(s, w--);
+                    to_sample = S;
                 }
-                load(after);
-                reverse_step<M, FENE>(ring[d], cF, G, lx, ly, lz, rs);
-                if ((n & 127) == 0) {
+                int len = min(min(to_sample, n - lo + 1), (n & 127) + 1);
+                to_sample -= len;
+                n -= len;
+                if constexpr (AHEAD > 1) {
+                    for (; len >= AHEAD; len -= AHEAD) {
+#pragma unroll
+                        for (int d = 0; d < AHEAD; ++d) {
+                            reverse_step<M, FENE>(ring[d], cF, G, lx, ly, lz, rs);
+                            if (d == AHEAD - 1) s = ring[d];
+                            load(ring[d]);
+                        }
+                    }
+                }
+                for (; len > 0; --len) {
+                    s = ring[0];
+#pragma unroll
+                    for (int d = 0; d + 1 < AHEAD; ++d) ring[d] = ring[d + 1];
+                    load(ring[AHEAD - 1]);
+                    reverse_step<M, FENE>(s, cF, G, lx, ly, lz, rs);
+                }
+                if (((n + 1) & 127) == 0) {
                     rev_flush(rs, G, gr, gH, gb);
                     rs = RevSums{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
                 }
-                rr = rr == 0 ? S - 1 : rr - 1;
+            }
+        } else {                                      // ring: Q^n, Q^{n - 1}, .. and last Q^{n + 1}
+            ring[AHEAD - 1] = s;
+#pragma unroll
+            for (int d = 0; d < AHEAD - 1; ++d) load(ring[d]);
+            // rr = (n + 1) mod S, w = window of state n + 1 when rr == 0
+            int rr = (hi + 1) % S, w = (hi + 1) / S - 1;
+            for (int n0 = hi; n0 >= lo; n0 -= AHEAD) {
+#pragma unroll
+                for (int d = 0; d < AHEAD; ++d) {
+                    const int n = n0 - d;
+                    if (n < lo) break;
+                    Lane<float, M>& after = ring[(d + AHEAD - 1) % AHEAD];   // Q^{n+1}
+                    if (rr == 0) sampled(after, w--);
+                    load(after);
+                    reverse_step<M, FENE>(ring[d], cF, G, lx, ly, lz, rs);
+                    if ((n & 127) == 0) {
+                        rev_flush(rs, G, gr, gH, gb);
+                        rs = RevSums{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                    }
+                    rr = rr == 0 ? S - 1 : rr - 1;
+                }
             }
         }
         rev_flush(rs, G, gr, gH, gb);
+    };
+    auto read_ckpt = [&](Lane<float, M>& q, const float* p) {
+        if constexpr (M <= 4) rows.load(q, p);
+        else load_ckpt<float, M>(q, valid, p, G, tg);
+    };
+    auto read_seg = [&](Lane<float, M>& q, const float* p) {
+        if constexpr (PACKED) rows.load(q, p);
+        else wave_rows<false>(q, (float*)p);
+    };
+    float* wp = seg;                          // next state of the segment
+    auto keep = [&]() {
+        if constexpr (PACKED) rows.store(s, wp);
+        else wave_rows<true>(s, wp);
+        wp += STRIDE;
     };
     const int n_seg = (int)((n_end + K - 1) / K);
     if (K == 1 && n_end > 0) {
@@ -253,14 +335,14 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
         } else {
             em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)(n_end - 1), keys, dummy);
         }
-        sweep(ckpt, ckpt_total, 0, (int)n_end - 1);
+        sweep(ckpt, ckpt_total, 0, (int)n_end - 1, read_ckpt);
     }
     for (int sgi = (K == 1 && n_end > 0) ? -1 : n_seg - 1; sgi >= 0; --sgi) {
         const int s0 = sgi * K;
         const int s1 = (int)min(n_end, (int64_t)s0 + K);
         load_ckpt<float, M>(s, valid, ckpt + (int64_t)sgi * ckpt_total, G, tg);
         set_slots();
-        float* wp = seg;
+        wp = seg;
         if constexpr (NMAP == 1) {
             Carry<float, M> cy;
             init_carry<float, M, false>(cy, lc, G, (uint32_t)s0, keys);
@@ -270,8 +352,7 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                 // three blocks per slot drawn first, each step's transform just
                 // before the step (the same normals as the carry gives)
                 for (; n < s1 && (n & 3) != 0; ++n) {
-                    rows.store(s, wp);
-                    wp += STRIDE;
+                    keep();
                     em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
                 }
                 for (; n + 4 <= s1; n += 4) {
@@ -294,34 +375,29 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
                             if (u == 1) e3.y[m] = d;
                             if (u == 2) e3.z[m] = d;
                         }
-                        rows.store(s, wp);
-                        wp += STRIDE;
+                        keep();
                         physics_step<float, M, FENE>(s, e, G, valid, mask, dummy);
                     }
-                    rows.store(s, wp);
-                    wp += STRIDE;
+                    keep();
                     physics_step<float, M, FENE>(s, e3, G, valid, mask, dummy);
                 }
             }
             for (; n < s1; ++n) {
-                rows.store(s, wp);
-                wp += STRIDE;
+                keep();
                 em_step_map1<float, M, FENE>(s, cy, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else if constexpr (NMAP == 2) {
             for (int n = s0; n < s1; ++n) {
-                rows.store(s, wp);
-                wp += STRIDE;
+                keep();
                 em_step_map2<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         } else {
             for (int n = s0; n < s1; ++n) {
-                rows.store(s, wp);
-                wp += STRIDE;
+                keep();
                 em_step<float, M, FENE>(s, lc, G, valid, mask, (uint32_t)n, keys, dummy);
             }
         }
-        sweep(seg, STRIDE, s0, s1 - 1);
+        sweep(seg, STRIDE, s0, s1 - 1, read_seg);
     }
     (void)spr_total;
     (void)lam_mu;
@@ -335,26 +411,27 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
     }
 }
 
-template <int M, int NMAP>
+template <int M, int NMAP, bool MANY>
 __device__ __forceinline__ void adjoint_item(const AdjArgs& a, const GroupDev& G, int item, int k_first) {
     if constexpr (M <= 4) {
         // the group's constants as a local value: read through the reference,
         // the recompute loop re-loads them from memory every step
         const GroupDev Gl = G;
-        if (Gl.spring == 1) run_adjoint<M, true, NMAP>(a, Gl, item, k_first);
-        else run_adjoint<M, false, NMAP>(a, Gl, item, k_first);
+        if (Gl.spring == 1) run_adjoint<M, true, NMAP, MANY>(a, Gl, item, k_first);
+        else run_adjoint<M, false, NMAP, MANY>(a, Gl, item, k_first);
     } else {   // noise map 1 is not compiled for wider lanes (rejected on the host)
         static_assert(NMAP != 1, "noise map 1 is compiled for 1-4 beads per lane");
-        if (G.spring == 1) run_adjoint<M, true, NMAP>(a, G, item, k_first);
-        else run_adjoint<M, false, NMAP>(a, G, item, k_first);
+        if (G.spring == 1) run_adjoint<M, true, NMAP, MANY>(a, G, item, k_first);
+        else run_adjoint<M, false, NMAP, MANY>(a, G, item, k_first);
     }
 }
 
 // A contiguous range of the work list (sorted by beads per lane, the most first).
 // MAX_M 2 holds the tiles of one and two beads per lane, 4 those of one to four, any
-// other MAX_M that width alone, each with a register budget of its own.
-template <int MAX_M, int NMAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAX_M <= 2 ? 4 : 1)))
+// other MAX_M that width alone, each with a register budget of its own. MANY: the
+// segments' rows are packed (adjoint_packed).
+template <int MAX_M, int NMAP, bool MANY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAX_M <= 2 ? 4 : MAX_M == 8 ? 2 : 1)))
 void adjoint_kernel(AdjArgs a, int item_begin, int item_end) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int item = item_begin + (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
@@ -362,14 +439,14 @@ void adjoint_kernel(AdjArgs a, int item_begin, int item_end) {
     const Item it = a.items[item];
     const GroupDev& G = a.groups[it.g];
     if constexpr (MAX_M == 2 || MAX_M == 4) {
-        if (G.M == 1) adjoint_item<1, NMAP>(a, G, item, it.k0);
-        else if (G.M == 2) adjoint_item<2, NMAP>(a, G, item, it.k0);
+        if (G.M == 1) adjoint_item<1, NMAP, MANY>(a, G, item, it.k0);
+        else if (G.M == 2) adjoint_item<2, NMAP, MANY>(a, G, item, it.k0);
         else if constexpr (MAX_M == 4) {
-            if (G.M == 3) adjoint_item<3, NMAP>(a, G, item, it.k0);
-            else adjoint_item<4, NMAP>(a, G, item, it.k0);
+            if (G.M == 3) adjoint_item<3, NMAP, MANY>(a, G, item, it.k0);
+            else adjoint_item<4, NMAP, MANY>(a, G, item, it.k0);
         }
     } else {
-        adjoint_item<MAX_M, NMAP>(a, G, item, it.k0);
+        adjoint_item<MAX_M, NMAP, MANY>(a, G, item, it.k0);
     }
 }
 
@@ -421,6 +498,17 @@ __global__ __launch_bounds__(GR_THREADS) void grad_reduce_kernel(const int32_t* 
     if (t < 3) grad[3 * g + t] = sh[t][0];
 }
 
+template <int MAX_M, int NMAP>
+static void launch_adj(const AdjArgs& a, int item_begin, int item_end, dim3 grid, dim3 block, hipStream_t st) {
+    if constexpr (MAX_M <= 4) {
+        if (adjoint_packed(MAX_M, a.n_items)) {
+            hipLaunchKernelGGL((adjoint_kernel<MAX_M, NMAP, true>), grid, block, 0, st, a, item_begin, item_end);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((adjoint_kernel<MAX_M, NMAP, false>), grid, block, 0, st, a, item_begin, item_end);
+}
+
 hipError_t launch_adjoint(const AdjArgs& a, int max_m, int item_begin, int item_end, int waves_per_block, int nmap,
                           hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
@@ -428,8 +516,8 @@ hipError_t launch_adjoint(const AdjArgs& a, int max_m, int item_begin, int item_
     if (n <= 0) return hipSuccess;
     const int wpb = waves_per_block;
     dim3 grid((n + wpb - 1) / wpb), block(WAVE * wpb);
-#define RA_ADJ(M_, NMAP_) \
-    hipLaunchKernelGGL((adjoint_kernel<M_, NMAP_>), grid, block, 0, st, a, item_begin, item_end); \
+#define RA_ADJ(M_, NMAP_)                                                 \
+    launch_adj<M_, NMAP_>(a, item_begin, item_end, grid, block, st);      \
     break
     if (nmap == 1) {
         switch (max_m) {

@@ -457,7 +457,7 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
         for (size_t it = 0; it < c->hitems.size(); ++it) {
             seg_off[it] = tot;
             const GroupDev& G = c->hgroups[c->hitems[it].g];
-            tot += (int64_t)K * G.M * 3 * G.P * G.L;
+            tot += (int64_t)K * G.M * 3 * (adjoint_packed(G.M, (int)c->hitems.size()) ? G.P * G.L : WAVE);
         }
         ALLOC(c->segbuf, tot);
         ALLOC(c->dseg_off, c->hitems.size());
@@ -712,7 +712,7 @@ ra_status ra_backward(ra_ctx* c, const double* mean, const double* grad_mean, co
     // beads: 340 + 280 + 236 us, together 269). Else one
     // launch per kernel over its contiguous range.
     const int n_items = (int)c->hitems.size();
-    const bool one = c->family == 4 && n_items <= 2048;
+    const bool one = c->family == 4 && n_items <= ADJOINT_ONE_LAUNCH;
     auto kernel = [](int M) { return M == 3 ? 4 : M; };
     for (int b = 0; b < n_items;) {
         const int M = kernel(c->hgroups[c->hitems[b].g].M);

@@ -58,7 +58,7 @@ struct AdjArgs {
     int64_t n_end;             // steps since init covered by the adjoint
     const double* lam_mu;      // dJ/d mean [W][spr_total]
     int64_t spr_total;
-    float* segbuf;             // per item: K states in checkpoint rows
+    float* segbuf;             // per item: K states in rows of the tile's lanes (adjoint_packed) or of 64
     const int64_t* seg_off;    // per item offset into segbuf (floats)
     double* partial;           // per item [3]: d/d(rate, H, b)
 };
@@ -106,6 +106,10 @@ hipError_t launch_pos_to_bonds(const GroupDev* groups, int n_groups, int64_t max
                                double* out, int precision, hipStream_t st);
 hipError_t launch_debug_noise(const uint32_t* ctr, int64_t n, uint32_t key0, uint32_t key1, uint32_t* words,
                               float* n32, double* n64, hipStream_t st);
+// Work lists of at most this many items go through the adjoint in one launch.
+constexpr int ADJOINT_ONE_LAUNCH = 2048;
+// Whether the rows of a segment's states hold the tile's P L lanes only (else 64).
+inline bool adjoint_packed(int M, int n_items) { return M <= 4 && n_items > ADJOINT_ONE_LAUNCH; }
 hipError_t launch_adjoint(const AdjArgs& a, int max_m, int item_begin, int item_end, int waves_per_block, int nmap,
                           hipStream_t st);
 hipError_t launch_lam_mu(const GroupDev* groups, int n_groups, int64_t n_windows, const double* mean,
