@@ -55,7 +55,6 @@ struct ra_ctx {
     int64_t* dstep = nullptr;
     double* src = nullptr;          // [sum_g N_g][3] centre-of-mass frame of the clone source
     int64_t* drep_off = nullptr;    // [n_groups + 1] first replica of each group
-    unsigned long long* event_queue = nullptr;   // [n_groups][2] work queues of ra_mftu_events, behind clamps
     int64_t n_reps = 0;
     hipEvent_t ev_parent = nullptr, ev_reclone = nullptr;   // RSF cycle across two streams
     int64_t step = 0;
@@ -427,8 +426,7 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
     ALLOC(c->dtiles, c->htiles.size());
     ALLOC(c->dpar_off, n_groups);
     ALLOC(c->status, 1);
-    ALLOC(c->clamps, 3 * n_groups);
-    c->event_queue = c->clamps + n_groups;
+    ALLOC(c->clamps, n_groups);
     ALLOC(c->dstep, 1);
     ALLOC(c->src, par);
     ALLOC(c->drep_off, n_groups + 1);
@@ -868,7 +866,7 @@ ra_status ra_mftu_events(ra_ctx* c, const double* rates, int64_t n_windows, int3
     for (const auto& g : c->hgroups) max_springs = std::max(max_springs, g.N - 1);
     HIPCHK(c, launch_mftu_events(c->dgroups, ng, rates, n_windows, c->spr_total, n_trials, max_windows,
                                  c->run.sample_every, (uint32_t)c->run.seed, (uint32_t)(c->run.seed >> 32),
-                                 max_springs, first_window, c->event_queue, mftu, c->stream));
+                                 max_springs, first_window, mftu, c->stream));
     return RA_OK;
 }
 

@@ -329,14 +329,18 @@ constexpr unsigned long long EVENT_NONE = ~0ull;   // no event found
 constexpr uint32_t EVENT_NEVER = 0x80000000u;      // the threshold 0: no draw unfolds
 constexpr int EVENT_BLOCKS = 2048;                 // workgroups of a launch: 8 on each of 256 CUs
 
-// The queue of group g: queue[2 g] the next ticket, queue[2 g + 1] the trials
-// that have an event.
+// The queue of group g is one word, the trials that have an event above the next
+// ticket (tickets stay below 2^39: 2^23 segments of 2^16 trials). It lies in the
+// caller's mftu[g], which the result overwrites: calls that overlap on one context
+// (host threads, replays of captured calls) share nothing.
+constexpr int EVENT_SHIFT = 44;
+
 __global__ void event_setup_kernel(unsigned long long* __restrict__ first, int64_t n_first,
                                    unsigned long long* __restrict__ queue, int n_groups) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = t; i < n_first; i += stride) first[i] = EVENT_NONE;
-    for (int64_t i = t; i < 2 * (int64_t)n_groups; i += stride) queue[i] = 0;
+    for (int64_t i = t; i < n_groups; i += stride) queue[i] = 0;
 }
 
 // What of the block (v, j, trial, ctr3) depends on the window v alone.
@@ -397,8 +401,8 @@ __global__ __launch_bounds__(EVENT_THREADS) void first_event_lds_kernel(
     for (;;) {
         __syncthreads();   // the table is written; every thread has read the last ticket
         if (tid == 0) {
-            const uint64_t with_event = __hip_atomic_load(queue + 2 * g + 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-            ticket = with_event < (uint64_t)n_trials ? atomicAdd(queue + 2 * g, 1ull) : n_tickets;
+            const uint64_t with_event = __hip_atomic_load(queue + g, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) >> EVENT_SHIFT;
+            ticket = with_event < (uint64_t)n_trials ? atomicAdd(queue + g, 1ull) & ((1ull << EVENT_SHIFT) - 1) : n_tickets;
         }
         __syncthreads();
         const uint64_t t = ticket;
@@ -438,7 +442,7 @@ __global__ __launch_bounds__(EVENT_THREADS) void first_event_lds_kernel(
                         const uint64_t last = ((uint64_t)thr[row[q] + j] << 20) | lo;
                         if (lo != EVENT_NEVER && m <= last && v < max_windows &&
                             atomicMin(mine, (unsigned long long)v) == EVENT_NONE)
-                            atomicAdd(queue + 2 * g + 1, 1ull);
+                            atomicAdd(queue + g, 1ull << EVENT_SHIFT);
                     }
                 }
             }
@@ -565,11 +569,11 @@ hipError_t launch_block_sigma(const GroupDev* groups, const ColTile* tiles, int 
 
 hipError_t launch_mftu_events(const GroupDev* groups, int n_groups, const double* rates, int64_t n_windows,
                               int64_t spr_total, int n_trials, int64_t max_windows, int S, uint32_t key0,
-                              uint32_t key1, int max_springs, int64_t* first_window, unsigned long long* queue,
-                              double* mftu, hipStream_t st) {
+                              uint32_t key1, int max_springs, int64_t* first_window, double* mftu, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     const size_t lds = (size_t)n_windows * (size_t)std::max(max_springs, 1) * sizeof(uint64_t);
     unsigned long long* first = (unsigned long long*)first_window;   // -1 is EVENT_NONE
+    unsigned long long* queue = (unsigned long long*)mftu;
     if (n_windows <= 0xFFFFFFFFll && lds <= EVENT_LDS_MAX) {
         const int64_t n_first = (int64_t)n_trials * n_groups;
         hipLaunchKernelGGL(event_setup_kernel, dim3((unsigned)std::min<int64_t>(1024, (n_first + 255) / 256)), dim3(256),

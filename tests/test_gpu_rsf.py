@@ -203,6 +203,44 @@ def test_mftu_events_at_the_edges_of_rounds_and_segments(cap, trials, rate):
     rep.close()
 
 
+def test_mftu_events_of_one_context_may_overlap():
+    # two captured calls on one context, with outputs of their own, replayed at the same
+    # time on two streams: the first windows of the calls made one after the other
+    import torch
+    from paper_2206_05851_amd import ra
+    groups = [wl.group(50, 1, 1e-3, stream_id=5), wl.group(20, 1, 1e-3, stream_id=6)]
+    T, cap = 1024, 1 << 18
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        rep = ra.Replicas(groups, 9, sample_every=10, max_windows=1)
+    rng = np.random.default_rng(3)
+    rates = [torch.from_numpy(10.0 ** rng.uniform(-5.5, -4.0, (2, 68))).cuda() for _ in range(2)]
+    torch.cuda.synchronize()
+    graphs, outs, want = [], [], []
+    for r in rates:
+        with torch.cuda.stream(s):
+            want.append(rep.mftu_events(r, T, cap))
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            outs.append(rep.mftu_events(r, T, cap))
+        graphs.append(g)
+    other = torch.cuda.Stream()
+    announce("event sampling, two calls at once")
+    for _ in range(3):
+        for o in outs:
+            o[0].zero_()
+            o[1].zero_()
+        torch.cuda.synchronize()
+        for g, st in zip(graphs, (s, other)):
+            with torch.cuda.stream(st):
+                g.replay()
+        torch.cuda.synchronize()
+        for (m, f), (m_ref, f_ref) in zip(outs, want):
+            assert torch.equal(f, f_ref)
+            assert torch.equal(m, m_ref)
+
+
 def test_conformation_after_cycle_matches_oracle():
     gs = [wl.group(40, 16, 1e-4, wl.FENE, 1.0, 100.0, wl.SHEAR, wl.wi_to_rate(50.0, 40), stream_id=1),
           wl.group(7, 9, 1e-3, wl.HOOKEAN, 1.0, 0.0, wl.QUIESCENT, 0.0, stream_id=2)]
