@@ -296,34 +296,50 @@ __device__ __forceinline__ uint64_t event_threshold(double p) {
     return (uint64_t)ceil((x - 1.0) * 0.5);
 }
 
-// Thresholds in LDS. The windows of a trial are cut into
-// segments, and the workgroups of a group take (segment, trial) tickets from a
-// queue, segment-major, so that all live trials advance together and the last
-// ones are shared by the whole chip (trials last exponentially long: with one
-// workgroup per trial the longest of 1024 kept a few SIMDs busy for most of
-// the call). A ticket whose trial already has an event in an earlier window is
-// skipped; tickets come in segment order, so once every trial has an event all
-// further tickets are dead and the workgroup leaves (the count is read before
-// the ticket is taken: an event known by then came from an earlier ticket). first[]
-// holds the least window found so far (atomicMin: the result does not depend on
-// the order of the work).
+// Thresholds in LDS, in three launches (two with one group):
+//  1. first_event_head_kernel: the first EVENT_HEAD windows of every trial, a few
+//     trials to a workgroup and no queue: short trials end here;
+//  2. event_live_kernel: the trials of each group that have an event, into its queue;
+//  3. first_event_queue_kernel: the rest. The windows of a trial are cut into segments,
+//     and workgroups take (segment, trial) tickets from a group's queue, segment-major,
+//     so that all live trials advance together and the last ones are shared by the whole
+//     chip (trials last exponentially long: with one workgroup per trial the longest of
+//     1024 kept a few SIMDs busy for most of the call). A workgroup stays with a
+//     group until its queue is done and goes on to the next live one: rates are
+//     exponential in the tension, so one group of many can hold nearly all the work.
+// A ticket whose trial already has an event in an earlier window is dead. Tickets
+// come in segment order, so once every trial has an event all further tickets are dead
+// and the group is done (an event counted by then came from an earlier ticket). A claim
+// is an atomic on one address that the chip takes in turn, about 50 ns each, so it
+// takes enough tickets that one of them is live on average, more live ones where
+// they outnumber the workgroups, and more of few springs. first[] holds the
+// least window found so far (atomicMin: the result does not depend on the order).
+// Measured, us, with one workgroup per trial / with a queue of single tickets and a fixed
+// share of the workgroups per group / now, trials of 49 springs unless said:
+//   512 groups, 128 trials, one group of mean 1e5 windows, others 100  3450 / 53000 / 2450
+//   64 groups, 1024 trials, means over three decades                   52300 / 86300 / 39200
+//   1024 trials, mean 300 windows                                      85 / 227 / 76
+//   8192 trials of one spring, mean 3e4                                922 / 7160 / 940
+//   8192 trials of nine springs, mean 1e6                              105000 / 125000 / 91000
 //
-// A thread draws all springs of its EVENT_WPT windows. Of the Philox block only
+// A thread draws all springs of its windows. Of the Philox block only
 // the first word is computed: m < t needs word 0 = m >> 20 <= (t - 1) >> 20, which
 // a draw meets about as rarely as it unfolds (1e-7 here); a wavefront where some
 // lane meets it recomputes the block and compares all 52 bits. With the spring
 // and the trial uniform, rounds 1-3 cost four VALU instructions: what depends
 // on the window alone is computed once per window, what depends on the spring
-// alone once per spring for both windows.
+// alone once per spring for all windows.
 // Bound by VALU issue: 34.5 instructions per draw. 1024 trials of up to 2^20
 // windows of 49 springs, 1.06e10 draws: 38.8 ms with a workgroup per trial and
-// whole blocks, 10.4 ms now, against 9.6 ms for the instructions at full rate.
-// With one segment of four rounds per ticket (5e5 tickets) it took 26.1 ms: the
-// atomics on the queue's address, about 50 ns each, bound it.
+// whole blocks, 9.35 ms now.
 constexpr int EVENT_THREADS = 256;
-constexpr int EVENT_WPT = 2;                       // windows per thread and round
-constexpr int EVENT_MOST_ROUNDS = 32;              // most rounds of a ticket
-constexpr int EVENT_ROUND = EVENT_THREADS * EVENT_WPT;   // windows of a round
+constexpr int EVENT_HEAD = 16 * EVENT_THREADS;     // windows of the first launch
+constexpr int EVENT_WPT = 2;                       // windows per thread and round of the queue kernel
+constexpr int EVENT_ROUND = EVENT_THREADS * EVENT_WPT;
+constexpr int EVENT_MOST_ROUNDS = 4;               // most rounds of a ticket
+constexpr int EVENT_MOST_LIVE = 8;                 // most live tickets of a claim, on average
+constexpr int EVENT_SHARE = 16;                    // workgroups per live trial at most
+constexpr int EVENT_CLAIM_DRAWS = 256;             // least spring-rounds of a claim
 constexpr size_t EVENT_LDS_MAX = 32 << 10;   // table of 64-bit thresholds up to this size, else the kernel below
 constexpr unsigned long long EVENT_NONE = ~0ull;   // no event found
 constexpr uint32_t EVENT_NEVER = 0x80000000u;      // the threshold 0: no draw unfolds
@@ -334,14 +350,7 @@ constexpr int EVENT_BLOCKS = 2048;                 // workgroups of a launch: 8 
 // caller's mftu[g], which the result overwrites: calls that overlap on one context
 // (host threads, replays of captured calls) share nothing.
 constexpr int EVENT_SHIFT = 44;
-
-__global__ void event_setup_kernel(unsigned long long* __restrict__ first, int64_t n_first,
-                                   unsigned long long* __restrict__ queue, int n_groups) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = t; i < n_first; i += stride) first[i] = EVENT_NONE;
-    for (int64_t i = t; i < n_groups; i += stride) queue[i] = 0;
-}
+constexpr unsigned long long EVENT_TICKETS = (1ull << EVENT_SHIFT) - 1;
 
 // What of the block (v, j, trial, ctr3) depends on the window v alone.
 struct EventWindow {
@@ -373,80 +382,227 @@ __device__ __forceinline__ uint32_t event_word0(const EventWindow& w, uint32_t s
     return c0;
 }
 
-__global__ __launch_bounds__(EVENT_THREADS) void first_event_lds_kernel(
-    const GroupDev* __restrict__ groups, const double* __restrict__ rates, int64_t n_windows, int64_t spr_total,
-    int n_trials, int64_t max_windows, int rounds, int S, uint32_t key0, uint32_t key1,
-    unsigned long long* __restrict__ first, unsigned long long* __restrict__ queue, int n_groups) {
-    extern __shared__ uint32_t thr[];   // [2][n_windows][N - 1]: upper 32 and lower 20 bits of t - 1
-    __shared__ unsigned long long ticket;
-    const int g = blockIdx.y;
-    const GroupDev& G = groups[g];
-    const int tid = threadIdx.x;
-    const int nm1 = G.N - 1;
-    const double window_time = (double)S * G.dt;
-    const uint32_t ctr3 = (2u << 24) | (G.stream & 0xFFFFFFu);
-    const RoundKeys keys = round_keys(key0, key1);
-    const int n_thr = (int)n_windows * nm1;
-    for (int i = tid; i < n_thr; i += EVENT_THREADS) {
-        const int w = i / nm1, j = i - w * nm1;
-        const double k = rates[w * spr_total + G.spr_off + j];
-        const uint64_t t = event_threshold(-expm1(-k * window_time));
-        thr[i] = t ? (uint32_t)((t - 1) >> 20) : 0u;
-        thr[n_thr + i] = t ? (uint32_t)(t - 1) & 0xFFFFFu : EVENT_NEVER;
-    }
-    const uint32_t nw = (uint32_t)n_windows;
-    const uint64_t seg = (uint64_t)rounds * EVENT_ROUND;
-    const uint64_t n_seg = ((uint64_t)max_windows + seg - 1) / seg;
-    const uint64_t n_tickets = n_seg * (uint64_t)n_trials;
-    for (;;) {
-        __syncthreads();   // the table is written; every thread has read the last ticket
-        if (tid == 0) {
-            const uint64_t with_event = __hip_atomic_load(queue + g, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) >> EVENT_SHIFT;
-            ticket = with_event < (uint64_t)n_trials ? atomicAdd(queue + g, 1ull) & ((1ull << EVENT_SHIFT) - 1) : n_tickets;
+struct EventArgs {
+    const GroupDev* groups;
+    const double* rates;
+    int64_t n_windows, spr_total, max_windows;
+    int n_groups, n_trials, S;
+    uint32_t key0, key1;
+    unsigned long long* first;   // [n_trials][n_groups]
+    unsigned long long* queue;   // [n_groups]
+};
+
+// One group's thresholds, [2][n_windows][N - 1] in LDS: upper 32 and lower 20 bits of
+// t - 1, and the scan of a trial's windows against them.
+struct EventTable {
+    uint32_t* thr;
+    int nm1, n_thr;
+    uint32_t nw, ctr3, key0, key1;
+
+    __device__ EventTable(const EventArgs& a, int g, uint32_t* lds) : thr(lds) {
+        const GroupDev& G = a.groups[g];
+        nm1 = G.N - 1;
+        n_thr = (int)a.n_windows * nm1;
+        nw = (uint32_t)a.n_windows;
+        ctr3 = (2u << 24) | (G.stream & 0xFFFFFFu);
+        key0 = a.key0;
+        key1 = a.key1;
+        const double window_time = (double)a.S * G.dt;
+        for (int i = threadIdx.x; i < n_thr; i += EVENT_THREADS) {
+            const int w = i / nm1, j = i - w * nm1;
+            const double k = a.rates[w * a.spr_total + G.spr_off + j];
+            const uint64_t t = event_threshold(-expm1(-k * window_time));
+            thr[i] = t ? (uint32_t)((t - 1) >> 20) : 0u;
+            thr[n_thr + i] = t ? (uint32_t)(t - 1) & 0xFFFFFu : EVENT_NEVER;
         }
-        __syncthreads();
-        const uint64_t t = ticket;
-        if (t >= n_tickets) return;
-        const uint32_t trial = __builtin_amdgcn_readfirstlane((uint32_t)(t % (uint64_t)n_trials));
-        const int64_t v0 = (int64_t)(t / (uint64_t)n_trials * seg);
-        unsigned long long* const mine = first + (int64_t)trial * n_groups + g;
+    }
+
+    // Least window with an unfolding among this thread's of the round at `base`: base
+    // + thread + 256 q; EVENT_NONE without one.
+    template <int WPT>
+    __device__ __forceinline__ unsigned long long scan(int64_t base, uint32_t trial, int64_t max_windows,
+                                                       const RoundKeys& keys) const {
+        EventWindow win[WPT];
+        int row[WPT];
+#pragma unroll
+        for (int q = 0; q < WPT; ++q) {
+            const uint32_t v = (uint32_t)(base + q * EVENT_THREADS + threadIdx.x);
+            win[q] = event_window(v, trial, ctr3, keys);
+            row[q] = (int)(v % nw) * nm1;
+        }
         const uint32_t n0_trial = (uint32_t)(((uint64_t)0xCD9E8D57u * trial) >> 32) ^ key0;
-        for (int round = 0; round < rounds; ++round) {
-            const int64_t base = v0 + (int64_t)round * EVENT_ROUND;
-            // an event in an earlier window, found here or by another
-            // workgroup, leaves nothing to find in the rest
-            if (base >= max_windows ||
-                __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned long long)base)
-                break;
-            EventWindow win[EVENT_WPT];
-            int row[EVENT_WPT];
+        unsigned long long hit = EVENT_NONE;
+        for (int j = 0; j < nm1; ++j) {
+            const uint64_t p = (uint64_t)0xD2511F53u * (n0_trial ^ (uint32_t)j);
+            const uint32_t sa = (uint32_t)(p >> 32) ^ (key1 + 0xBB67AE85u);
+            const uint32_t sb = (uint32_t)p ^ (key1 + 2u * 0xBB67AE85u);
 #pragma unroll
-            for (int q = 0; q < EVENT_WPT; ++q) {
-                const uint32_t v = (uint32_t)(base + q * EVENT_THREADS + tid);
-                win[q] = event_window(v, trial, ctr3, keys);
-                row[q] = (int)(v % nw) * nm1;
-            }
-            for (int j = 0; j < nm1; ++j) {
-                const uint64_t p = (uint64_t)0xD2511F53u * (n0_trial ^ (uint32_t)j);
-                const uint32_t sa = (uint32_t)(p >> 32) ^ (key1 + 0xBB67AE85u);
-                const uint32_t sb = (uint32_t)p ^ (key1 + 2u * 0xBB67AE85u);
-#pragma unroll
-                for (int q = 0; q < EVENT_WPT; ++q) {
-                    const uint32_t x = event_word0(win[q], sa, sb, keys);
-                    const bool near = x <= thr[row[q] + j];
-                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(near) != 0, 0)) {
-                        const int64_t v = base + q * EVENT_THREADS + tid;
-                        const Words u = philox10((uint32_t)v, (uint32_t)j, trial, ctr3, keys);
-                        const uint64_t m = ((uint64_t)u.x << 20) | (uint64_t)(u.y >> 12);
-                        const uint32_t lo = thr[n_thr + row[q] + j];
-                        const uint64_t last = ((uint64_t)thr[row[q] + j] << 20) | lo;
-                        if (lo != EVENT_NEVER && m <= last && v < max_windows &&
-                            atomicMin(mine, (unsigned long long)v) == EVENT_NONE)
-                            atomicAdd(queue + g, 1ull << EVENT_SHIFT);
-                    }
+            for (int q = 0; q < WPT; ++q) {
+                const uint32_t x = event_word0(win[q], sa, sb, keys);
+                const bool near = x <= thr[row[q] + j];
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(near) != 0, 0)) {
+                    const int64_t v = base + q * EVENT_THREADS + threadIdx.x;
+                    const Words u = philox10((uint32_t)v, (uint32_t)j, trial, ctr3, keys);
+                    const uint64_t m = ((uint64_t)u.x << 20) | (uint64_t)(u.y >> 12);
+                    const uint32_t lo = thr[n_thr + row[q] + j];
+                    const uint64_t last = ((uint64_t)thr[row[q] + j] << 20) | lo;
+                    if (lo != EVENT_NEVER && m <= last && v < max_windows) hit = min(hit, (unsigned long long)v);
                 }
             }
         }
+        return hit;
+    }
+};
+
+__global__ __launch_bounds__(EVENT_THREADS) void first_event_head_kernel(EventArgs a, int trials_per_block) {
+    extern __shared__ uint32_t event_thr[];
+    __shared__ unsigned long long best;
+    const int g = blockIdx.y;
+    const EventTable tab(a, g, event_thr);
+    const RoundKeys keys = round_keys(a.key0, a.key1);
+    const int64_t head = min((int64_t)EVENT_HEAD, a.max_windows);
+    const int t0 = (int)blockIdx.x * trials_per_block, t1 = min(a.n_trials, t0 + trials_per_block);
+    for (int trial = t0; trial < t1; ++trial) {
+        if (threadIdx.x == 0) best = EVENT_NONE;
+        __syncthreads();   // and, the first time, the table is written
+        for (int64_t base = 0; base < head; base += EVENT_THREADS) {
+            const unsigned long long hit = tab.scan<1>(base, (uint32_t)trial, a.max_windows, keys);
+            if (hit != EVENT_NONE)
+                __hip_atomic_fetch_min(&best, hit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __syncthreads();
+            // the same answer in every wavefront: one that is ahead adds later windows only
+            if (__hip_atomic_load(&best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <
+                (unsigned long long)(base + EVENT_THREADS))
+                break;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) a.first[(int64_t)trial * a.n_groups + g] = best;
+    }
+    if (a.n_groups == 1 && blockIdx.x == 0 && threadIdx.x == 0) a.queue[0] = 0;
+}
+
+__global__ __launch_bounds__(EVENT_THREADS) void event_live_kernel(EventArgs a) {
+    __shared__ int events;
+    const int g = blockIdx.x;
+    if (threadIdx.x == 0) events = 0;
+    __syncthreads();
+    int n = 0;
+    for (int t = threadIdx.x; t < a.n_trials; t += EVENT_THREADS) n += a.first[(int64_t)t * a.n_groups + g] != EVENT_NONE;
+    if (n) atomicAdd(&events, n);
+    __syncthreads();
+    if (threadIdx.x == 0) a.queue[g] = (unsigned long long)events << EVENT_SHIFT;
+}
+
+__global__ __launch_bounds__(EVENT_THREADS) void first_event_queue_kernel(EventArgs a, int rounds) {
+    extern __shared__ uint32_t event_thr[];
+    __shared__ unsigned long long ticket, claim, alive[EVENT_THREADS / WAVE];
+    __shared__ uint32_t trial_of[EVENT_THREADS], segment_of[EVENT_THREADS];
+    __shared__ unsigned long long live;
+    __shared__ int next, found;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const RoundKeys keys = round_keys(a.key0, a.key1);
+    const uint64_t n_trials = (uint64_t)a.n_trials;
+    const uint64_t seg = (uint64_t)rounds * EVENT_ROUND;
+    const uint64_t n_tickets = ((uint64_t)a.max_windows - EVENT_HEAD + seg - 1) / seg * n_trials;
+    auto queue_word = [&](int g) { return __hip_atomic_load(a.queue + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // one group: counted here, the trials that the head has left (their windows, if any by
+    // now, lie behind it), and its queue counts from there
+    uint64_t trials = n_trials;
+    auto unfinished = [&](unsigned long long w) {   // trials without an event, 0 when no ticket is left either
+        return (w & EVENT_TICKETS) < n_tickets ? trials - (w >> EVENT_SHIFT) : 0;
+    };
+    auto sum = [&](unsigned long long mine) {
+        __syncthreads();
+        if (tid == 0) live = 0;
+        __syncthreads();
+        if (mine) atomicAdd(&live, mine);
+        __syncthreads();
+        return live;
+    };
+    unsigned long long mine = 0;
+    if (a.n_groups == 1) {
+        for (int t = tid; t < a.n_trials; t += EVENT_THREADS)
+            mine += __hip_atomic_load(a.first + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= EVENT_HEAD;
+        trials = sum(mine);
+        mine = tid == 0 ? unfinished(queue_word(0)) : 0;
+    } else {
+        for (int g = tid; g < a.n_groups; g += EVENT_THREADS) mine += unfinished(queue_word(g));
+    }
+    // few live trials: no more workgroups than share them usefully, as each claim waits for the others'
+    if (blockIdx.x >= EVENT_SHARE * sum(mine)) return;
+    int g = (int)(blockIdx.x % (unsigned)a.n_groups);
+    for (;;) {
+        // the next live group from g on
+        if (tid == 0) next = INT32_MAX;
+        __syncthreads();
+        int ahead = INT32_MAX;
+        for (int o = 0; o < a.n_groups && ahead == INT32_MAX; o += EVENT_THREADS) {
+            if (o + tid < a.n_groups) {
+                const int c = (int)(((int64_t)g + o + tid) % a.n_groups);
+                if (unfinished(queue_word(c))) atomicMin(&next, o + tid);
+            }
+            __syncthreads();
+            ahead = next;
+            __syncthreads();   // every thread has read it
+        }
+        if (ahead == INT32_MAX) return;
+        g = (int)(((int64_t)g + ahead) % a.n_groups);
+        const EventTable tab(a, g, event_thr);
+        const int stride = max(1, 32 / tab.nm1);   // rounds between looks at first[]
+        const uint64_t least = (uint64_t)max(1, EVENT_CLAIM_DRAWS / (rounds * tab.nm1));
+        if (tid == 0) found = 0;
+        for (;;) {
+            __syncthreads();   // the table is written; `found` is complete, every thread has read the last claim
+            if (tid == 0) {
+                const unsigned long long add = (unsigned long long)found << EVENT_SHIFT;
+                unsigned long long w = queue_word(g);
+                const uint64_t left = unfinished(w + add);
+                // more live ones a claim where they outnumber the workgroups
+                const uint64_t many = min((uint64_t)EVENT_MOST_LIVE, max((uint64_t)1, left * a.n_groups / gridDim.x));
+                claim = left ? max(many * n_trials / left, least) : 0;
+                if (left || found) w = atomicAdd(a.queue + g, add + claim);
+                ticket = w & EVENT_TICKETS;
+                found = 0;
+                if (left && !unfinished(w + add)) claim = 0;
+            }
+            __syncthreads();
+            const uint64_t t0 = ticket, t1 = min(ticket + claim, n_tickets);
+            if (claim == 0 || t0 >= n_tickets) break;
+            for (uint64_t c = t0; c < t1; c += EVENT_THREADS) {
+                const uint32_t segment = (uint32_t)((c + tid) / n_trials);
+                const uint32_t trial = (uint32_t)(c + tid - segment * n_trials);
+                trial_of[tid] = trial;
+                segment_of[tid] = segment;
+                const bool on = c + tid < t1 && __hip_atomic_load(a.first + (int64_t)trial * a.n_groups + g, __ATOMIC_RELAXED,
+                                                                  __HIP_MEMORY_SCOPE_AGENT) >= EVENT_HEAD + segment * seg;
+                const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+                if ((tid & (WAVE - 1)) == 0) alive[wave] = b;
+                __syncthreads();
+                for (int i = 0; i < EVENT_THREADS; ++i) {
+                    if (!(alive[i >> 6] >> (i & 63) & 1)) {
+                        if (alive[i >> 6] >> (i & 63) == 0) i |= 63;
+                        continue;
+                    }
+                    const uint32_t trial = __builtin_amdgcn_readfirstlane(trial_of[i]);
+                    int64_t base = EVENT_HEAD + (int64_t)(__builtin_amdgcn_readfirstlane(segment_of[i]) * seg);
+                    unsigned long long* const best = a.first + (int64_t)trial * a.n_groups + g;
+                    for (int round = 0; round < rounds; ++round, base += EVENT_ROUND) {
+                        // an event in an earlier window, found here or by another
+                        // workgroup, leaves nothing to find in the rest
+                        if (base >= a.max_windows ||
+                            (round % stride == 0 && __hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                                                        (unsigned long long)base))
+                            break;
+                        const unsigned long long hit = tab.scan<EVENT_WPT>(base, trial, a.max_windows, keys);
+                        if (hit != EVENT_NONE && atomicMin(best, hit) == EVENT_NONE) atomicAdd(&found, 1);
+                        if (__builtin_amdgcn_ballot_w64(hit != EVENT_NONE)) break;
+                    }
+                }
+                __syncthreads();   // alive[] is rewritten
+            }
+        }
+        __syncthreads();   // the table is rewritten
     }
 }
 
@@ -573,20 +729,23 @@ hipError_t launch_mftu_events(const GroupDev* groups, int n_groups, const double
     (void)hipGetLastError();   // report only this launch's own error
     const size_t lds = (size_t)n_windows * (size_t)std::max(max_springs, 1) * sizeof(uint64_t);
     unsigned long long* first = (unsigned long long*)first_window;   // -1 is EVENT_NONE
-    unsigned long long* queue = (unsigned long long*)mftu;
     if (n_windows <= 0xFFFFFFFFll && lds <= EVENT_LDS_MAX) {
-        const int64_t n_first = (int64_t)n_trials * n_groups;
-        hipLaunchKernelGGL(event_setup_kernel, dim3((unsigned)std::min<int64_t>(1024, (n_first + 255) / 256)), dim3(256),
-                           0, st, first, n_first, queue, n_groups);
-        // about 64 segments per trial, of 1 to 32 rounds: a ticket is an atomic on
-        // one address that the whole chip takes in turn
-        const int rounds = (int)std::min<int64_t>(EVENT_MOST_ROUNDS, std::max<int64_t>(1, max_windows / (64 * EVENT_ROUND)));
-        const int64_t seg = (int64_t)rounds * EVENT_ROUND;
-        const int64_t tickets = (max_windows + seg - 1) / seg * n_trials;
-        const int64_t blocks = std::min<int64_t>(tickets, (EVENT_BLOCKS + n_groups - 1) / n_groups);
-        hipLaunchKernelGGL(first_event_lds_kernel, dim3((unsigned)blocks, (unsigned)n_groups), dim3(EVENT_THREADS),
-                           lds, st, groups, rates, n_windows, spr_total, n_trials, max_windows, rounds, S, key0, key1,
-                           first, queue, n_groups);
+        const EventArgs a{groups, rates, n_windows, spr_total, max_windows, n_groups, n_trials, S, key0, key1, first,
+                          (unsigned long long*)mftu};
+        const int64_t trials = (int64_t)n_trials * n_groups;
+        const int per_block = (int)std::min<int64_t>(16, std::max<int64_t>(1, trials / (2 * EVENT_BLOCKS)));
+        hipLaunchKernelGGL(first_event_head_kernel, dim3((unsigned)((n_trials + per_block - 1) / per_block), (unsigned)n_groups),
+                           dim3(EVENT_THREADS), lds, st, a, per_block);
+        if (max_windows > EVENT_HEAD) {
+            if (n_groups > 1)
+                hipLaunchKernelGGL(event_live_kernel, dim3((unsigned)n_groups), dim3(EVENT_THREADS), 0, st, a);
+            // 64 segments per trial or more, of 1 to 4 rounds
+            const int rounds = (int)std::min<int64_t>(EVENT_MOST_ROUNDS, std::max<int64_t>(1, max_windows / (64 * EVENT_ROUND)));
+            const int64_t seg = (int64_t)rounds * EVENT_ROUND;
+            const int64_t tickets = (max_windows - EVENT_HEAD + seg - 1) / seg * trials;
+            hipLaunchKernelGGL(first_event_queue_kernel, dim3((unsigned)std::min<int64_t>(tickets, EVENT_BLOCKS)),
+                               dim3(EVENT_THREADS), lds, st, a, rounds);
+        }
     } else {
         hipLaunchKernelGGL(first_event_kernel, dim3((unsigned)n_trials, (unsigned)n_groups), dim3(64), 0, st, groups,
                            rates, n_windows, spr_total, max_windows, S, key0, key1, first, n_groups);

@@ -203,6 +203,61 @@ def test_mftu_events_at_the_edges_of_rounds_and_segments(cap, trials, rate):
     rep.close()
 
 
+@pytest.mark.parametrize("cap,trials", [(4095, 300), (4096, 3), (4097, 300), (4096 + 512, 65), (9000, 600)])
+def test_mftu_events_of_many_groups_match_oracle(cap, trials):
+    # 40 groups, each with rates of its own from certain to none over the head, the
+    # queue's segments and the cap, chains of one to seven springs: workgroups go from
+    # group to group, claims hold up to `trials` tickets, more than a workgroup's threads
+    import torch
+    from oracle import ora
+    from paper_2206_05851_amd import ra
+    ng = 40
+    groups = [wl.group(2 + g % 7, 1, 1e-3, stream_id=100 + g) for g in range(ng)]
+    mean = [0.3 * 10.0 ** (g % 6) for g in range(ng)]               # windows to an event
+    S = 10
+    rates = np.concatenate([np.full((3, g["n_beads"] - 1), 0.0 if i % 13 == 12 else 1.0 / (mean[i] * (g["n_beads"] - 1) * S * 1e-3))
+                            for i, g in enumerate(groups)], axis=1)
+    rates *= np.random.default_rng(1).uniform(0.5, 1.5, rates.shape)
+    small = [g for g in range(ng)][: ng if trials < 100 else 12]     # the oracle's share
+    groups = [groups[g] for g in small]
+    rates = np.ascontiguousarray(rates[:, : sum(g["n_beads"] - 1 for g in groups)])
+    rep = ra.Replicas(groups, 13, sample_every=S, max_windows=1)
+    o = ora.Oracle(groups, 13, S, 1)
+    announce("event sampling, %d groups, %d trials, cap %d" % (len(groups), trials, cap))
+    m_ref, f_ref = o.mftu_events(rates, trials, cap)
+    m, f = rep.mftu_events(torch.from_numpy(rates).cuda(), trials, cap)
+    assert np.array_equal(f.cpu().numpy(), f_ref)
+    assert np.allclose(m.cpu().numpy(), m_ref, rtol=1e-13, atol=0)
+    rep.close()
+
+
+def test_mftu_events_of_one_slow_group_take_the_whole_chip():
+    # 64 groups of which one holds nearly all the work, against that group alone: 1.6 times
+    # its time; with a fixed share of the workgroups per group it was 17
+    import time
+    import torch
+    from paper_2206_05851_amd import ra
+    groups = [wl.group(50, 1, 1e-3, stream_id=g) for g in range(64)]
+    rates = torch.full((1, 64 * 49), 1.0 / (100 * 49 * 1e-2), dtype=torch.float64)
+    rates[:, 20 * 49:21 * 49] = 1.0 / (1e5 * 49 * 1e-2)
+    best = []
+    for gs, r in ((groups, rates), (groups[20:21], rates[:, 20 * 49:21 * 49].contiguous())):
+        rep = ra.Replicas(gs, 3, sample_every=10, max_windows=1)
+        r = r.cuda()
+        rep.mftu_events(r, 1024, 1 << 17)
+        t_best = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            rep.mftu_events(r, 1024, 1 << 17)
+            torch.cuda.synchronize()
+            t_best = min(t_best, time.perf_counter() - t)
+        best.append(t_best)
+        rep.close()
+    announce("event sampling: 64 groups %.2f ms, the slow one alone %.2f ms" % (best[0] * 1e3, best[1] * 1e3))
+    assert best[0] < 5 * best[1]
+
+
 def test_mftu_events_of_one_context_may_overlap():
     # two captured calls on one context, with outputs of their own, replayed at the same
     # time on two streams: the first windows of the calls made one after the other
