@@ -329,15 +329,15 @@ __device__ __forceinline__ void run_forward_impl(const FwdArgs& a, const GroupDe
     // step. Under noise map 1 the ring starts at a multiple of 4 and the steps
     // before it, three at most, draw their own noise.
     int at = 0, buf = 0;   // steps taken of the current chunk, its half of the ring
+    [[maybe_unused]] int head = NMAP == 1 ? (int)steps_to_group(n0) : 0;
     auto run_steps_ring = [&](auto n, int len) {
         int i = 0;
         if constexpr (NMAP == 1) {
-            if (n < ((n0 + 3u) & ~3u))
-                for (; i < len && ((n + (uint32_t)i) & 3u) != 0u; ++i) {
-                    keep();
-                    em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
-                    accumulate_tsf();
-                }
+            for (; i < len && head > 0; ++i, --head) {
+                keep();
+                em_step_map1<T, M, FENE, FUSED, UNIFORM_K>(s, cy, lc, G, valid, mask, n + (uint32_t)i, keys, clamps, tsum);
+                accumulate_tsf();
+            }
         }
         // noise of step `st` of the chunk; its fourth normals into the carry (map 1)
         auto fetch = [&](Noise<T, M>& e, int st) {

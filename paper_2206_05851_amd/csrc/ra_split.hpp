@@ -35,9 +35,9 @@ __device__ __forceinline__ void produce(const FwdArgs& a, const GroupDev& G, int
     const LaneCounters<M, UNIFORM_K> lc =
         lane_counters<M, UNIFORM_K>((uint32_t)tg.j0, (uint32_t)tg.k, G.stream, a.key0, a.key1);
     const uint32_t n0 = (uint32_t)n0_64;
-    const uint32_t first = NMAP == 1 ? (n0 + 3u) & ~3u : n0;
-    const int left = (int)a.n_steps - (int)(first - n0);
-    uint32_t n = first;
+    const uint32_t head = NMAP == 1 ? steps_to_group(n0) : 0u;   // steps that draw their own noise
+    const int left = (int)a.n_steps - (int)head;
+    uint32_t n = n0 + head;
     int buf = 0;
     for (int done = 0; done < left; done += Ring::STEPS) {
         for (int b = p; b < Ring::BLOCKS; b += SplitWaves<T>::PRODUCERS) {

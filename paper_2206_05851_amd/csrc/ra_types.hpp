@@ -6,6 +6,10 @@ namespace ra {
 
 constexpr int WAVE = 64;
 
+// Steps from n0 to the next multiple of 4 (0-3); a run may start at the last steps
+// below 2^32, where n0 rounded up is 0.
+constexpr uint32_t steps_to_group(uint32_t n0) { return (0u - n0) & 3u; }
+
 // Per-group constants, precomputed on the host in FP64 (both precisions kept
 // so that the FP32 kernels never round a sum like 1 + dt*rate).
 struct GroupDev {

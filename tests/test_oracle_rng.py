@@ -254,3 +254,21 @@ def test_fourth_normals_are_standard_and_independent_of_the_third():
     assert stats.kstest(fourth, "norm").pvalue > 1e-3
     assert abs(np.corrcoef(third, fourth)[0, 1]) < 4.5 / np.sqrt(n)
     assert stats.kstest(third ** 2 + fourth ** 2, "expon", args=(0, 2.0)).pvalue > 1e-3
+
+
+def test_steps_before_a_group_of_four_up_to_the_last_step(tmp_path):
+    # noise map 1 in the split forward: the steps that a run takes before its noise
+    # ring starts, at a multiple of 4 and modulo 2^32 for a run that starts at one of the last
+    # steps (the next multiple of 4 rounded up in 32 bits is 0 there, below the first step)
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    n0 = [0, 1, 2, 3, 4, 7, 750, 2 ** 31 - 1, 2 ** 31, 2 ** 32 - 5, 2 ** 32 - 4, 2 ** 32 - 3, 2 ** 32 - 2]
+    src = tmp_path / "steps.cpp"
+    src.write_text('#include <cstdio>\n#include <initializer_list>\n#include "ra_types.hpp"\nint main() {\n'
+                   'for (uint32_t n : {%s}) std::printf("%%u\\n", ra::steps_to_group(n));\n}\n' %
+                   ", ".join("%uu" % n for n in n0))
+    exe = tmp_path / "steps"
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2206_05851_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-I" + csrc, "-o", str(exe), str(src)])
+    got = [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()]
+    assert got == [-n % 4 for n in n0]
