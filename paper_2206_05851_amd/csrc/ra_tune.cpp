@@ -46,15 +46,19 @@ int choose_beads_per_lane(int n_beads, int n_replicas, int family, int forced, i
 // Time of a launch of few items, the widest with M beads per lane: measured, us
 // per 400 steps, up to 256, 512, 768, 1024, 1536 and 2048 items (the split forward's
 // workgroups go one to a CU, the others' wavefronts one to a SIMD).
+static constexpr int FEW_ITEMS[6] = {256, 512, 768, 1024, 1536, 2048};
+static int few_items_class(int64_t n_items) {
+    int i = 0;
+    while (n_items > FEW_ITEMS[i]) ++i;
+    return i;
+}
 static double few_items_cost(int M, int64_t n_items, int precision) {
-    static constexpr int items[6] = {256, 512, 768, 1024, 1536, 2048};
     static constexpr double f32[4][6] = {{61, 74, 85, 100, 143, 147},
                                          {90, 115, 170, 184, 260, 265},
                                          {119, 223, 226, 230, 357, 367},
                                          {143, 272, 281, 290, 450, 455}};
     static constexpr double f64[6] = {100, 195, 290, 355, 590, 600};   // times M
-    int i = 0;
-    while (n_items > items[i]) ++i;
+    const int i = few_items_class(n_items);
     return precision == 64 ? M * f64[i] : f32[M - 1][i];
 }
 
@@ -76,11 +80,11 @@ std::vector<int> choose_tiles(const ra_chain_desc* groups, int n_groups, int fam
     int64_t n_items;
     int max_m;
     std::vector<int> best = tiles(64, n_items, max_m);
-    if (forced > 0 || family != 4 || n_items > 2048) return best;
+    if (forced > 0 || family != 4 || n_items > FEW_ITEMS[5]) return best;
     double cost = few_items_cost(max_m, n_items, precision);
     for (int widest = max_m - 1; widest >= 1; --widest) {
         std::vector<int> Ms = tiles(widest, n_items, max_m);
-        if (n_items > 2048) break;
+        if (n_items > FEW_ITEMS[5]) break;
         const double t = few_items_cost(max_m, n_items, precision);
         if (t <= cost) {
             cost = t;
@@ -94,8 +98,11 @@ namespace {
 
 // One tuning result: the fastest M for a chain length and spring law under a
 // precision, kernel family, wavefronts per workgroup and noise map, and its
-// time per replica for 96 steps (to compare workgroup sizes across a batch).
-using Key = std::tuple<int, int, int, int, int, int>;   // N, spring, precision, family, wpb, noise_map
+// time per replica for 96 steps (to compare workgroup sizes across a batch); for
+// work lists of at most that many items where they do not fill the chip (FEW_ITEMS),
+// 0 for longer ones. Lines of a cache file without "items" hold for every list.
+using Key = std::tuple<int, int, int, int, int, int, int>;   // N, spring, precision, family, wpb, noise_map, items
+constexpr int ANY_ITEMS = -1;
 struct Entry {
     int M;
     double ms_per_replica;
@@ -116,16 +123,23 @@ std::map<Key, Entry>& table_for(const std::string& path) {
     if (path.empty()) return t;
     std::ifstream f(path);
     // one entry per line: {"N": .., "spring": .., "precision": .., "family": .., "wpb": ..,
-    //                      "noise_map": .., "M": .., "ms_per_replica": ..}
+    //                      "noise_map": .., "items": .., "M": .., "ms_per_replica": ..}
     std::string line;
     while (f && std::getline(f, line)) {
-        int v[7];
+        int v[7], items = ANY_ITEMS;
         double ms = 0.0;
+        if (std::sscanf(line.c_str(),
+                        " {\"N\": %d, \"spring\": %d, \"precision\": %d, \"family\": %d, \"wpb\": %d, "
+                        "\"noise_map\": %d, \"items\": %d, \"M\": %d, \"ms_per_replica\": %lf}",
+                        &v[0], &v[1], &v[2], &v[3], &v[4], &v[5], &items, &v[6], &ms) == 9) {
+            t[Key{v[0], v[1], v[2], v[3], v[4], v[5], items}] = Entry{v[6], ms};
+            continue;
+        }
         if (std::sscanf(line.c_str(),
                         " {\"N\": %d, \"spring\": %d, \"precision\": %d, \"family\": %d, \"wpb\": %d, "
                         "\"noise_map\": %d, \"M\": %d, \"ms_per_replica\": %lf}",
                         &v[0], &v[1], &v[2], &v[3], &v[4], &v[5], &v[6], &ms) == 8)
-            t[Key{v[0], v[1], v[2], v[3], v[4], v[5]}] = Entry{v[6], ms};
+            t[Key{v[0], v[1], v[2], v[3], v[4], v[5], ANY_ITEMS}] = Entry{v[6], ms};
     }
     return t;
 }
@@ -136,18 +150,21 @@ void append_cache_file(const std::string& path, const Key& k, const Entry& e) {
     char buf[256];
     std::snprintf(buf, sizeof buf,
                   "{\"N\": %d, \"spring\": %d, \"precision\": %d, \"family\": %d, \"wpb\": %d, "
-                  "\"noise_map\": %d, \"M\": %d, \"ms_per_replica\": %.9g}\n",
+                  "\"noise_map\": %d, \"items\": %d, \"M\": %d, \"ms_per_replica\": %.9g}\n",
                   std::get<0>(k), std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k),
-                  std::get<5>(k), e.M, e.ms_per_replica);
+                  std::get<5>(k), std::get<6>(k), e.M, e.ms_per_replica);
     f << buf;
 }
 
 // Time 96 fused steps of one group with a forced tile M of the batch's kernel
-// family (a short chain in a wide-lane batch runs the wide-lane kernels) and enough replicas
-// to give every SIMD TUNE_WAVES_PER_SIMD wavefronts of that packing, so the
+// family (a short chain in a wide-lane batch runs the wide-lane kernels). few = 0:
+// enough replicas to give every SIMD TUNE_WAVES_PER_SIMD wavefronts of that packing, so the
 // candidates are ranked by throughput (as in a saturated batch), not by the
-// latency of a few wavefronts. Returns ms per replica, or -1.
-double time_tile(const ra_chain_desc& d, const ra_run_desc& run, int family, int M, int wpb, hipStream_t st) {
+// latency of a few wavefronts. few > 0: that many replicas, those of a batch that
+// does not fill the chip, whose kernels and best tiles are others (40 beads, 300
+// replicas, 400 steps: the saturated ranking's M = 2 135 us, M = 1 67). Returns ms per
+// replica, or -1.
+double time_tile(const ra_chain_desc& d, const ra_run_desc& run, int family, int M, int wpb, int few, hipStream_t st) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -155,12 +172,14 @@ double time_tile(const ra_chain_desc& d, const ra_run_desc& run, int family, int
     const int lanes = (d.n_beads + M - 1) / M;
     const int per_wave = std::max(1, 64 / lanes);
     ra_chain_desc g = d;
-    g.n_replicas = TUNE_WAVES_PER_SIMD * 4 * cus * per_wave;
+    g.n_replicas = few > 0 ? few : TUNE_WAVES_PER_SIMD * 4 * cus * per_wave;
+    // a short list's launch is short: the best of three times as many steps each
+    const int steps = few > 0 ? 288 : 96, runs = few > 0 ? 3 : 1;
     ra_run_desc r{};
     r.seed = run.seed;
     r.precision = run.precision;
     r.sample_every = 64;
-    r.max_windows = 2;
+    r.max_windows = (32 + runs * steps) / 64;
     r.tile_policy = 1000 + M;
     r.waves_per_block = wpb;
     r.noise_map = run.noise_map;
@@ -181,14 +200,15 @@ double time_tile(const ra_chain_desc& d, const ra_run_desc& run, int family, int
         hipEventCreate(&e0) == hipSuccess) {
         if (hipEventCreate(&e1) == hipSuccess) {
             if (ra_init_chains(ctx, dp) == RA_OK && ra_step(ctx, 32) == RA_OK) {
-                (void)hipEventRecord(e0, st);
-                if (ra_step(ctx, 96) == RA_OK) {
+                for (int i = 0; i < runs; ++i) {
+                    (void)hipEventRecord(e0, st);
+                    if (ra_step(ctx, steps) != RA_OK) break;
                     (void)hipEventRecord(e1, st);
-                    if (hipEventSynchronize(e1) == hipSuccess) {
-                        float t = 0.f;
-                        (void)hipEventElapsedTime(&t, e0, e1);
-                        ms = t / g.n_replicas;
-                    }
+                    if (hipEventSynchronize(e1) != hipSuccess) break;
+                    float t = 0.f;
+                    (void)hipEventElapsedTime(&t, e0, e1);
+                    const double per = (double)t * 96 / steps / g.n_replicas;
+                    ms = ms < 0 ? per : std::min(ms, per);
                 }
             }
             (void)hipEventDestroy(e1);
@@ -212,23 +232,41 @@ ra_status autotune_tiles(const std::vector<ra_chain_desc>& descs, const ra_run_d
     const char* env = std::getenv("RA_AUTOTUNE_CACHE");
     const std::string path = env ? env : "";
     std::map<Key, Entry>& table = table_for(path);
-    // candidate workgroup sizes: the caller's, or all three when it left the choice open
-    std::vector<int> wpbs = waves_per_block ? std::vector<int>{waves_per_block} : std::vector<int>{1, 2, 4};
     double best_total = -1.0;
     std::vector<int> best_Ms = Ms;
+    int64_t n_items = 0;
+    double beads = 0.0;
+    for (size_t i = 0; i < descs.size(); ++i) {
+        const int P = std::max(1, 64 / ((descs[i].n_beads + Ms[i] - 1) / Ms[i]));
+        n_items += (descs[i].n_replicas + P - 1) / P;
+        beads += (double)descs[i].n_beads * descs[i].n_replicas;
+    }
+    const bool few = family == 4 && n_items <= FEW_ITEMS[5];
+    const int items = few ? FEW_ITEMS[few_items_class(n_items)] : 0;
+    // candidate workgroup sizes: the caller's, or all three when it left the choice open. Most
+    // short lists run kernels with a workgroup size of their own: there the default
+    // stays unless another one is clearly faster (contexts of a cycle need the same).
+    const std::vector<int> wpbs = waves_per_block ? std::vector<int>{waves_per_block}
+                                  : few           ? std::vector<int>{4, 1, 2}
+                                                  : std::vector<int>{1, 2, 4};
+    const double gain = few ? 0.95 : 1.0;
     int best_wpb = waves_per_block ? waves_per_block : 4;
     for (int wpb : wpbs) {
         std::vector<int> Mw(descs.size());
         double total = 0.0;   // predicted batch time: sum over groups of R x time per replica
         for (size_t i = 0; i < descs.size(); ++i) {
             const ra_chain_desc& d = descs[i];
-            const Key k{d.n_beads, d.spring, run.precision, family, wpb, run.noise_map};
+            const Key k{d.n_beads, d.spring, run.precision, family, wpb, run.noise_map, items};
             auto it = table.find(k);
+            if (it == table.end())
+                it = table.find(Key{d.n_beads, d.spring, run.precision, family, wpb, run.noise_map, ANY_ITEMS});
             if (it == table.end()) {
                 Entry best{Ms[i], -1.0};
                 for (int M : family_beads_per_lane(family)) {
                     if (!legal(d.n_beads, M) || !map_allows(run.noise_map, M)) continue;
-                    const double ms = time_tile(d, run, family, M, wpb, stream);
+                    // a short list: as many of these chains as make up the whole batch
+                    const int replicas = few ? std::max(d.n_replicas, (int)std::ceil(beads / d.n_beads)) : 0;
+                    const double ms = time_tile(d, run, family, M, wpb, replicas, stream);
                     if (ms < 0) { why = "timing run failed"; return RA_EDEVICE; }
                     if (best.ms_per_replica < 0 || ms < best.ms_per_replica) best = Entry{M, ms};
                 }
@@ -238,7 +276,7 @@ ra_status autotune_tiles(const std::vector<ra_chain_desc>& descs, const ra_run_d
             Mw[i] = it->second.M;
             total += it->second.ms_per_replica * d.n_replicas;
         }
-        if (best_total < 0 || total < best_total) {
+        if (best_total < 0 || total < gain * best_total) {
             best_total = total;
             best_Ms = Mw;
             best_wpb = wpb;

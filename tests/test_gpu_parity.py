@@ -487,6 +487,28 @@ def test_autotuner_tiles_bit_equal_and_cache_round_trip(tmp_path, monkeypatch):
     forced.close()
 
 
+def test_autotuner_times_a_short_list_as_it_will_run(tmp_path, monkeypatch):
+    # a batch that does not fill the chip: no wider tile than the cost model's (which
+    # knows such lists), and its results in the cache leave longer lists alone
+    from paper_2206_05851_amd import ra
+    f = tmp_path / "t.jsonl"
+    monkeypatch.setenv("RA_AUTOTUNE_CACHE", str(f))
+    announce("autotuner: short and long lists")
+    for N, R in ((40, 300), (100, 200)):
+        M = {}
+        for policy in (0, 1):
+            rep = ra.Replicas([wl.group(N, R, 1e-4, wl.FENE, 1.0, 100.0)], 5, sample_every=50, max_windows=1,
+                              tile_policy=policy)
+            M[policy] = rep.tile_info()[0][0]
+            rep.close()
+        assert M[1] <= M[0]
+    assert sum('"items": 0,' in ln for ln in f.read_text().splitlines()) == 0
+    ra.Replicas([wl.group(40, 30000, 1e-4, wl.FENE, 1.0, 100.0)], 5, sample_every=50, max_windows=1,
+                tile_policy=1).close()
+    lines = f.read_text().splitlines()
+    assert len(lines) == 9 and sum('"items": 0,' in ln for ln in lines) == 3
+
+
 def torch_equal(x, y):
     import torch
     return bool(torch.equal(x, y))
