@@ -61,7 +61,7 @@ struct ra_ctx {
     bool initialised = false;
     bool recloned = false;          // a re-clone since the last init (no adjoint)
     int max_m = 1;                  // most beads per lane of any group
-    int hi_nmax = 0;                // largest N of an HI context (sizes the kernel's LDS)
+    int max_beads = 0;              // largest N of any group
     std::map<int64_t, hipGraphExec_t> graphs;
     std::string err;
 };
@@ -299,10 +299,10 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
     const bool pair = is_pair_group(groups[0]);   // validated: all groups or none
     const bool hi = is_hi_group(groups[0]);
     if (pair) family = 2;
+    for (int i = 0; i < n_groups; ++i) c->max_beads = std::max(c->max_beads, groups[i].n_beads);
     if (hi) {
         family = 3;
-        int nmax = 2;
-        for (int i = 0; i < n_groups; ++i) nmax = std::max(nmax, groups[i].n_beads);
+        const int nmax = c->max_beads;
         int dev = 0, lds_max = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
@@ -317,7 +317,6 @@ ra_status ra::create_context(ra_ctx** out, const ra_chain_desc* groups, int32_t 
             ra_destroy(c);
             return fail(nullptr, RA_EINVAL, b2);
         }
-        c->hi_nmax = nmax;
     }
     if (pair || hi) Ms.assign(n_groups, 1);
     else
@@ -551,8 +550,8 @@ static ra_status enqueue_forward(ra_ctx* c, int64_t n_steps, hipStream_t st) {
     const int64_t chunk = (int64_t)1 << 30;
     for (int64_t done = 0; done < n_steps; done += chunk) {
         a.n_steps = std::min(chunk, n_steps - done);
-        if (c->family == 2) HIPCHK(c, launch_forward_pair(a, c->run.precision, c->wpb, st));
-        else if (c->family == 3) HIPCHK(c, launch_forward_hi(a, c->run.precision, c->hi_nmax, st));
+        if (c->family == 2) HIPCHK(c, launch_forward_pair(a, c->run.precision, c->wpb, c->max_beads, st));
+        else if (c->family == 3) HIPCHK(c, launch_forward_hi(a, c->run.precision, c->max_beads, st));
         else HIPCHK(c, launch_forward(a, c->run.precision, c->family, c->wpb, c->max_m, c->run.noise_map, st));
         HIPCHK(c, launch_advance(c->dstep, a.n_steps, st));
     }
@@ -569,9 +568,10 @@ static ra_status enqueue_forward_dual(ra_ctx* ca, int64_t n_a, ra_ctx* cb, int64
     a.n_steps = n_a;
     b.n_steps = n_b;
     hipStream_t st = ca->stream;
-    if (ca->family == 2) HIPCHK(ca, launch_forward_pair_dual(a, b, ca->run.precision, ca->wpb, st));
+    if (ca->family == 2) HIPCHK(ca, launch_forward_pair_dual(a, b, ca->run.precision, ca->wpb,
+                                                          std::max(ca->max_beads, cb->max_beads), st));
     else if (ca->family == 3)
-        HIPCHK(ca, launch_forward_hi_dual(a, b, ca->run.precision, std::max(ca->hi_nmax, cb->hi_nmax), st));
+        HIPCHK(ca, launch_forward_hi_dual(a, b, ca->run.precision, std::max(ca->max_beads, cb->max_beads), st));
     else
         HIPCHK(ca, launch_forward_dual(a, b, ca->run.precision, ca->family, ca->wpb, std::max(ca->max_m, cb->max_m),
                                        ca->run.noise_map, st));

@@ -7,7 +7,7 @@
 // lane), and with few items by its latency in a single wavefront: up to four
 // wavefronts step one item together (fwd_pair_shared_kernel), one run of the
 // partners each. 50 beads, FP32, us a step: 50 replicas 2.31 -> 1.18, 512 2.30 -> 1.38,
-// 1000 2.31 -> 2.12, 2048 3.24 -> 3.34 (four sums in place of one, so that the bits
+// 1000 2.31 -> 2.12, 2048 3.24 -> 3.2 (four sums in place of one, so that the bits
 // stay the same for any number of wavefronts); FP64: 50 replicas 4.74 -> 2.16, 1024
 // 4.95 -> 4.90, 2048 9.55 -> 8.08.
 //
@@ -91,11 +91,15 @@ __device__ __forceinline__ T segment_scan(T v, int i) {
 // LJ sums of one bead, in units of rmin: s = rmin^2 / r^2 is the reciprocal of the
 // scaled r^2, and the pair term is s (s^6 - s^3) dx'. `row` is the bead's own row of
 // the doubled table: partner i + t is row t.
-// The reciprocal is paced (see paced()): a single wavefront per SIMD shares its item
-// with others unless there are more items than SIMDs.
-template <typename T> struct PairSum {
+// The reciprocal is paced (see paced()) where wavefronts share an item or hold one
+// replica each; several short replicas per wavefront are 1-6% faster without (8000 replicas of
+// 12 beads, 100 steps, 178 against 173 us; 50 beads, 4000 replicas, 551 against 561 with).
+template <typename T, bool PACED> struct PairSum {
     T x, y, z;
-    __device__ __forceinline__ static float rcp(float v) { return paced<'r'>(v); }
+    __device__ __forceinline__ static float rcp(float v) {
+        if constexpr (PACED) return paced<'r'>(v);
+        else return fast_rcp(v);
+    }
     __device__ __forceinline__ static double rcp(double v) { return fast_rcp(v); }
     __device__ __forceinline__ void add(T px, T py, T pz, const T* r, bool use) {
         const T dx = px - r[0], dy = py - r[1], dz = pz - r[2];
@@ -117,9 +121,9 @@ template <typename T> struct PairSum {
 // the runs in fixed order, whichever wavefronts take them.
 constexpr int PARTS = 4;
 
-template <typename T>
-__device__ __forceinline__ PairSum<T> pair_part(int part, T px, T py, T pz, const T* row, int i, int N) {
-    PairSum<T> l{(T)0, (T)0, (T)0};
+template <typename T, bool PACED>
+__device__ __forceinline__ PairSum<T, PACED> pair_part(int part, T px, T py, T pz, const T* row, int i, int N) {
+    PairSum<T, PACED> l{(T)0, (T)0, (T)0};
     const int nm1 = N - 1;
     const int blocks = N > 3 ? N / 4 : 0;                // ceil((N - 3) / 4)
     if (part == PARTS - 1 && N >= 3) l.add(px, py, pz, row + 4 * (i == 0 ? nm1 : 1), i == 0 || i == nm1);
@@ -175,7 +179,7 @@ template <typename T> struct PairShare {
 // state and step it alike; each sums one run of the partners and draws every fourth
 // step's noise. One barrier a step: the sums are written before and read after it,
 // the noise of a step is read before it.
-template <typename T, int SPRING, bool LJ, int WAVES>
+template <typename T, int SPRING, bool LJ, int WAVES, bool ONE_SEG>
 __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, int k_first, T (*xs)[4], int wave,
                                          PairShare<T>* sh) {
     // the group's constants as a local value: read through the reference,
@@ -211,7 +215,6 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
     // tb .. tb + 2N - 1), so that partner i + t is row tb + i + t for every
     // t < N; lanes past the last segment read segment 0 and write nothing
     const bool seg_ok = seg < G.P;
-    const bool one_seg = G.P == 1;
     const int tb = seg_ok ? 2 * N * seg : 0;
     const RoundKeys keys = round_keys(a.key0, a.key1);
     const uint32_t n0 = (uint32_t)*a.step0;
@@ -257,7 +260,7 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
             // one replica per wavefront (N > 32): the whole-wave DPP scan;
             // else the segmented scan by lane shuffles
             T sx, sy, sz;
-            if (one_seg) {
+            if constexpr (ONE_SEG) {
                 sx = qx;
                 sy = qy;
                 sz = qz;
@@ -282,8 +285,9 @@ __device__ __forceinline__ void run_pair(const FwdArgs& a, const GroupDev& Gm, i
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             const T* row = xs[tb + i];
-            using Sum = PairSum<T>;
-            auto part_sum = [&](int p) { return pair_part<T>(p, px, py, pz, row, i, N); };
+            constexpr bool PACED = WAVES > 1 || ONE_SEG;
+            using Sum = PairSum<T, PACED>;
+            auto part_sum = [&](int p) { return pair_part<T, PACED>(p, px, py, pz, row, i, N); };
             Sum l;
             if constexpr (WAVES == 1) {
                 const Sum a0 = part_sum(0), a1 = part_sum(1), a2 = part_sum(2), a3 = part_sum(3);
@@ -355,14 +359,19 @@ __device__ __forceinline__ void pair_item(const FwdArgs& a, int item, T (*xs)[4]
     if (*(const volatile int*)a.status & 1) return;   // invalid parent: no work (whole block)
     const Item it = a.items[item];
     const GroupDev& G = a.groups[it.g];
-    if (G.lj12u_d > 0.0) {
-        if (G.spring == 0) run_pair<T, 0, true, WAVES>(a, G, it.k0, xs, wave, sh);
-        else if (G.spring == 1) run_pair<T, 1, true, WAVES>(a, G, it.k0, xs, wave, sh);
-        else run_pair<T, 2, true, WAVES>(a, G, it.k0, xs, wave, sh);
+    if (G.lj12u_d > 0.0 && G.N > 2) {                 // two beads have no pair that is not bonded
+        auto run = [&](auto One) {
+            constexpr bool ONE = decltype(One)::value;
+            if (G.spring == 0) run_pair<T, 0, true, WAVES, ONE>(a, G, it.k0, xs, wave, sh);
+            else if (G.spring == 1) run_pair<T, 1, true, WAVES, ONE>(a, G, it.k0, xs, wave, sh);
+            else run_pair<T, 2, true, WAVES, ONE>(a, G, it.k0, xs, wave, sh);
+        };
+        if (G.P == 1) run(Bool<true>{});
+        else run(Bool<false>{});
     } else if (wave == 0 || WAVES == 1) {             // springs alone: nothing to share
-        if (G.spring == 0) run_pair<T, 0, false, 1>(a, G, it.k0, xs, wave, sh);
-        else if (G.spring == 1) run_pair<T, 1, false, 1>(a, G, it.k0, xs, wave, sh);
-        else run_pair<T, 2, false, 1>(a, G, it.k0, xs, wave, sh);
+        if (G.spring == 0) run_pair<T, 0, false, 1, false>(a, G, it.k0, xs, wave, sh);
+        else if (G.spring == 1) run_pair<T, 1, false, 1, false>(a, G, it.k0, xs, wave, sh);
+        else run_pair<T, 2, false, 1, false>(a, G, it.k0, xs, wave, sh);
     }
 }
 
@@ -399,10 +408,13 @@ __global__ __launch_bounds__(WAVE * WAVES) void fwd_pair_shared_kernel(FwdArgs a
 // 2.63 3.14, 2.54 2.58 2.68 3.32 3.33; 24 beads 1.41 1.73 2.08, 1.50 1.60 1.74 2.04 2.32,
 // 1.93 1.97 2.01 2.37 2.37; FP64, 50 beads 3.20 4.87 6.11, 4.48 4.62 5.10 7.18,
 // 4.77 4.91 4.97 7.93. Four share the work best while a CU holds two items; from
-// there the state that each steps for itself costs more than their overlap gives.
-static int pair_waves(int n_items, int precision) {
+// there the state that each steps for itself costs more than their overlap gives, the
+// earlier the fewer partners there are to share (100 steps, us, at 800 / 1250 items with two
+// and one: 6 beads 123 145, 110 123; 9 beads 128 150, 121 145; 12 beads 143 167, 134 165;
+// 16 beads 144 171, 149 184).
+static int pair_waves(int n_items, int precision, int max_beads) {
     if (n_items <= 512) return 4;
-    return n_items <= (precision == 64 ? 768 : 1280) ? 2 : 1;
+    return n_items <= (precision == 64 || max_beads <= 12 ? 768 : 1280) ? 2 : 1;
 }
 
 template <typename T> static void launch_shared(const FwdArgs& a, const FwdArgs& b, int waves, hipStream_t st) {
@@ -417,10 +429,10 @@ static hipError_t launch_pair_shared(const FwdArgs& a, const FwdArgs& b, int pre
     return hipGetLastError();
 }
 
-hipError_t launch_forward_pair(const FwdArgs& a, int precision, int waves_per_block, hipStream_t st) {
+hipError_t launch_forward_pair(const FwdArgs& a, int precision, int waves_per_block, int max_beads, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     if (a.n_items <= 0 || a.n_steps <= 0) return hipSuccess;
-    const int shared = pair_waves(a.n_items, precision);
+    const int shared = pair_waves(a.n_items, precision, max_beads);
     if (shared > 1) {
         FwdArgs none = a;
         none.n_items = 0;
@@ -434,12 +446,12 @@ hipError_t launch_forward_pair(const FwdArgs& a, int precision, int waves_per_bl
 }
 
 hipError_t launch_forward_pair_dual(const FwdArgs& a, const FwdArgs& b, int precision, int waves_per_block,
-                                    hipStream_t st) {
+                                    int max_beads, hipStream_t st) {
     (void)hipGetLastError();   // report only this launch's own error
     const int wpb = waves_per_block;
     const int ba = (a.n_items + wpb - 1) / wpb, bb = (b.n_items + wpb - 1) / wpb;
     if (ba + bb == 0) return hipSuccess;
-    const int shared = pair_waves(a.n_items + b.n_items, precision);
+    const int shared = pair_waves(a.n_items + b.n_items, precision, max_beads);
     if (shared > 1) return launch_pair_shared(a, b, precision, shared, st);
     dim3 grid((unsigned)(ba + bb)), block(WAVE * wpb);
     if (precision == 64) hipLaunchKernelGGL(fwd_pair_dual_kernel<double>, grid, block, 0, st, a, b, ba);

@@ -178,3 +178,24 @@ def test_pair_wavefronts_per_item_keep_the_bits(N, precision):
     for other in out[1:]:
         for x, y in zip(out[0], other):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("N", [2, 9, 12, 13])
+def test_pair_short_chains_share_fewer_wavefronts_with_the_same_bits(N):
+    # up to 12 beads two wavefronts step an item up to 768 items, above that one, longer
+    # chains up to 1280; two beads have no pair: the same bits as without LJ
+    from paper_2206_05851_amd import ra
+    P = 64 // N
+    out = []
+    for items, eps in ((700, 0.7), (1000, 0.7), (1290, 0.7)) + (((700, 0.0),) if N == 2 else ()):
+        g = wl.group(N, items * P, 1e-5, wl.HARMONIC, 50.0, 0.0, wl.SHEAR, 5.0, rest_length=2.0, lj_eps=eps, lj_rmin=2.0,
+                     stream_id=3)
+        announce("pair short chains N=%d items=%d" % (N, items))
+        rep = ra.Replicas([g], 13, sample_every=7, max_windows=3)
+        rep.init_chains([_parent(g, 11)])
+        for c in (1, 4, 9, 7):   # 21
+            rep.step(c)
+        out.append(rep.bonds()[0][:5 * P].cpu().numpy())
+        rep.sync_status()
+    for other in out[1:]:
+        assert np.array_equal(out[0], other)
