@@ -4,14 +4,14 @@
 namespace ra {
 
 template <typename T, int NMAP, int TSFK, int MAX_M>
-__global__ __launch_bounds__(split_threads<T>()) void fwd_split_kernel(FwdArgs a) {
+__global__ __launch_bounds__((split_threads<T, MAX_M>())) void fwd_split_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char split_lds[];
     split_item<T, NMAP, TSFK, MAX_M>(a, (int)blockIdx.x, (T*)split_lds);
 }
 
 template <typename T, int NMAP, int MAX_M> static void launch_split_m(const FwdArgs& a, hipStream_t st) {
     constexpr int lds = split_lds_bytes<T, NMAP, MAX_M>();
-    const dim3 grid((unsigned)a.n_items), block(split_threads<T>());
+    const dim3 grid((unsigned)a.n_items), block((split_threads<T, MAX_M>()));
     if (a.tsf) {
         hipLaunchKernelGGL((fwd_split_kernel<T, NMAP, 1, MAX_M>), grid, block, lds, st, a);
         return;

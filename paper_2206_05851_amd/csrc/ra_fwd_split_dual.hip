@@ -4,7 +4,7 @@
 namespace ra {
 
 template <typename T, int NMAP, int MAX_M>
-__global__ __launch_bounds__(split_threads<T>()) void fwd_split_dual_kernel(FwdArgs a, FwdArgs b) {
+__global__ __launch_bounds__((split_threads<T, MAX_M>())) void fwd_split_dual_kernel(FwdArgs a, FwdArgs b) {
     extern __shared__ __align__(16) unsigned char split_lds[];
     const int item = (int)blockIdx.x;
     if (item < a.n_items) split_item<T, NMAP, 2, MAX_M>(a, item, (T*)split_lds);
@@ -14,7 +14,7 @@ __global__ __launch_bounds__(split_threads<T>()) void fwd_split_dual_kernel(FwdA
 template <typename T, int NMAP, int MAX_M>
 static void launch_split_m(const FwdArgs& a, const FwdArgs& b, hipStream_t st) {
     hipLaunchKernelGGL((fwd_split_dual_kernel<T, NMAP, MAX_M>), dim3((unsigned)(a.n_items + b.n_items)),
-                       dim3(split_threads<T>()), (split_lds_bytes<T, NMAP, MAX_M>()), st, a, b);
+                       dim3((split_threads<T, MAX_M>())), (split_lds_bytes<T, NMAP, MAX_M>()), st, a, b);
 }
 
 template <typename T, int NMAP> static void launch_split(const FwdArgs& a, const FwdArgs& b, int max_m, hipStream_t st) {

@@ -19,14 +19,18 @@ namespace ra {
 
 // Producing wavefronts: noise is 1.5-2 times the update in FP32, five in FP64. FP64 with
 // 6 / 9 / 12, us: 64 replicas of 10 beads, 5000 steps 1125 1061 994; 256 of 50 beads,
-// 400 steps 135 131 139, 768 321 327 352; 256 of 100 beads 229 216 235.
-template <typename T> struct SplitWaves {
-    static constexpr int PRODUCERS = sizeof(T) == 4 ? 3 : 9;
+// 400 steps 135 131 139, 768 321 327 352; 256 of 100 beads 229 216 235. With more than
+// two beads per lane nine leave 168 registers, and noise map 1 spills 470-2265 of
+// them (six 110-700; three none, but 10% slower). Against the one-wavefront kernel, N = 129-256,
+// time at 256 / 512 / 768 items with six: map 0 0.34 0.61 0.91, map 1 0.29 0.56 0.83, with
+// TSF 0.93 (nine 1.04); in a cycle 0.34 0.55 0.77, map 1 0.34 0.54 0.74 (nine 0.37 0.58 0.79).
+template <typename T, int MAX_M> struct SplitWaves {
+    static constexpr int PRODUCERS = sizeof(T) == 4 ? 3 : MAX_M == 4 ? 6 : 9;
 };
 
 // Producer p of PRODUCERS: blocks p, p + PRODUCERS, .. of every chunk, one
 // barrier after each chunk. Blocks past the last step are drawn and not used.
-template <typename T, int M, bool UNIFORM_K, int NMAP>
+template <typename T, int M, bool UNIFORM_K, int NMAP, int PRODUCERS>
 __device__ __forceinline__ void produce(const FwdArgs& a, const GroupDev& G, int k_first, int64_t n0_64, int p,
                                         const NoiseRing<T, M, NMAP>& ring) {
     using Ring = NoiseRing<T, M, NMAP>;
@@ -40,7 +44,7 @@ __device__ __forceinline__ void produce(const FwdArgs& a, const GroupDev& G, int
     uint32_t n = n0 + head;
     int buf = 0;
     for (int done = 0; done < left; done += Ring::STEPS) {
-        for (int b = p; b < Ring::BLOCKS; b += SplitWaves<T>::PRODUCERS) {
+        for (int b = p; b < Ring::BLOCKS; b += PRODUCERS) {
             const StepWords sw = lc.words(n + (uint32_t)(NMAP == 1 ? b + b / 3 : b));
 #pragma unroll
             for (int m = 0; m < M; ++m) {
@@ -56,7 +60,7 @@ __device__ __forceinline__ void produce(const FwdArgs& a, const GroupDev& G, int
 }
 
 // TSFK as in dispatch_spring.
-template <typename T, int M, int NMAP, int TSFK>
+template <typename T, int M, int NMAP, int TSFK, int PRODUCERS>
 __device__ __forceinline__ void split_tile(const FwdArgs& a, const GroupDev& Gm, int k_first, int64_t n0, int wave,
                                            T* lds) {
     const int gidx = (int)(&Gm - a.groups);
@@ -70,7 +74,7 @@ __device__ __forceinline__ void split_tile(const FwdArgs& a, const GroupDev& Gm,
             else run_forward_impl<T, M, false, UK, TSF, NMAP, TSFK == 3>(a, G, gidx, k_first, n0, ring);
         };
         if (wave > 0) {
-            produce<T, M, UK, NMAP>(a, G, k_first, n0, wave - 1, ring);
+            produce<T, M, UK, NMAP, PRODUCERS>(a, G, k_first, n0, wave - 1, ring);
         } else if constexpr (TSFK == 2) {
             if (a.tsf) consume(Bool<true>{});
             else consume(Bool<false>{});
@@ -93,16 +97,16 @@ __device__ __forceinline__ void split_item(const FwdArgs& a, int item, T* lds) {
     const GroupDev& G = a.groups[it.g];
     const int64_t n0 = *a.step0;
     if (MAX_M == 1 || G.M == 1) {
-        split_tile<T, 1, NMAP, TSFK>(a, G, it.k0, n0, wave, lds);
+        split_tile<T, 1, NMAP, TSFK, SplitWaves<T, MAX_M>::PRODUCERS>(a, G, it.k0, n0, wave, lds);
     } else if (MAX_M == 2 || G.M == 2) {
-        if constexpr (MAX_M >= 2) split_tile<T, 2, NMAP, TSFK>(a, G, it.k0, n0, wave, lds);
+        if constexpr (MAX_M >= 2) split_tile<T, 2, NMAP, TSFK, SplitWaves<T, MAX_M>::PRODUCERS>(a, G, it.k0, n0, wave, lds);
     } else if constexpr (MAX_M == 4) {
-        if (G.M == 3) split_tile<T, 3, NMAP, TSFK>(a, G, it.k0, n0, wave, lds);
-        else split_tile<T, 4, NMAP, TSFK>(a, G, it.k0, n0, wave, lds);
+        if (G.M == 3) split_tile<T, 3, NMAP, TSFK, SplitWaves<T, MAX_M>::PRODUCERS>(a, G, it.k0, n0, wave, lds);
+        else split_tile<T, 4, NMAP, TSFK, SplitWaves<T, MAX_M>::PRODUCERS>(a, G, it.k0, n0, wave, lds);
     }
 }
 
-template <typename T> constexpr int split_threads() { return WAVE * (1 + SplitWaves<T>::PRODUCERS); }
+template <typename T, int MAX_M> constexpr int split_threads() { return WAVE * (1 + SplitWaves<T, MAX_M>::PRODUCERS); }
 
 template <typename T, int NMAP, int MAX_M> constexpr int split_lds_bytes() {
     int lds = NoiseRing<T, 1, NMAP>::BYTES;
