@@ -649,6 +649,11 @@ __device__ __forceinline__ void run_hi(const FwdArgs& a, const GroupDev& G, int 
     if (w0) flush_clamps(clamps, a.clamps + (&G - a.groups));
 }
 
+// Wavefronts per SIMD that the registers leave room for. FP64 up to 10 beads: 188 registers
+// held a CU to two replicas, 168 (three spilled) to three: 600 replicas of 2 beads, 40
+// steps, 298 -> 178 us, 5000 1579 -> 1126.
+template <typename T, int NB> struct HiWaves { static constexpr int value = sizeof(T) == 4 ? 2 : NB == 2 ? 3 : 1; };
+
 // One kernel per register tile NB (16-row blocks of the tensor): the host
 // picks the smallest NB with 16 NB >= 3 N_max, so each instance gets its own
 // register allocation.
@@ -663,7 +668,7 @@ __device__ __forceinline__ void hi_item(const FwdArgs& a, int item, T* lds) {
 }
 
 template <typename T, int NB>
-__global__ __launch_bounds__(HI_THREADS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1)))
+__global__ __launch_bounds__(HI_THREADS) __attribute__((amdgpu_waves_per_eu(HiWaves<T, NB>::value)))
 void fwd_hi_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char hi_lds[];
     hi_item<T, NB>(a, (int)blockIdx.x, (T*)hi_lds);
@@ -671,7 +676,7 @@ void fwd_hi_kernel(FwdArgs a) {
 
 // Two contexts in one launch (see fwd_dual_kernel): blocks [0, n_items of a) run a.
 template <typename T, int NB>
-__global__ __launch_bounds__(HI_THREADS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1)))
+__global__ __launch_bounds__(HI_THREADS) __attribute__((amdgpu_waves_per_eu(HiWaves<T, NB>::value)))
 void fwd_hi_dual_kernel(FwdArgs a, FwdArgs b) {
     extern __shared__ __align__(16) unsigned char hi_lds[];
     if ((int)blockIdx.x < a.n_items) hi_item<T, NB>(a, (int)blockIdx.x, (T*)hi_lds);

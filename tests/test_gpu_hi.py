@@ -163,3 +163,26 @@ def test_hi_full_size_hi50_first_window_per_replica():
     e = [rel_err(psmp[0], op.samples()[0][0], fl), rel_err(smp[0, :2], orr.samples()[0][0], fl)]
     announce("hi50 window 0: parent rel err %.2e, replicas 0-1 rel err %.2e" % tuple(e))
     assert max(e) < 1e-4
+
+
+def test_hi_three_short_fp64_replicas_share_a_cu():
+    # 600 replicas of 2 beads on 256 CUs: three workgroups to a CU at once, 1.2 times
+    # the time of 256 replicas; with registers for two it was 2.0
+    import time
+    import torch
+    best = {}
+    for R in (256, 600):
+        g = wl.group(2, R, 1e-4, wl.FENE, 1.0, 50.0, wl.UNIAXIAL, 0.02, hi_radius=0.25)
+        rep = run_gpu([g], [wl.equilibrium_parent(2, wl.FENE, 1.0, 50.0, seed=1)], 3, 40, 20, max_windows=1000, precision=64)
+        best[R] = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(5):
+                rep.step(80)
+            torch.cuda.synchronize()
+            best[R] = min(best[R], time.perf_counter() - t)
+        rep.sync_status()
+        rep.close()
+    announce("HI, 2 beads in FP64: 256 replicas %.0f us, 600 %.0f us" % (best[256] * 1e5, best[600] * 1e5))
+    assert best[600] < 1.6 * best[256]
