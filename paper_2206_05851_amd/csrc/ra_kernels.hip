@@ -414,6 +414,8 @@ hipError_t launch_reset(int32_t* status, unsigned long long* clamps, int n_group
     return hipGetLastError();
 }
 
+constexpr int64_t INIT_BLOCKS = 4096;
+
 // Fused path: everything that starts a run, in one launch or, with several groups,
 // after a reset.
 hipError_t launch_init(const GroupDev* groups, int n_groups, int64_t max_elems, const double* parent,
@@ -424,7 +426,12 @@ hipError_t launch_init(const GroupDev* groups, int n_groups, int64_t max_elems, 
         const hipError_t e = launch_reset(status, clamps, n_groups, step, st);
         if (e != hipSuccess) return e;
     }
-    dim3 grid((unsigned)std::min<int64_t>((max_elems + 255) / 256, 4096), (unsigned)n_groups), block(256);
+    // one thread per bond of the largest group (max_elems counts its bead coordinates), with
+    // many groups a loop over them: 512 groups of 100 replicas of 100 beads, a thread per
+    // coordinate 36.9 us, per bond 27.1, with the limit 21.3; 2000 groups 124, 89, 64
+    const int64_t most = std::max<int64_t>(8, INIT_BLOCKS / n_groups);
+    const int64_t blocks = std::min<int64_t>({(max_elems / 3 + 255) / 256, most, 4096});
+    dim3 grid((unsigned)std::max<int64_t>(1, blocks), (unsigned)n_groups), block(256);
     if (precision == 64)
         hipLaunchKernelGGL(clone_kernel<double>, grid, block, 0, st, groups, parent, par_off, (double*)state, tsf_acc,
                            status, clamps, step, src);
