@@ -508,7 +508,6 @@ ra_status ra_init_chains(ra_ctx* c, const double* parent_xyz) {
         HIPCHK(c, launch_reset(c->status, c->clamps, ng, c->dstep, c->stream));
         HIPCHK(c, launch_clone_plain(c->dgroups, ng, c->max_group_elems, parent_xyz, c->dpar_off, c->pos[0],
                                      c->tsf_acc, c->status, c->run.precision, c->stream));
-        HIPCHK(c, launch_src_from_xyz(c->dgroups, ng, parent_xyz, c->dpar_off, c->src, c->stream));
     } else {
         HIPCHK(c, launch_init(c->dgroups, ng, c->max_group_elems, parent_xyz, c->dpar_off, c->state, c->tsf_acc,
                               c->status, c->clamps, c->dstep, c->src, c->run.precision, c->stream));

@@ -136,8 +136,6 @@ hipError_t launch_reclone(const GroupDev* groups, const GroupDev* pgroups, int n
                           const void* pstate, void* state, double* tsf_acc, int32_t* status, const int64_t* par_off,
                           double* src, int64_t* step, int64_t step_value, int64_t* parent_step, int64_t parent_steps,
                           int precision, hipStream_t st);
-hipError_t launch_src_from_xyz(const GroupDev* groups, int n_groups, const double* parent, const int64_t* par_off,
-                               double* src, hipStream_t st);
 hipError_t launch_conformation(const GroupDev* groups, int n_groups, const int64_t* rep_off, int64_t n_reps,
                                const void* state, const int64_t* par_off, const double* src, double* dbar,
                                double* d_bead, double* rg2, double* src_rg2, int precision, hipStream_t st);

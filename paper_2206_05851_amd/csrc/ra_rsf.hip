@@ -76,15 +76,6 @@ __device__ void com_frame_from_bonds(const T* bonds, int N, double* out, int lan
     }
 }
 
-// Clone source from FP64 bead positions.
-__global__ __launch_bounds__(64) void src_from_xyz_kernel(const GroupDev* __restrict__ groups,
-                                                          const double* __restrict__ parent,
-                                                          const int64_t* __restrict__ par_off,
-                                                          double* __restrict__ src) {
-    const int64_t o = par_off[blockIdx.x];
-    clone_source(parent + o, src + o, groups[blockIdx.x].N);
-}
-
 // ---------------------------------------------------------------------------
 // Re-clone: state of every replica of group g := replica 0 of the parent
 // context's group g. A FENE bond at or past full extension (or non-finite)
@@ -678,13 +669,6 @@ hipError_t launch_reclone(const GroupDev* groups, const GroupDev* pgroups, int n
     else
         hipLaunchKernelGGL(reclone_kernel<float>, grid, block, 0, st, groups, pgroups, (const float*)pstate,
                            (float*)state, tsf_acc, status, par_off, src, step, step_value, parent_step, parent_steps);
-    return hipGetLastError();
-}
-
-hipError_t launch_src_from_xyz(const GroupDev* groups, int n_groups, const double* parent, const int64_t* par_off,
-                               double* src, hipStream_t st) {
-    (void)hipGetLastError();   // report only this launch's own error
-    hipLaunchKernelGGL(src_from_xyz_kernel, dim3((unsigned)n_groups), dim3(64), 0, st, groups, parent, par_off, src);
     return hipGetLastError();
 }
 
