@@ -674,13 +674,16 @@ void fwd_hi_kernel(FwdArgs a) {
     hi_item<T, NB>(a, (int)blockIdx.x, (T*)hi_lds);
 }
 
-// Two contexts in one launch (see fwd_dual_kernel): blocks [0, n_items of a) run a.
+// Two contexts in one launch (see fwd_dual_kernel): blocks [0, n_items of a) run a. One
+// body for both: with a copy each, NB = 12 in FP64 had every register taken, and the
+// compiler saved one of b's addresses where the threads with tid >= n were masked off:
+// parents of two block rows or more became NaN.
 template <typename T, int NB>
 __global__ __launch_bounds__(HI_THREADS) __attribute__((amdgpu_waves_per_eu(HiWaves<T, NB>::value)))
 void fwd_hi_dual_kernel(FwdArgs a, FwdArgs b) {
     extern __shared__ __align__(16) unsigned char hi_lds[];
-    if ((int)blockIdx.x < a.n_items) hi_item<T, NB>(a, (int)blockIdx.x, (T*)hi_lds);
-    else hi_item<T, NB>(b, (int)blockIdx.x - a.n_items, (T*)hi_lds);
+    const bool first = (int)blockIdx.x < a.n_items;
+    hi_item<T, NB>(first ? a : b, (int)blockIdx.x - (first ? 0 : a.n_items), (T*)hi_lds);
 }
 
 // Register tile of the kernel instance launched for nb = ceil(3 N_max / 16).

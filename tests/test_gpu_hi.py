@@ -129,6 +129,39 @@ def test_hi_rsf_cycle_matches_oracle():
     assert max(e) < 1e-4
 
 
+@pytest.mark.parametrize("N", [10, 21, 32, 42, 53, 54, 60, 64])
+@pytest.mark.parametrize("precision", [32, 64])
+def test_hi_cycle_of_each_tile_matches_oracle(N, precision):
+    # Parents and replicas in one launch, the last and first chain length of a register
+    # tile and the longest chain that fits, beside a chain of one block row. 3 windows
+    # of 10 steps; tolerances as for the same tiles in single launches.
+    from oracle import ora
+    from paper_2206_05851_amd import ra
+    if not _fits(N, precision):
+        pytest.skip("N=%d at precision %d needs more LDS than the device's" % (N, precision))
+    gs = [wl.group(n, 3, 1e-3, wl.HOOKEAN, 1.0, 0.0, wl.SHEAR, 0.3, hi_radius=0.4, stream_id=i)
+          for i, n in enumerate((4, N))]
+    ps = [_parent(g, i + 1) for i, g in enumerate(gs)]
+    S, P, W = 10, 8, 3
+    announce("hi cycle N=%d precision %d" % (N, precision))
+    par = ra.Replicas([dict(g, n_replicas=1) for g in gs], 7, sample_every=P, max_windows=W, tsf=True, noise_tag=1,
+                      precision=precision)
+    par.init_chains(ps)
+    rep = ra.Replicas(gs, 7, sample_every=S, max_windows=W, precision=precision)
+    rep.rsf_cycle(par, W, P)
+    op = ora.Oracle([dict(g, n_replicas=1) for g in gs], 7, P, W, tsf=True)
+    op.set_tag(ora.TAG_PARENT)
+    op.init_chains(ps)
+    orr = ora.Oracle(gs, 7, S, W)
+    orr.rsf_cycle(op, W, P)
+    par.sync_status()
+    rep.sync_status()
+    e = [rel_err(a.cpu().numpy(), b, 1.0) for r, o in ((par, op), (rep, orr)) for a, b in zip(r.samples(), o.samples())]
+    e += [rel_err(a.cpu().numpy(), b, 1.0) for a, b in zip(par.samples(tsf=True)[1], op.samples(tsf=True)[1])]
+    announce("samples and tsf " + " ".join("%.1e" % x for x in e))
+    assert max(e) < (1e-4 if precision == 32 else 1e-10)
+
+
 def test_hi_full_size_hi50_first_window_per_replica():
     # The hi50 workload in full (the paper's model with HI: 50 replicas and the
     # parent, 4 windows of 750 steps), launched as bench.py runs it (parent on
