@@ -118,9 +118,14 @@ typedef struct {
     int32_t  max_steps;         /* steps since ra_init_chains the checkpoints must hold */
     int32_t  plain;             /* 1: plain path, one launch per step, state in HBM */
     int32_t  use_graph;         /* 1: capture ra_step's launch sequence in a hipGraph */
-    int32_t  tile_policy;       /* 0 cost model; 1 autotune by timing; 1000 + m: force
+    int32_t  tile_policy;       /* 0 cost model; 1 autotune by timing (a work list that does
+                                   not fill the chip at its own size); 1000 + m: force
                                    m beads per lane where legal (m <= 16) */
-    int32_t  waves_per_block;   /* 0 = default (4) */
+    int32_t  waves_per_block;   /* wavefronts per workgroup, 1, 2 or 4; 0 = default (4). No effect
+                                   where a kernel sets its own: short work lists (noise drawn
+                                   by further wavefronts, or a pair-model item shared by
+                                   several) and HI; the two contexts of a one-launch cycle
+                                   need the same value */
     int32_t  noise_tag;         /* 0: replica noise; 1: parent trajectory (RSF cycle, Sec. II) */
     int32_t  noise_map;         /* 0: one Philox block per (step, bead), three normals;
                                    1: each block gives four normals (both of Box-Muller's
@@ -239,7 +244,8 @@ RA_API ra_status ra_mftu(ra_ctx* ctx, const double* rate_sum, int64_t n_windows,
  * total rate K it estimates S dt / (1 - exp(-K S dt)) = 1/K + S dt/2 + ...
  * rates: device FP64 [n_windows][sum_g(N_g-1)] from ra_bell_rates;
  * first_window: device int64 [n_trials][n_groups] (first window or -1);
- * mftu: device FP64 [n_groups]. 1 <= n_trials <= 65535, 1 <= max_windows < 2^32. */
+ * mftu: device FP64 [n_groups], which holds the call's work queues until the
+ * result is written (calls on one context may overlap). 1 <= n_trials <= 65535, 1 <= max_windows < 2^32. */
 RA_API ra_status ra_mftu_events(ra_ctx* ctx, const double* rates, int64_t n_windows, int32_t n_trials,
                                 int64_t max_windows, int64_t* first_window, double* mftu);
 

@@ -26,7 +26,9 @@
 
 namespace ra {
 
-// g, s and the guard flag, computed exactly as the forward computes g.
+// g, s and the guard flag by the forward's law and FP64 guard. The forward folds cF into its
+// reciprocal (fene_force), so the two round differently by a few ulp / (1 - s), and
+// bonds within that of s = 0.9 may take the FP64 branch in one only.
 template <bool FENE>
 __device__ __forceinline__ void factor_gs(float qx, float qy, float qz, const GroupDev& G, float& g, float& s,
                                           bool& smooth) {
@@ -98,8 +100,7 @@ __device__ __forceinline__ void inject(const Lane<float, M>& q, const bool (&val
     }
 }
 
-// FP32 partial sums of one reverse sweep (a segment, or one step when every
-// state is kept), turned into the (rate, H, b) gradient terms by rev_flush:
+// FP32 partial sums of at most 128 steps of a reverse sweep, turned into the (rate, H, b) gradient terms by rev_flush:
 //   rate: lambda . d(dt kappa Q)/d rate = dt (fx Sxx + fy Syy + fz Szz + fxz Sxz)
 //         with (fx, fy, fz, fxz) the flow pattern and S_ab = sum lambda_a Q_b;
 //   H:    dtz (S1 + S2), b: -cF S2 / b, with S1 = sum g mu.Q and
@@ -186,9 +187,8 @@ template <int M, bool FENE, int NMAP, bool MANY>
 __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G, int item, int k_first) {
     // kernel arguments into locals (the loops must not address the argument block)
     const int S = a.S, K = a.K;
-    const int64_t n_end = a.n_end, ckpt_total = a.ckpt_total, spr_total = a.spr_total;
+    const int64_t n_end = a.n_end, ckpt_total = a.ckpt_total;
     const float* const ckpt = ckpt_item<const float, M>((const float*)a.ckpt, G, k_first);
-    const double* const lam_mu = a.lam_mu;
     float* const seg = a.segbuf + a.seg_off[item];
     double* const partial = a.partial + 3 * item;
     const TileGeom tg = tile_geom(G, k_first, M);
@@ -399,8 +399,6 @@ __device__ __forceinline__ void run_adjoint(const AdjArgs& a, const GroupDev& G,
         }
         sweep(seg, STRIDE, s0, s1 - 1, read_seg);
     }
-    (void)spr_total;
-    (void)lam_mu;
     gr = wave_sum(gr);
     gH = wave_sum(gH);
     gb = wave_sum(gb);

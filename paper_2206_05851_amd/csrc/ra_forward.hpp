@@ -20,9 +20,6 @@ namespace ra {
 // ---------------------------------------------------------------------------
 // Fused persistent forward: all n_steps of one work item in registers.
 // ---------------------------------------------------------------------------
-// Noise run-ahead per beads-per-lane: with one bead per lane the wave has
-// little independent work per step, so U steps of noise (U independent Philox
-// chains per lane) are generated before the U physics steps consume them.
 // Noise from other wavefronts of the workgroup (split forward, fwd_split_kernel):
 // a ring of two chunks of BLOCKS Philox blocks in LDS, transformed (radius and
 // sines as polars4 gives them) by the producing wavefronts. Each chunk starts
@@ -79,6 +76,9 @@ struct OwnNoise {
     template <typename... A> __device__ void get(A&&...) const {}
 };
 
+// Noise run-ahead per beads-per-lane: with one bead per lane the wave has
+// little independent work per step, so U steps of noise (U independent Philox
+// chains per lane) are generated before the U physics steps consume them.
 template <int M> struct RunAhead { static constexpr int U = M == 1 ? 4 : (M == 2 ? 2 : 1); };
 
 // Fused persistent forward over all n_steps of one work item. The step loop is

@@ -364,8 +364,9 @@ static dim3 grid1d(int64_t n, int block) {
 // against the one-wavefront kernels, 500 steps, time ratio (above 1: split faster)
 // at 256 / 512 / 768 / 1024 / 1536 items: FP32 one bead per lane 1.36 / 1.19 / 1.10 /
 // 1.02 / 1.02 (noise map 1: 1.31 / 1.33 / 1.18 / 1.10 / 1.14; at 2048 0.95), two
-// 1.58 / 1.35 / 0.95, three and four 1.78 / 1.03 / 0.75 (their rings leave one or two
-// workgroups per CU); FP64 2.7-3.2 / 1.6-1.7 / 1.1-1.3 / 0.83-1.02.
+// 1.58 / 1.35 / 0.95, three and four 1.78 / 1.03 / 0.75 (two workgroups fit a CU beside the
+// rings of two beads per lane, one beside those of four); FP64 2.7-3.2 / 1.6-1.7 / 1.1-1.3
+// / 0.83-1.02, three and four beads per lane see SplitWaves.
 static bool split_forward(int n_items, int precision, int family, int max_m) {
     return family == 4 && n_items <= (precision == 64 ? 768 : max_m == 1 ? 1536 : 512);
 }

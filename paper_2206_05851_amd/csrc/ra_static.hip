@@ -137,7 +137,7 @@ extern "C" ra_status ra_run_static(const ra_chain_desc* group, const ra_run_desc
     const size_t o_status = off;  off = align256(off + sizeof(int32_t));
     const size_t o_clamps = off;  off = align256(off + sizeof(unsigned long long));
     const size_t o_step = off;    off = align256(off + sizeof(int64_t));
-    off = align256(off + sizeof(int64_t));   // unused: the limit stays where it was
+    off += 256;   // counted in the limit that callers meet, and empty
     const size_t o_state = off;   off = align256(off + esz * (size_t)state_total);
     const size_t o_items = off;
     const double smp_bytes = (double)esz * (double)smp_total * (double)W;
