@@ -83,8 +83,8 @@ SLOTS_PER_BEAD_STEP = {0: 32 + 8 + 2 + 24, 1: 24 + 6 + 1.5 + 24, 2: 24 + 6 + 1.5
 # launch tile (beads per lane, replicas per wavefront, kernel family) and the
 # noise map are recorded with the figure, and traffic is reported as null when
 # any of them differs.
-FWD_TRAFFIC = {"sha256": "2d1aaed9014de8b9c2af1dae69891dfeff021719728b0186737188bbab48ae0c", "noise_map": 2,
-               "tile": (16, 1, 16), "bytes": (48753.5 * 2.0 + 2655976.406) * 1024}
+FWD_TRAFFIC = {"sha256": "5f049bd8617e362b5032aeb869e25633e736cf427e8e68b075019a5e8973e586", "noise_map": 2,
+               "tile": (16, 1, 16), "bytes": (48749.104 * 2.0 + 2655995.458) * 1024}
 FWD_SOURCES = ("ra_fwd_wide.hip", "ra_forward.hpp", "ra_chain.hpp", "ra_device.hpp", "ra_types.hpp", "ra_launch.hpp")
 
 
@@ -97,14 +97,18 @@ def fwd_sources_digest(files=FWD_SOURCES):
     return h.hexdigest()
 
 
-# The pair kernel's lane-slots per replica*bead*step on collapsed50 (N = 50):
-# non-transcendental VALU instructions per replica-step (one bead per lane, two
-# wavefronts per replica) of fwd_pair_shared_kernel<float, 2>, from rocprofv3 --pmc
-# SQ_INSTS_VALU SQ_INSTS_VALU_TRANS_F32 SQ_WAVES: (732,517,773 - 45,066,518) / 1001
-# replicas / 750 steps. It holds for the pair kernel sources with this digest only.
+# The pair model's lane-slots per replica*bead*step at collapsed50's N = 50:
+# non-transcendental VALU instructions per replica-step (one bead per lane), from
+# rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_VALU_TRANS_F32 SQ_WAVES. "slots", what the
+# fraction is taken of, is the one-wavefront kernel's (fwd_pair_kernel<float>, 2048
+# replicas); "issued" is what fwd_pair_shared_kernel<float, 2>, which the cycle runs,
+# issues over a replica's two wavefronts (1001 replicas): both of them do the springs,
+# the noise and the update. 750 steps each. They hold for the pair kernel sources with
+# this digest only.
 PAIR_SOURCES = ("ra_pair.hip", "ra_chain.hpp", "ra_device.hpp", "ra_dpp.hpp")
-PAIR_SLOTS = {"sha256": "30fd29552ee7f10cb4b486fab8663ff9f3f061971bb159b03832015963e8e455",
-              "slots": (732517773.0 - 45066518.0) / 1001 / 750}
+PAIR_SLOTS = {"sha256": "c32a3f57fc587e5faf15013288fc5393efe431e21eeac504cb1d6aed210e4c3c",
+              "slots": (1341286400.0 - 89094144.0) / 2048 / 750,
+              "issued": (732448704.0 - 45066518.0) / 1001 / 750}
 FP32_VECTOR_PEAK = 157.3e12   # FLOP/s, packed FP32 included
 
 
@@ -369,7 +373,8 @@ def rsf_cycle_bench(workload, desc, dev, name, noise_map=0):
     else:
         pair = g0.get("lj_eps", 0.0) > 0.0 or g0["spring"] == 2
         if pair:
-            slots = PAIR_SLOTS["slots"] if fwd_sources_digest(PAIR_SOURCES) == PAIR_SLOTS["sha256"] else None
+            known = fwd_sources_digest(PAIR_SOURCES) == PAIR_SLOTS["sha256"]
+            slots, issued = (PAIR_SLOTS["slots"], PAIR_SLOTS["issued"]) if known else (None, None)
         else:
             slots = SLOTS_PER_BEAD_STEP[noise_map]
         rate = (g0["n_replicas"] + 1) * g0["n_beads"] * rS * rW / t
@@ -378,8 +383,12 @@ def rsf_cycle_bench(workload, desc, dev, name, noise_map=0):
                            "achieved": None if slots is None else slots * rate / 1e12,
                            "frac": None if slots is None else slots * rate / VALU_PEAK_LANE_SLOTS,
                            "note": "over the cycle's wall time, the parent included; "
-                                   + ("pair kernel slots measured by counters at N = 50" if pair
+                                   + ("slots of the one-wavefront pair kernel, by counters at N = 50" if pair
                                       else "the chain kernels' slot count")}
+        if pair and issued is not None:
+            res["roofline"]["issued"] = {"lane_slots_per_replica_bead_step": issued,
+                                         "frac": issued * rate / VALU_PEAK_LANE_SLOTS,
+                                         "note": "what a replica's two wavefronts issue, work done by both included"}
     log("%s: %.2f ms per cycle (%.1f us per window)" % (name, 1e3 * t, 1e6 * t / rW))
     return res
 
