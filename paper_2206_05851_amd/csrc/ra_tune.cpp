@@ -107,7 +107,8 @@ struct Entry {
     int M;
     double ms_per_replica;
 };
-constexpr int TUNE_WAVES_PER_SIMD = 4;             // timing runs fill every SIMD this many times
+constexpr int TUNE_WAVES_PER_SIMD = 4;             // timing runs fill every SIMD at least this many times
+constexpr double TUNE_TILE_GAIN = 0.97;            // a tile other than the cost model's has to be this much faster
 
 // The process keeps one table of results per cache file (the empty path when
 // RA_AUTOTUNE_CACHE is unset): the library's only process-wide state. Tuning
@@ -158,9 +159,12 @@ void append_cache_file(const std::string& path, const Key& k, const Entry& e) {
 
 // Time 96 fused steps of one group with a forced tile M of the batch's kernel
 // family (a short chain in a wide-lane batch runs the wide-lane kernels). few = 0:
-// enough replicas to give every SIMD TUNE_WAVES_PER_SIMD wavefronts of that packing, so the
-// candidates are ranked by throughput (as in a saturated batch), not by the
-// latency of a few wavefronts. few > 0: that many replicas, those of a batch that
+// enough replicas to give every SIMD TUNE_WAVES_PER_SIMD wavefronts of the densest
+// packing, so the candidates are ranked by throughput (as in a saturated batch), not by
+// the latency of a few wavefronts. It is the same number for all: with four wavefronts
+// of its own packing the narrowest tile ran the shortest, and its launch and its last
+// wavefronts weighed the most (64 beads, 12500 replicas, noise map 1: M = 4 chosen, 3.79
+// ms for 2000 steps, M = 1 2.90). few > 0: that many replicas, those of a batch that
 // does not fill the chip, whose kernels and best tiles are others (40 beads, 300
 // replicas, 400 steps: the saturated ranking's M = 2 135 us, M = 1 67). Returns ms per
 // replica, or -1.
@@ -169,8 +173,10 @@ double time_tile(const ra_chain_desc& d, const ra_run_desc& run, int family, int
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    const int lanes = (d.n_beads + M - 1) / M;
-    const int per_wave = std::max(1, 64 / lanes);
+    int per_wave = 1;
+    for (int m : family_beads_per_lane(family))
+        if (legal(d.n_beads, m) && map_allows(run.noise_map, m))
+            per_wave = std::max(per_wave, 64 / ((d.n_beads + m - 1) / m));
     ra_chain_desc g = d;
     g.n_replicas = few > 0 ? few : TUNE_WAVES_PER_SIMD * 4 * cus * per_wave;
     // a short list's launch is short: the best of three times as many steps each
@@ -262,6 +268,7 @@ ra_status autotune_tiles(const std::vector<ra_chain_desc>& descs, const ra_run_d
                 it = table.find(Key{d.n_beads, d.spring, run.precision, family, wpb, run.noise_map, ANY_ITEMS});
             if (it == table.end()) {
                 Entry best{Ms[i], -1.0};
+                double keep = -1.0;   // time of the cost model's tile
                 for (int M : family_beads_per_lane(family)) {
                     if (!legal(d.n_beads, M) || !map_allows(run.noise_map, M)) continue;
                     // a short list: as many of these chains as make up the whole batch
@@ -269,7 +276,9 @@ ra_status autotune_tiles(const std::vector<ra_chain_desc>& descs, const ra_run_d
                     const double ms = time_tile(d, run, family, M, wpb, replicas, stream);
                     if (ms < 0) { why = "timing run failed"; return RA_EDEVICE; }
                     if (best.ms_per_replica < 0 || ms < best.ms_per_replica) best = Entry{M, ms};
+                    if (M == Ms[i]) keep = ms;
                 }
+                if (!few && keep >= 0 && best.ms_per_replica > TUNE_TILE_GAIN * keep) best = Entry{Ms[i], keep};
                 it = table.emplace(k, best).first;
                 append_cache_file(path, k, best);
             }

@@ -29,9 +29,10 @@ std::vector<int> choose_tiles(const ra_chain_desc* groups, int n_groups, int fam
                               int nmap);
 
 // Times every legal M for each distinct (N, spring) of the batch with a short
-// run of the fused kernel and keeps the fastest per replica: a run that fills every
-// SIMD four times, or for a work list of at most 2048 items one of the batch's
-// size. With waves_per_block = 0 on entry it also tries 1, 2
+// run of the fused kernel and keeps the fastest per replica: a run of as many replicas
+// for each M, that fills every SIMD at least four times (another tile than the cost
+// model's has to be 3% faster), or for a work list of at most 2048 items one of the
+// batch's size. With waves_per_block = 0 on entry it also tries 1, 2
 // and 4 wavefronts per workgroup and returns the size whose tiles give the
 // least predicted batch time (sum over groups of R x time per replica).
 // Results are kept per process and, if RA_AUTOTUNE_CACHE names a file, in that
